@@ -44,8 +44,8 @@ void free_plan(rmsynth_plan_s* p)
 {
     if (!p) return;
     free_plan(p->adj);
-    void* bufs[] = {p->d_b, p->d_lambda2, p->d_w, p->d_phi, p->d_base, p->d_Tbf[0], p->d_Tbf[1],
-                    p->d_Thf[0], p->d_Thf[1], p->d_nufft_rot, p->d_nufft_off, p->d_nufft_ent,
+    void* bufs[] = {p->d_b, p->d_lambda2, p->d_w, p->d_phi, p->d_base, p->d_Tbf, p->d_Thf, p->d_Tf32,
+                    p->d_nufft_rot, p->d_nufft_off, p->d_nufft_ent,
                     p->d_nufft_tw, p->d_nufft_deconv, p->d_kw, p->d_kbase, p->d_krot,
                     p->d_Kbf[0], p->d_Kbf[1], p->d_Khf[0], p->d_Khf[1], p->d_ew,
                     p->d_Ebf[0], p->d_Ebf[1], p->d_Ehf[0], p->d_Ehf[1]};
@@ -54,7 +54,7 @@ void free_plan(rmsynth_plan_s* p)
     delete p;
 }
 
-// The factored kernels evaluate F at phi_0 + k dphi, dphi = (phi_last -
+// The mirrored-pair kernels evaluate F at phi_0 + k dphi, dphi = (phi_last -
 // phi_0) / (nphi - 1), and report the caller's phi_k.  A grid is treated as
 // uniform when the phase this moves, 2 |phi_k - (phi_0 + k dphi)| |a_j| of
 // eq. (11), stays below kUniformPhaseTol radians for every k and every
@@ -70,21 +70,20 @@ bool detect_uniform(const double* phi, int32_t nphi, double amax, double* phi0, 
     return 2.0 * dev * amax <= kUniformPhaseTol;
 }
 
-int build_factor_tables(rmsynth_plan_s* p)
+int build_mirror_tables(rmsynth_plan_s* p)
 {
-    p->ftiles = (int32_t)((p->nphi + kFactorTile - 1) / kFactorTile);
-    const size_t nT = (size_t)(p->nchan_pad / 4) * kFactorTile;
+    p->ftiles = (int32_t)((p->nphi + kMirrorTile - 1) / kMirrorTile);
+    const size_t nT = (size_t)((p->nchan + kMirrorChan - 1) / kMirrorChan) * 1024;
     hipError_t e;
     if ((e = hipMalloc(&p->d_base, sizeof(float2) * (size_t)p->ftiles * p->nchan_pad)) != hipSuccess ||
-        (e = hipMalloc(&p->d_Tbf[0], sizeof(uint4) * nT)) != hipSuccess ||
-        (e = hipMalloc(&p->d_Tbf[1], sizeof(uint4) * nT)) != hipSuccess ||
-        (e = hipMalloc(&p->d_Thf[0], sizeof(uint4) * nT)) != hipSuccess ||
-        (e = hipMalloc(&p->d_Thf[1], sizeof(uint4) * nT)) != hipSuccess)
+        (e = hipMalloc(&p->d_Tbf, sizeof(uint4) * nT)) != hipSuccess ||
+        (e = hipMalloc(&p->d_Thf, sizeof(uint4) * nT)) != hipSuccess ||
+        (e = hipMalloc(&p->d_Tf32, sizeof(uint4) * nT)) != hipSuccess)
         return rms_fail(RMSYNTH_ENOMEM, "rmsynth_plan: hipMalloc (phase tables): %s", hipGetErrorString(e));
     hipStream_t s = nullptr;
     if ((e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking)) != hipSuccess)
         return rms_hip_fail(e, "rmsynth_plan: hipStreamCreate");
-    e = launch_factor_tables(*p, s);
+    e = launch_mirror_tables(*p, s);
     hipError_t e2 = hipStreamSynchronize(s);
     (void)hipStreamDestroy(s);
     if (e != hipSuccess) return rms_hip_fail(e, "rmsynth_plan: phase-table kernel");
@@ -115,7 +114,6 @@ int build_etable(rmsynth_plan_s* p)
     if (e != hipSuccess) return rms_hip_fail(e, "rmsynth_plan: phase-table kernel");
     if (e2 != hipSuccess) return rms_hip_fail(e2, "rmsynth_plan: phase-table kernel");
     p->etab = true;
-    p->ftiles = (int32_t)((p->nphi + kFactorTile - 1) / kFactorTile);  // peak records per LOS: 2 ftiles
     return RMSYNTH_OK;
 }
 
@@ -157,7 +155,7 @@ int build_adjoint_plan(rmsynth_plan_s* p, const double* lambda2, const double* p
         (e = hipMemcpy(q->d_phi, hgrid.data(), sizeof(double) * q->nphi_pad, hipMemcpyHostToDevice)) != hipSuccess)
         return rms_hip_fail(e, "rmsynth_plan: hipMemcpy (adjoint)");
     q->uniform = detect_uniform(hgrid.data(), q->nphi, amax, &q->phi0, &q->dphi);
-    if (q->uniform) return build_factor_tables(q);
+    if (q->uniform) return build_mirror_tables(q);
     // A uniform phi grid makes the contracted axis uniform: the channel-factored
     // tables then replace per-element phase generation (same phase tolerance,
     // now over every output lambda^2).
@@ -283,7 +281,7 @@ int rmsynth_plan(const double* lambda2, const double* weights, int32_t nchan, co
         if (weights[j] > 0.0) amax = std::max(amax, std::fabs(lambda2[j] - p->lambda0_sq));
     p->uniform = detect_uniform(phi, nphi, amax, &p->phi0, &p->dphi);
     if (p->uniform) {
-        if (int rc = build_factor_tables(p)) {
+        if (int rc = build_mirror_tables(p)) {
             free_plan(p);
             return rc;
         }
@@ -459,8 +457,8 @@ int run_execute(const rmsynth_plan_s* p, const float* Q, const float* U, int64_t
             if (e != hipSuccess) return rms_hip_fail(e, who);
         }
         hipError_t e;
-        if (precision == RMSYNTH_FP32) e = launch_synth_fp32(*p, a);
-        else if (p->uniform) e = launch_synth_factored(*p, a, precision);
+        if (p->uniform) e = launch_synth_mirrored(*p, a, precision);
+        else if (precision == RMSYNTH_FP32) e = launch_synth_fp32(*p, a);
         else if (p->cuniform && layout == RMSYNTH_LOS_MAJOR && !parts && !recs)
             e = launch_synth_kfactored(*p, a, precision);
         else if (p->etab) e = launch_synth_etable(*p, a, precision);

@@ -31,18 +31,19 @@ struct rmsynth_plan_s {
     double* d_lambda2;   // [nchan] lambda^2 as given
     float* d_w;
     double* d_phi;
-    // Factored phase tables, present when the phi grid is uniform
-    // (phi_k = phi_0 + k dphi).  With tiles of kFactorTile phi,
-    //   exp(-i theta_{j,k0+m}) = exp(-i theta_{j,k0}) * exp(-2i a_j m dphi):
-    //   d_base [ftiles][nchan_pad] float2  K w_j (cos, sin)(theta_{j,k0}), k0 = tile start
-    //   d_T{bf,hf}[hi/lo] [nchan_pad/4][kFactorTile] uint4: 4 channels x (cos, sin)
-    //                   of 2 a_j m dphi, split into 16-bit hi/lo (bfloat16, half)
+    // Mirrored-pair tables (synth_mirrored.hip), present when the phi grid is
+    // uniform (phi_k = phi_0 + k dphi), in tiles of kMirrorTile phi:
+    //   d_base [ftiles][nchan_pad] float2  K w_j (cos, sin)(2 a_j phi_c), phi_c the tile's centre
+    //   d_T{bf,hf,32} [K-steps][4][4][64] uint4: (cos, sin)(2 a_j (i + 1/2) dphi) of 16
+    //                   channels x 128 pairs in MFMA operand order, split into 16-bit
+    //                   hi/lo (bfloat16, half) or FP32
     bool uniform;
     double phi0, dphi;
     int32_t ftiles;
     float2* d_base;
-    uint4* d_Tbf[2];
-    uint4* d_Thf[2];
+    uint4* d_Tbf;
+    uint4* d_Thf;
+    uint4* d_Tf32;
     bool any_flagged;    // some channel has weight 0
     // Channel-factored tables (synth_factored.hip, KF), present when the
     // contracted axis is uniform, b_j = kb0 + j kdb, and the output grid is
@@ -92,6 +93,8 @@ hipError_t launch_nufft(const rmsynth_plan_s& p, const float* Q, const float* U,
                         float* Fq, float* Fu, float* Fabs, hipStream_t s);
 
 constexpr int kFactorTile = 128;  // phi per tile of the factored kernels
+constexpr int kMirrorTile = 256;  // phi per tile of the mirrored-pair kernels
+constexpr int kMirrorChan = 16;   // channels per K-step of the mirrored-pair kernels
 constexpr int kKTile = 96;        // channels per K-tile of the channel-factored form
 constexpr size_t kEtabMaxBytes = size_t(256) << 20;  // largest explicit phase table (4 arrays)
 
@@ -247,9 +250,9 @@ struct ExecArgs {
 
 hipError_t launch_synth_fp32(const rmsynth_plan_s& p, const ExecArgs& a);
 hipError_t launch_synth_split(const rmsynth_plan_s& p, const ExecArgs& a, int precision);
-hipError_t launch_synth_factored(const rmsynth_plan_s& p, const ExecArgs& a, int precision);
+hipError_t launch_synth_mirrored(const rmsynth_plan_s& p, const ExecArgs& a, int precision);
 hipError_t launch_los_scale(const rmsynth_plan_s& p, const ExecArgs& a);
-hipError_t launch_factor_tables(const rmsynth_plan_s& p, hipStream_t s);
+hipError_t launch_mirror_tables(const rmsynth_plan_s& p, hipStream_t s);
 hipError_t launch_kfactor_tables(const rmsynth_plan_s& p, hipStream_t s);
 hipError_t launch_synth_kfactored(const rmsynth_plan_s& p, const ExecArgs& a, int precision);
 hipError_t launch_etable(const rmsynth_plan_s& p, hipStream_t s);

@@ -1,15 +1,22 @@
-// Faraday-depth transform on a uniform phi grid with a factored phase matrix.
+// Split-precision contraction against a phase table, for plans whose output
+// grid is not uniform (uniform output grids: synth_mirrored.hip).
 //
-// For phi_k = phi_0 + k dphi and a tile of NT phi starting at k0,
-//   exp(-i theta_{j,k0+m}) = exp(-i theta_{j,k0}) * exp(-2i a_j m dphi),
-// so (eqs. (11), (13))
-//   F_l(k0 + m) = sum_j [K w_j X_lj exp(-i theta_{j,k0})] T_jm,
-//   T_jm = exp(-2i a_j m dphi).
-// The bracket is a per-channel rotation of the data, applied while the Q/U
-// tile is packed into LDS; T does not depend on the tile and is a table of
-// nchan x NT entries built once per plan (FP64 argument reduction, then split
-// into 16-bit hi/lo), small enough to stay in every XCD's L2.  The
-// nchan x nphi phase matrix itself is never formed.
+// KF: the contracted axis is uniform (the adjoint transform on a uniform phi
+// grid, where the phi_k are the contracted "channels" b_j = b_0 + j db).  With
+// K-tiles of KT = 96 channels starting at j_J = J KT - P (P channels of zero
+// padding below channel 0 make the top K-tile full), j = j_J + i,
+//   exp(-2 pi i b_j g_k) = base_k r_k^J T'_{i,k},  base_k = exp(-2 pi i (b_0 - P db) g_k),
+//   r_k = exp(-2 pi i KT db g_k),  T'_{i,k} = exp(-2 pi i i db g_k),
+// so F_k = K base_k sum_J r_k^J S_J(k) with S_J the contraction of K-tile J
+// against the table T' (KT x nphi, tile-independent).  The K-tiles are taken
+// from the top down and the accumulators are multiplied by r_k before each
+// new K-tile (Horner's rule), K base_k in the epilogue; the data are only
+// split, not rotated.  KT is a multiple of three K-steps, so every K-tile
+// starts at the same point of the loop's register rotation.
+//
+// ET: neither axis is uniform; the plan holds the whole split phase matrix (a
+// plan-time table of nchan x nphi entries, capped in size), the B tiles are
+// read from it, and the data are only weighted (K w_j).
 //
 // Contraction: v_mfma_f32_32x32x16_{bf16,f16}, hi*hi + hi*lo + lo*hi with FP32
 // accumulation.  Real form of eqs. (15)-(16): A rows (x', y') and (y', -x')
@@ -26,25 +33,6 @@
 // accumulators per lane), so two workgroups share a CU: while one waits on
 // memory, a barrier or its output stores, the other keeps the matrix cores
 // busy.  Q/U loads run two K-steps ahead of their use.
-//
-// The same kernel also serves plans whose contracted axis is uniform and
-// whose output grid is not (KF: the adjoint transform on a uniform phi grid,
-// where the phi_k are the contracted "channels" b_j = b_0 + j db).  With
-// K-tiles of KT = 96 channels starting at j_J = J KT - P (P channels of zero
-// padding below channel 0 make the top K-tile full), j = j_J + i,
-//   exp(-2 pi i b_j g_k) = base_k r_k^J T'_{i,k},  base_k = exp(-2 pi i (b_0 - P db) g_k),
-//   r_k = exp(-2 pi i KT db g_k),  T'_{i,k} = exp(-2 pi i i db g_k),
-// so F_k = K base_k sum_J r_k^J S_J(k) with S_J the contraction of K-tile J
-// against the table T' (KT x nphi, tile-independent).  The K-tiles are taken
-// from the top down and the accumulators are multiplied by r_k before each
-// new K-tile (Horner's rule), K base_k in the epilogue; the data are only
-// weighted and split, not rotated.  KT is a multiple of three K-steps, so
-// every K-tile starts at the same point of the loop's register rotation.
-//
-// On a phi grid that is not uniform (and channels not uniform either) the
-// plan may hold the whole split phase matrix instead (ET: a plan-time table
-// of nchan x nphi entries, capped in size): the B tiles are then read from it
-// like the T tiles, and the data only weighted (K w_j), not rotated.
 #include <float.h>
 
 #include <type_traits>
@@ -116,13 +104,11 @@ __device__ __forceinline__ f32x16_t mfma16(uint4 a, uint4 b, f32x16_t c)
 // peak_merge_kernel, at part[half tile * part_ld + LOS].
 // PEAKS 2: F is not stored; the epilogue writes one PeakRec per (LOS, half
 // tile) instead, at rec[half tile * part_ld + LOS], for peak_merge_rec_kernel.
-// BM selects where the B tiles come from: 0 the tile-independent table T
-// with a per-tile rotation of the data (base [tile][channel]); 1 (KF) the
-// K-tile form above: base holds (w_j, 0) per channel, Thi/Tlo hold T' as
-// [KT/4][ldT] quads, kbase and krot the K base_k and r_k per output
-// (LOS-major input, no peaks); 2 (ET) the explicit phase table, [nchan/4][ldT]
-// quads, base holding (K w_j, 0) per channel.
-template <int LAYOUT, bool FP16, bool FAST, bool FLAGS, int PEAKS, int BM>
+// KF: base holds (w_j, 0) per channel, Thi/Tlo hold T' as [KT/4][ldT] quads,
+// kbase and krot the K base_k and r_k per output (LOS-major input, no peaks).
+// Otherwise (ET) Thi/Tlo hold the phase table, [nchan/4][ldT] quads, and base
+// (K w_j, 0) per channel.
+template <int LAYOUT, bool FP16, bool FAST, bool FLAGS, int PEAKS, bool KF>
 __global__ __launch_bounds__(256, 2) void synth_factored_kernel(
     const float* __restrict__ Q, const float* __restrict__ U, int64_t nlos, int64_t ld,
     int nchan, const float2* __restrict__ base, const uint4* __restrict__ Thi,
@@ -132,7 +118,6 @@ __global__ __launch_bounds__(256, 2) void synth_factored_kernel(
     PeakRec* __restrict__ rec, uint32_t neg_hi, const float2* __restrict__ kbase,
     const float2* __restrict__ krot, int ldT)
 {
-    constexpr bool KF = BM == 1, ET = BM == 2;
     static_assert(!KF || (PEAKS == 0 && LAYOUT == RMSYNTH_LOS_MAJOR), "KF: LOS-major, no peaks");
     // Triple-buffered A tiles (packed data) and T tiles (phase table), in one
     // block so that the epilogue can reuse all of it.
@@ -182,7 +167,7 @@ __global__ __launch_bounds__(256, 2) void synth_factored_kernel(
         const int64_t g = l0 + rq + 32 * i;
         csc[i] = COAL && FP16 ? los_scale[g < nlos ? g : nlos - 1] : 1.0f;
     }
-    const_f4_ptr bt = (const_f4_ptr)(base + ((KF || ET) ? 0 : (int64_t)tn * nchan_pad));
+    const_f4_ptr bt = (const_f4_ptr)base;
     // KF: the K-step contracted at position k of the loop.  K-tile J covers
     // K-steps J KTS - pad .. (J + 1) KTS - pad - 1; the full K-tiles come
     // first, from the top down, then the valid K-steps of K-tile 0.
@@ -220,13 +205,10 @@ __global__ __launch_bounds__(256, 2) void synth_factored_kernel(
     auto gload_vec = [&](Regs& R, int k) __attribute__((always_inline)) {
         const int ks = ks_of(k);
         const int j0 = ks * KC + 4 * hh;
-        if (ET) {
+        if (!KF) {
             const int64_t at = (int64_t)(ks * NQ + (t >> 7)) * ldT + n0 + (t & 127);
             R.th = Thi[at];
             R.tl = Tlo[at];
-        } else if (!KF) {
-            R.th = Thi[(int64_t)ks * (NQ * NT) + t];
-            R.tl = Tlo[(int64_t)ks * (NQ * NT) + t];
         }
         if (FAST) {
             if (LAYOUT == RMSYNTH_LOS_MAJOR) {
@@ -765,43 +747,6 @@ __global__ void peak_merge_rec_kernel(const PeakRec* __restrict__ rec, int npart
     }
 }
 
-// Plan-time tables (FP64 argument reduction, FP32 sin/cos):
-//   base[t][j] = K w_j (cos, sin)(2 pi (phi_0 + NT t dphi) b_j)   (K of eq. (13) folded in)
-//   T[j][m]    = (cos, sin)(2 pi m dphi b_j), stored per 4-channel quad and split.
-__global__ void factor_tables_kernel(const double* __restrict__ bj, const float* __restrict__ wj,
-                                     int nchan_pad, int ftiles, double phi0, double dphi, double K,
-                                     float2* __restrict__ base, uint4* __restrict__ bf_hi,
-                                     uint4* __restrict__ bf_lo, uint4* __restrict__ hf_hi,
-                                     uint4* __restrict__ hf_lo)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nT = (int64_t)(nchan_pad / 4) * NT;
-    if (idx < nT) {
-        const int quad = (int)(idx / NT), m = (int)(idx % NT);
-        uint32_t bh[4], bl[4], hh[4], hl[4];
-        float cs[4], sn[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int j = 4 * quad + i;
-            phase_cos_sin((double)m * dphi * bj[j], cs[i], sn[i]);
-            split2_bf16(cs[i], sn[i], bh[i], bl[i]);
-            split2_f16(cs[i], sn[i], hh[i], hl[i]);
-        }
-        bf_hi[idx] = make_uint4(bh[0], bh[1], bh[2], bh[3]);
-        bf_lo[idx] = make_uint4(bl[0], bl[1], bl[2], bl[3]);
-        hf_hi[idx] = make_uint4(hh[0], hh[1], hh[2], hh[3]);
-        hf_lo[idx] = make_uint4(hl[0], hl[1], hl[2], hl[3]);
-    }
-    const int64_t nB = (int64_t)ftiles * nchan_pad;
-    if (idx < nB) {
-        const int tt = (int)(idx / nchan_pad), j = (int)(idx % nchan_pad);
-        float c, s;
-        phase_cos_sin((phi0 + (double)tt * NT * dphi) * bj[j], c, s);
-        const float kw = (float)(K * (double)wj[j]);
-        base[idx] = make_float2(kw * c, kw * s);
-    }
-}
-
 // Per-LOS power-of-two scale for the FP16 split: M = K max_j w_j max(|Q_j|, |U_j|)
 // (K = 1 for the per-element split kernel, which applies K after the sums)
 // bounds the rotated components up to a factor sqrt 2; the scale 2^(13 - E), with
@@ -849,47 +794,6 @@ __global__ __launch_bounds__(256) void los_scale_kernel(const float* __restrict_
     scale[l] = __builtin_ldexpf(1.0f, e);
 }
 
-template <bool FP16>
-hipError_t launch_t(const rmsynth_plan_s& p, const ExecArgs& a)
-{
-    const int tiles_n = p.ftiles;
-    const int nk = (p.nchan + KC - 1) / KC;
-    const int64_t tiles_m = (a.nlos + MT - 1) / MT;
-    const int64_t blocks = tiles_m * tiles_n;
-    if (blocks <= 0) return hipSuccess;
-    const uint4* Thi = FP16 ? p.d_Thf[0] : p.d_Tbf[0];
-    const uint4* Tlo = FP16 ? p.d_Thf[1] : p.d_Tbf[1];
-    const bool full_k = p.nchan % KC == 0;
-    const bool fast = full_k && (a.layout != RMSYNTH_LOS_MAJOR || a.vec4);
-#define RMS_LAUNCH(L, F, G, P)                                                                           \
-    hipLaunchKernelGGL((synth_factored_kernel<L, FP16, F, G, P, 0>), dim3((unsigned)blocks), dim3(256),     \
-                       0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_base, Thi, Tlo, p.nchan_pad, nk,  \
-                       p.nphi, tiles_n, a.Fq, a.Fu, a.Fabs, a.los_scale, a.peak_part, a.peak_part_ld,      \
-                       a.peak_rec, 0x80000000u, nullptr, nullptr, 0)
-#define RMS_LAUNCH_P(L, F, G)                         \
-    do {                                              \
-        if (a.peak_rec) RMS_LAUNCH(L, F, G, 2);       \
-        else if (a.peak_part) RMS_LAUNCH(L, F, G, 1); \
-        else RMS_LAUNCH(L, F, G, 0);                  \
-    } while (0)
-#define RMS_LAUNCH_G(L, F)                           \
-    do {                                             \
-        if (p.any_flagged) RMS_LAUNCH_P(L, F, true); \
-        else RMS_LAUNCH_P(L, F, false);              \
-    } while (0)
-    if (a.layout == RMSYNTH_LOS_MAJOR) {
-        if (fast) RMS_LAUNCH_G(RMSYNTH_LOS_MAJOR, true);
-        else RMS_LAUNCH_G(RMSYNTH_LOS_MAJOR, false);
-    } else {
-        if (fast) RMS_LAUNCH_G(RMSYNTH_FREQ_MAJOR, true);
-        else RMS_LAUNCH_G(RMSYNTH_FREQ_MAJOR, false);
-    }
-#undef RMS_LAUNCH_G
-#undef RMS_LAUNCH_P
-#undef RMS_LAUNCH
-    return hipGetLastError();
-}
-
 // The channel-factored form (KF): LOS-major input, F stored, no peaks.
 template <bool FP16>
 hipError_t launch_kf(const rmsynth_plan_s& p, const ExecArgs& a)
@@ -905,7 +809,7 @@ hipError_t launch_kf(const rmsynth_plan_s& p, const ExecArgs& a)
     // KF plans (adjoint plans) weight every channel 1: the flag-free forms.
     if (p.any_flagged) return hipErrorInvalidValue;
 #define RMS_LAUNCH_KF(F, G)                                                                              \
-    hipLaunchKernelGGL((synth_factored_kernel<RMSYNTH_LOS_MAJOR, FP16, F, G, 0, 1>), dim3((unsigned)blocks),  \
+    hipLaunchKernelGGL((synth_factored_kernel<RMSYNTH_LOS_MAJOR, FP16, F, G, 0, true>), dim3((unsigned)blocks),  \
                        dim3(256), 0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_kw, Thi, Tlo,        \
                        p.nchan_pad, nk, p.nphi, tiles_n, a.Fq, a.Fu, a.Fabs, a.los_scale, nullptr,       \
                        (int64_t)0, nullptr, 0x80000000u, p.d_kbase, p.d_krot, p.nphi_pad)
@@ -966,7 +870,7 @@ hipError_t launch_et(const rmsynth_plan_s& p, const ExecArgs& a)
     const uint4* Tlo = FP16 ? p.d_Ehf[1] : p.d_Ebf[1];
     const bool fast = p.nchan % KC == 0 && (a.layout != RMSYNTH_LOS_MAJOR || a.vec4);
 #define RMS_LAUNCH_ET(L, F, G, P)                                                                        \
-    hipLaunchKernelGGL((synth_factored_kernel<L, FP16, F, G, P, 2>), dim3((unsigned)blocks), dim3(256),  \
+    hipLaunchKernelGGL((synth_factored_kernel<L, FP16, F, G, P, false>), dim3((unsigned)blocks), dim3(256),  \
                        0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_ew, Thi, Tlo, p.nchan_pad, nk,  \
                        p.nphi, tiles_n, a.Fq, a.Fu, a.Fabs, a.los_scale, a.peak_part, a.peak_part_ld,    \
                        a.peak_rec, 0x80000000u, nullptr, nullptr, p.nphi_pad)
@@ -1072,23 +976,10 @@ hipError_t launch_los_scale(const rmsynth_plan_s& p, const ExecArgs& a)
     return hipGetLastError();
 }
 
-hipError_t launch_synth_factored(const rmsynth_plan_s& p, const ExecArgs& a, int precision)
+int factored_peak_parts(const rmsynth_plan_s& p)
 {
-    return precision == RMSYNTH_SPLIT_FP16 ? launch_t<true>(p, a) : launch_t<false>(p, a);
+    return p.uniform ? (p.nphi + 63) / 64 : 2 * ((p.nphi + NT - 1) / NT);
 }
-
-hipError_t launch_factor_tables(const rmsynth_plan_s& p, hipStream_t stream)
-{
-    const int64_t nT = (int64_t)(p.nchan_pad / 4) * NT;
-    const int64_t nB = (int64_t)p.ftiles * p.nchan_pad;
-    const int64_t n = nT > nB ? nT : nB;
-    hipLaunchKernelGGL(factor_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                       p.d_b, p.d_w, p.nchan_pad, p.ftiles, p.phi0, p.dphi, p.K, p.d_base, p.d_Tbf[0],
-                       p.d_Tbf[1], p.d_Thf[0], p.d_Thf[1]);
-    return hipGetLastError();
-}
-
-int factored_peak_parts(const rmsynth_plan_s& p) { return 2 * p.ftiles; }
 
 hipError_t launch_peak_merge(const rmsynth_plan_s& p, const PeakPart* part, int64_t nlos,
                              const float* Fq, const float* Fu, int32_t* idx, float* phi_pk,
@@ -1099,7 +990,7 @@ hipError_t launch_peak_merge(const rmsynth_plan_s& p, const PeakPart* part, int6
     for (int64_t l0 = 0; l0 < nlos;) {
         const int64_t n = nlos - l0 < max_items(256, 256) ? nlos - l0 : max_items(256, 256);
         hipLaunchKernelGGL(peak_merge_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           part + l0, 2 * p.ftiles, n, nlos, p.nphi, p.d_phi, Fq + l0 * p.nphi,
+                           part + l0, factored_peak_parts(p), n, nlos, p.nphi, p.d_phi, Fq + l0 * p.nphi,
                            Fu + l0 * p.nphi, idx + l0, phi_pk ? phi_pk + l0 : nullptr,
                            amp ? amp + l0 : nullptr, q_pk ? q_pk + l0 : nullptr,
                            u_pk ? u_pk + l0 : nullptr);
@@ -1117,7 +1008,7 @@ hipError_t launch_peak_merge_rec(const rmsynth_plan_s& p, const PeakRec* rec, in
     for (int64_t l0 = 0; l0 < nlos;) {
         const int64_t n = nlos - l0 < max_items(256, 256) ? nlos - l0 : max_items(256, 256);
         hipLaunchKernelGGL(peak_merge_rec_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           rec + l0, 2 * p.ftiles, n, rec_ld, p.nphi, p.d_phi, idx + l0,
+                           rec + l0, factored_peak_parts(p), n, rec_ld, p.nphi, p.d_phi, idx + l0,
                            phi_pk ? phi_pk + l0 : nullptr, amp ? amp + l0 : nullptr,
                            q_pk ? q_pk + l0 : nullptr, u_pk ? u_pk + l0 : nullptr,
                            phi_fit ? phi_fit + l0 : nullptr, amp_fit ? amp_fit + l0 : nullptr);

@@ -1,0 +1,554 @@
+// Faraday-depth transform on a uniform phi grid, by mirrored pairs of depths.
+//
+// For a tile of 2 NH depths centred on phi_c (half way between its two middle
+// depths), phi = phi_c +- h with h = (i + 1/2) dphi, i = 0 .. NH - 1.  With the
+// data rotated to the centre, x_j + i y_j = K w_j X_lj exp(-2i a_j phi_c)
+// (eqs. (11), (13)), and c = cos(2 a_j h), s = sin(2 a_j h),
+//   F(phi_c + h) = (S_xc + S_ys) + i (S_yc - S_xs),
+//   F(phi_c - h) = (S_xc - S_ys) + i (S_yc + S_xs),
+// where S_xc = sum_j x_j c etc.: four real sums give two complex outputs, half
+// the multiply-adds of the direct real form (which needs four for each).
+// The rotation is applied while a Q/U tile is packed into LDS; c and s do not
+// depend on the tile and are a plan-time table (FP64 argument reduction) that
+// stays in every XCD's L2.  The nchan x nphi phase matrix is never formed.
+//
+// The sums run on the matrix cores with FP32 accumulation, in one of
+//   FP32   v_mfma_f32_32x32x2_f32 on FP32 operands,
+//   split  v_mfma_f32_32x32x16_{bf16,f16} on x = hi + lo in 16 bits each,
+//          hi*hi + hi*lo + lo*hi (lo*lo dropped).
+//
+// Workgroup: 256 threads, 64 LOS x 256 phi, 16 channels per K-step.  Wave w
+// owns all 64 LOS and the pairs i = 32 w .. 32 w + 31 (64 phi): 2 LOS groups x
+// 4 sums (128 accumulators per lane), so two workgroups share a CU.  A wave's
+// table columns are its own, so they go from L2 straight to registers, one
+// K-step ahead, in MFMA operand order (1 KB contiguous per load); LDS carries
+// only the packed data (8 KB per K-step, triple buffered).  Per K-step and
+// wave the split forms issue 24 MFMAs, 8 LDS reads of 16 bytes and the packing
+// of 4 channels of 64 LOS.
+#include <float.h>
+
+#include "common.h"
+
+namespace {
+
+constexpr int MT = 64;             // LOS per tile
+constexpr int NH = kMirrorTile / 2;  // pairs per tile
+constexpr int KC = kMirrorChan;    // channels per K-step
+constexpr int STEP = 4 * MT * 2;   // uint4 of a packed K-step: [2 channel octets or quad pairs][4][MT]
+constexpr int SR = kMirrorTile + 4;  // row stride (floats) of the epilogue's tile: conflict-free b128 rows
+
+enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2 };
+
+typedef const __attribute__((address_space(4))) f32x4_t* const_f4_ptr;
+
+template <int PREC>
+__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& lo)
+{
+    if (PREC == RMSYNTH_SPLIT_FP16) split2_f16(a, b, hi, lo);
+    else split2_bf16(a, b, hi, lo);
+}
+
+template <int PREC>
+__device__ __forceinline__ f32x16_t mfma16(uint4 a, uint4 b, f32x16_t c)
+{
+    if (PREC == RMSYNTH_SPLIT_FP16)
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a),
+                                                      __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),
+                                                       __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
+// LOAD: how Q/U are read.  ROW4: LOS-major rows of 16-byte aligned quads;
+// ROW: LOS-major, any alignment; PLANE: frequency-major.
+// FLAGS: some channel has weight 0; its (zero) rotation then also clears
+// whatever the data hold there, NaN included.
+// PEAKS 1: the epilogue also reduces |F|^2 of every LOS over each 64 phi and
+// writes one PeakPart per (LOS, 64 phi) for peak_merge_kernel, at
+// part[(64-phi block) * part_ld + LOS].  PEAKS 2: F is not stored; one PeakRec
+// each instead, for peak_merge_rec_kernel.
+template <int LOAD, int PREC, bool FLAGS, int PEAKS>
+__global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
+    const float* __restrict__ Q, const float* __restrict__ U, int64_t nlos, int64_t ld, int nchan,
+    const float2* __restrict__ base, const uint4* __restrict__ T, int nchan_pad, int nk, int nphi,
+    int tiles_n, float* __restrict__ Fq, float* __restrict__ Fu, float* __restrict__ Fabs,
+    const float* __restrict__ los_scale, PeakPart* __restrict__ part, int64_t part_ld,
+    PeakRec* __restrict__ rec)
+{
+    constexpr bool F32 = PREC == RMSYNTH_FP32;
+    union Lds {
+        uint4 a[3][STEP];
+        float f[PEAKS ? MT * SR : 1];
+    };
+    __shared__ Lds lds;
+    const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t tm = tile / tiles_n;
+    const int tn = (int)(tile - tm * tiles_n);
+    const int64_t l0 = tm * MT;
+    const int n0 = tn * kMirrorTile;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int half = lane >> 5, col = lane & 31;
+
+    // Pack role: LOS `lane` of the tile, channel quad `wave` of the K-step (so
+    // that the channel rotations are scalar loads).  Rows past the cube read
+    // its last LOS; their outputs are never stored.  Channels past the end
+    // read the last ones; their rotation is zero, and a non-finite value they
+    // pick up there belongs to the same LOS, which it spoils anyway (or, in a
+    // flagged channel, is cleared by FLAGS).
+    const int64_t left = nlos - 1 - l0;
+    const int lr = lane < left ? lane : (int)left;
+    const float lsc = PREC == RMSYNTH_SPLIT_FP16 ? los_scale[l0 + lr] : 1.0f;
+    const uint32_t voff = 4u * (LOAD == LOAD_PLANE ? (uint32_t)lr : (uint32_t)(lr * (int)ld));  // < 2^24
+    const float* const Qt = LOAD == LOAD_PLANE ? Q + l0 : Q + l0 * ld;
+    const float* const Ut = LOAD == LOAD_PLANE ? U + l0 : U + l0 * ld;
+    const_f4_ptr bt = (const_f4_ptr)(base + (int64_t)tn * nchan_pad);
+    const uint4* const Tw = T + wave * 256 + lane;
+
+    struct Data {
+        float q[4], u[4];
+    };
+    struct Frag {
+        uint4 v[4];
+    };
+    f32x4_t rot[2];  // (cos, sin) K w_j of the quad to be packed next
+
+    auto load_data = [&](Data& R, int k) __attribute__((always_inline)) {
+        const int j0 = k * KC + 4 * wave;
+        if (LOAD == LOAD_ROW4) {
+            const int j = j0 < nchan ? j0 : nchan - 4;
+            const float4 a = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(Qt + j) + voff);
+            const float4 b = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(Ut + j) + voff);
+            R.q[0] = a.x; R.q[1] = a.y; R.q[2] = a.z; R.q[3] = a.w;
+            R.u[0] = b.x; R.u[1] = b.y; R.u[2] = b.z; R.u[3] = b.w;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = j0 + i < nchan ? j0 + i : nchan - 1;
+                const int64_t at = LOAD == LOAD_PLANE ? (int64_t)j * ld : (int64_t)j;
+                R.q[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Qt + at) + voff);
+                R.u[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ut + at) + voff);
+            }
+        }
+    };
+    auto load_rot = [&](int k) __attribute__((always_inline)) {
+        const int at = (k * KC + 4 * wave) >> 1;
+        rot[0] = bt[at];
+        rot[1] = bt[at + 1];
+    };
+    auto load_b = [&](Frag& B, int k) __attribute__((always_inline)) {
+        const uint4* p = Tw + (int64_t)k * (4 * 256);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) B.v[i] = p[64 * i];
+    };
+    // Rotate and pack the quad: FP32 as float4 x, y of quad `wave`; split as
+    // the 8-byte half of the channel octet's x hi, x lo, y hi, y lo.
+    float px[4], py[4];
+    auto rotate1 = [&](const Data& R, int i) __attribute__((always_inline)) {
+        const f32x4_t rr = rot[i >> 1];
+        const float rc = (i & 1) ? rr.z : rr.x;
+        const float rs = (i & 1) ? rr.w : rr.y;
+        float xr = __builtin_fmaf(R.q[i], rc, R.u[i] * rs);
+        float yr = __builtin_fmaf(R.u[i], rc, -(R.q[i] * rs));
+        if (FLAGS) {
+            const bool flagged = ((__float_as_uint(rc) | __float_as_uint(rs)) << 1) == 0u;
+            xr = flagged ? 0.0f : xr;
+            yr = flagged ? 0.0f : yr;
+        }
+        if (PREC == RMSYNTH_SPLIT_FP16) {
+            xr *= lsc;
+            yr *= lsc;
+        }
+        px[i] = xr;
+        py[i] = yr;
+    };
+    auto store_data = [&](int buf) __attribute__((always_inline)) {
+        if (F32) {
+            // [quad pair][x, y][quad of the pair][row]
+            uint4* const a = &lds.a[buf][(wave >> 1) * (4 * MT) + (wave & 1) * MT + lane];
+            a[0] = __builtin_bit_cast(uint4, f32x4_t{px[0], px[1], px[2], px[3]});
+            a[2 * MT] = __builtin_bit_cast(uint4, f32x4_t{py[0], py[1], py[2], py[3]});
+        } else {
+            uint2 xh, xl, yh, yl;
+            split2<PREC>(px[0], px[1], xh.x, xl.x);
+            split2<PREC>(px[2], px[3], xh.y, xl.y);
+            split2<PREC>(py[0], py[1], yh.x, yl.x);
+            split2<PREC>(py[2], py[3], yh.y, yl.y);
+            // [octet][x hi, x lo, y hi, y lo][row], 8-byte halves
+            uint2* const a = reinterpret_cast<uint2*>(&lds.a[buf][(wave >> 1) * (4 * MT) + lane]) + (wave & 1);
+            a[0] = xh;
+            a[2 * MT] = xl;
+            a[4 * MT] = yh;
+            a[6 * MT] = yl;
+        }
+    };
+    auto load_a = [&](Frag& A, int buf, int g) __attribute__((always_inline)) {
+        if (F32) {
+            // v[2 p + xy]: quad pair p, this lane's quad of it
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                A.v[i] = lds.a[buf][(i >> 1) * (4 * MT) + (i & 1) * (2 * MT) + half * MT + 32 * g + col];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) A.v[i] = lds.a[buf][half * (4 * MT) + i * MT + 32 * g + col];
+        }
+    };
+
+    // acc[g][s]: LOS group g (32 LOS), sums s = xc, ys, yc, xs.
+    f32x16_t acc[2][4];
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[g][s][v] = 0.0f;
+
+    auto mma = [&](const Frag& A, const Frag& B, int g) __attribute__((always_inline)) {
+        if constexpr (F32) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const f32x4_t x = __builtin_bit_cast(f32x4_t, A.v[2 * p]);
+                const f32x4_t y = __builtin_bit_cast(f32x4_t, A.v[2 * p + 1]);
+                const f32x4_t c = __builtin_bit_cast(f32x4_t, B.v[2 * p]);
+                const f32x4_t s = __builtin_bit_cast(f32x4_t, B.v[2 * p + 1]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    acc[g][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], c[i], acc[g][0], 0, 0, 0);
+                    acc[g][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(y[i], s[i], acc[g][1], 0, 0, 0);
+                    acc[g][2] = __builtin_amdgcn_mfma_f32_32x32x2f32(y[i], c[i], acc[g][2], 0, 0, 0);
+                    acc[g][3] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], s[i], acc[g][3], 0, 0, 0);
+                }
+            }
+        } else {
+            // v: x hi, x lo, y hi, y lo and c hi, c lo, s hi, s lo
+            const uint4 xh = A.v[0], xl = A.v[1], yh = A.v[2], yl = A.v[3];
+            const uint4 ch = B.v[0], cl = B.v[1], sh = B.v[2], sl = B.v[3];
+            acc[g][0] = mfma16<PREC>(xl, ch, acc[g][0]);
+            acc[g][1] = mfma16<PREC>(yl, sh, acc[g][1]);
+            acc[g][2] = mfma16<PREC>(yl, ch, acc[g][2]);
+            acc[g][3] = mfma16<PREC>(xl, sh, acc[g][3]);
+            acc[g][0] = mfma16<PREC>(xh, cl, acc[g][0]);
+            acc[g][1] = mfma16<PREC>(yh, sl, acc[g][1]);
+            acc[g][2] = mfma16<PREC>(yh, cl, acc[g][2]);
+            acc[g][3] = mfma16<PREC>(xh, sl, acc[g][3]);
+            acc[g][0] = mfma16<PREC>(xh, ch, acc[g][0]);
+            acc[g][1] = mfma16<PREC>(yh, sh, acc[g][1]);
+            acc[g][2] = mfma16<PREC>(yh, ch, acc[g][2]);
+            acc[g][3] = mfma16<PREC>(xh, sh, acc[g][3]);
+        }
+    };
+
+    // LDS writes and reads of this wave done, then the barrier; unlike
+    // __syncthreads() this does not wait for the loads still in flight, which
+    // only fill registers.
+    auto sync_next = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    // Step k contracts buffer k % 3, packs K-step k + 2 into buffer
+    // (k + 2) % 3 (last read in step k - 1), loads the table columns of k + 1
+    // and the data of k + 4, and reads the first fragments of k + 1 (complete
+    // since the previous barrier).  Indices past the end are clamped: such
+    // loads and stores stay in bounds and are never used.
+    Frag A0, A1;
+    int bc = 0;
+    auto step = [&](const Frag& B, Frag& Bn, Data& R, int k) __attribute__((always_inline)) {
+        const int bf = bc == 2 ? 0 : bc + 1;
+        const int bn = bf == 2 ? 0 : bf + 1;
+        load_b(Bn, k + 1 < nk ? k + 1 : nk - 1);
+        load_a(A1, bc, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(A0, B, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rotate1(R, i);
+        store_data(bn);
+        __builtin_amdgcn_sched_barrier(0);
+        load_data(R, k + 4 < nk ? k + 4 : nk - 1);
+        load_a(A0, bf, 0);
+        mma(A1, B, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        load_rot(k + 3 < nk ? k + 3 : nk - 1);
+        sync_next();
+        bc = bf;
+    };
+
+    Data R0, R1;
+    Frag B0, B1;
+    {
+        load_data(R0, 0);
+        load_data(R1, nk > 1 ? 1 : 0);
+        load_b(B0, 0);
+        load_rot(0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rotate1(R0, i);
+        store_data(0);
+        load_rot(nk > 1 ? 1 : 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rotate1(R1, i);
+        store_data(1);
+        load_data(R0, nk > 2 ? 2 : nk - 1);
+        load_data(R1, nk > 3 ? 3 : nk - 1);
+        load_rot(nk > 2 ? 2 : nk - 1);
+        sync_next();
+        load_a(A0, 0, 0);
+    }
+    int k = 0;
+    for (; k + 1 < nk; k += 2) {
+        step(B0, B1, R0, k);
+        step(B1, B0, R1, k + 1);
+    }
+    if (k < nk) step(B0, B1, R0, k);
+
+    // Epilogue.  Rows of this lane: 32 g + 8 (v >> 2) + 4 half + (v & 3).
+    if (PREC == RMSYNTH_SPLIT_FP16) {
+        // Undo the per-LOS scale 2^e: multiply by 2^-e, formed from the
+        // scale's exponent (exact; no division).
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int64_t l = l0 + 32 * g + 8 * (v >> 2) + 4 * half + (v & 3);
+                const float sc = los_scale[l < nlos ? l : nlos - 1];
+                const float inv = __builtin_ldexpf(1.0f, 1 - __builtin_amdgcn_frexp_expf(sc));
+#pragma unroll
+                for (int s = 0; s < 4; ++s) acc[g][s][v] *= inv;
+            }
+    }
+    // The sums become the outputs in place: Fq, Fu at +h in acc[g][0], acc[g][2],
+    // at -h in acc[g][1], acc[g][3].
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float xc = acc[g][0][v], ys = acc[g][1][v], yc = acc[g][2][v], xs = acc[g][3][v];
+            acc[g][0][v] = xc + ys;
+            acc[g][1][v] = xc - ys;
+            acc[g][2][v] = yc - xs;
+            acc[g][3][v] = yc + xs;
+        }
+    const int cp = NH + 32 * wave + col, cm = NH - 1 - 32 * wave - col;  // columns of +h and -h
+    if constexpr (PEAKS != 2) {
+        const bool full = (l0 + MT <= nlos) && (n0 + kMirrorTile <= nphi);
+        const bool okp = n0 + cp < nphi, okm = n0 + cm < nphi;
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int64_t l = l0 + 32 * g + 8 * (v >> 2) + 4 * half + (v & 3);
+                const int64_t off = l * nphi + n0;
+                float* const fq = Fq + off;
+                float* const fu = Fu + off;
+                if (full) {
+                    fq[cp] = acc[g][0][v];
+                    fq[cm] = acc[g][1][v];
+                    fu[cp] = acc[g][2][v];
+                    fu[cm] = acc[g][3][v];
+                } else if (l < nlos) {
+                    if (okp) {
+                        fq[cp] = acc[g][0][v];
+                        fu[cp] = acc[g][2][v];
+                    }
+                    if (okm) {
+                        fq[cm] = acc[g][1][v];
+                        fu[cm] = acc[g][3][v];
+                    }
+                }
+                if (Fabs && l < nlos) {
+                    float* const fa = Fabs + off;
+                    const float a = acc[g][0][v], b = acc[g][2][v], c = acc[g][1][v], d = acc[g][3][v];
+                    if (okp) fa[cp] = sqrtf(a * a + b * b);
+                    if (okm) fa[cm] = sqrtf(c * c + d * d);
+                }
+            }
+    }
+    if constexpr (PEAKS != 0) {
+        // |F|^2 of the tile goes through LDS (free once every wave has passed
+        // the last K-step's barrier; columns past the grid: -1); thread
+        // (row `lane`, 64-phi block `wave`) scans its row in phi order (strict
+        // >: ties to the lower phi) and writes one record.  A |F|^2 that is
+        // not finite marks the record.
+        float* const sm = lds.f;
+        auto put = [&](int g, int v, float p, float m) __attribute__((always_inline)) {
+            float* const r = sm + (32 * g + 8 * (v >> 2) + 4 * half + (v & 3)) * SR;
+            r[cp] = p;
+            r[cm] = m;
+        };
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float a = acc[g][0][v], b = acc[g][2][v], c = acc[g][1][v], d = acc[g][3][v];
+                put(g, v, n0 + cp < nphi ? __builtin_fmaf(a, a, b * b) : -1.0f,
+                    n0 + cm < nphi ? __builtin_fmaf(c, c, d * d) : -1.0f);
+            }
+        __syncthreads();
+        float best = -1.0f;
+        int bk = 0;
+        bool bad = false;
+        // PEAKS 2: |F|^2 just before and after the best (prv, nxt) and at the
+        // two ends of the 64 (first, last); -1 where there is none.
+        float prv = -1.0f, nxt = -1.0f, first = -1.0f, last = -1.0f;
+        bool want_next = false;
+        const float* const row = sm + lane * SR + 64 * wave;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const float4 m4 = reinterpret_cast<const float4*>(row)[q];
+            const float mm[4] = {m4.x, m4.y, m4.z, m4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v = mm[e];
+                bad |= !(v <= FLT_MAX);
+                if constexpr (PEAKS == 2) {
+                    if (q == 0 && e == 0) first = v;
+                    if (want_next) nxt = v;
+                    want_next = false;
+                    if (v > best) {
+                        prv = last;
+                        nxt = -1.0f;
+                        want_next = true;
+                    }
+                    last = v;
+                }
+                if (v > best) {
+                    best = v;
+                    bk = 4 * q + e;
+                }
+            }
+        }
+        const int64_t l = l0 + lane;
+        const int blk = 4 * tn + wave;
+        const bool mine = l < nlos && 64 * blk < nphi;
+        const int idx = bad ? -2 : 64 * blk + bk;
+        if constexpr (PEAKS == 1) {
+            if (mine) part[blk * part_ld + l] = PeakPart{best, idx};
+        } else {
+            // Fq, then Fu, through the same LDS rows: each thread picks up the
+            // value at its column.
+            __syncthreads();
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) put(g, v, acc[g][0][v], acc[g][1][v]);
+            __syncthreads();
+            const float pq = row[bk];
+            __syncthreads();
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) put(g, v, acc[g][2][v], acc[g][3][v]);
+            __syncthreads();
+            const float pu = row[bk];
+            if (mine) rec[blk * part_ld + l] = PeakRec{best, idx, pq, pu, prv, nxt, first, last};
+        }
+    }
+}
+
+// Plan-time tables (FP64 argument reduction, FP32 sin/cos):
+//   base[tile][j] = K w_j (cos, sin)(2 pi phi_c b_j), phi_c the tile's centre;
+//   T[K-step][32-pair block][4][lane], (c, s) = (cos, sin)(2 pi (i + 1/2) dphi b_j)
+//   for pair i = 32 block + (lane & 31):
+//     split: c hi, c lo, s hi, s lo of the channel octet lane >> 5;
+//     FP32:  c, s of quad lane >> 5, then c, s of quad 2 + (lane >> 5).
+__global__ void mirror_tables_kernel(const double* __restrict__ bj, const float* __restrict__ wj,
+                                     int nchan_pad, int nk, int ftiles, double phi0, double dphi,
+                                     double K, float2* __restrict__ base, uint4* __restrict__ Tbf,
+                                     uint4* __restrict__ Thf, uint4* __restrict__ Tf32)
+{
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx < (int64_t)nk * 256) {
+        const int ks = (int)(idx >> 8), blk = (int)(idx >> 6) & 3, lane = (int)idx & 63;
+        const double h = ((double)(32 * blk + (lane & 31)) + 0.5) * dphi;
+        uint4* const at[3] = {Tbf + (idx - lane) * 4 + lane, Thf + (idx - lane) * 4 + lane,
+                              Tf32 + (idx - lane) * 4 + lane};
+        float c[8], s[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) phase_cos_sin(h * bj[ks * KC + 8 * (lane >> 5) + i], c[i], s[i]);
+        uint32_t b[4][4], f[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            split2_bf16(c[2 * i], c[2 * i + 1], b[0][i], b[1][i]);
+            split2_bf16(s[2 * i], s[2 * i + 1], b[2][i], b[3][i]);
+            split2_f16(c[2 * i], c[2 * i + 1], f[0][i], f[1][i]);
+            split2_f16(s[2 * i], s[2 * i + 1], f[2][i], f[3][i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            at[0][64 * i] = make_uint4(b[i][0], b[i][1], b[i][2], b[i][3]);
+            at[1][64 * i] = make_uint4(f[i][0], f[i][1], f[i][2], f[i][3]);
+        }
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                phase_cos_sin(h * bj[ks * KC + 4 * (2 * p + (lane >> 5)) + i], c[i], s[i]);
+            at[2][64 * (2 * p)] = __builtin_bit_cast(uint4, f32x4_t{c[0], c[1], c[2], c[3]});
+            at[2][64 * (2 * p + 1)] = __builtin_bit_cast(uint4, f32x4_t{s[0], s[1], s[2], s[3]});
+        }
+    }
+    if (idx < (int64_t)ftiles * nchan_pad) {
+        const int tt = (int)(idx / nchan_pad), j = (int)(idx % nchan_pad);
+        float c, s;
+        phase_cos_sin((phi0 + ((double)tt * kMirrorTile + (NH - 0.5)) * dphi) * bj[j], c, s);
+        const float kw = (float)(K * (double)wj[j]);
+        base[idx] = make_float2(kw * c, kw * s);
+    }
+}
+
+template <int LOAD, int PREC>
+hipError_t launch(const rmsynth_plan_s& p, const ExecArgs& a)
+{
+    const int nk = (p.nchan + KC - 1) / KC;
+    const int64_t blocks = (a.nlos + MT - 1) / MT * p.ftiles;
+    if (blocks <= 0) return hipSuccess;
+    const uint4* T = PREC == RMSYNTH_FP32 ? p.d_Tf32 : PREC == RMSYNTH_SPLIT_FP16 ? p.d_Thf : p.d_Tbf;
+#define RMS_LAUNCH(G, P)                                                                              \
+    hipLaunchKernelGGL((synth_mirrored_kernel<LOAD, PREC, G, P>), dim3((unsigned)blocks), dim3(256), 0,  \
+                       a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_base, T, p.nchan_pad, nk,        \
+                       p.nphi, p.ftiles, a.Fq, a.Fu, a.Fabs, a.los_scale, a.peak_part, a.peak_part_ld,  \
+                       a.peak_rec)
+#define RMS_LAUNCH_P(G)                         \
+    do {                                        \
+        if (a.peak_rec) RMS_LAUNCH(G, 2);       \
+        else if (a.peak_part) RMS_LAUNCH(G, 1); \
+        else RMS_LAUNCH(G, 0);                  \
+    } while (0)
+    if constexpr (PREC == RMSYNTH_FP32) {  // peaks are a kernel of their own
+        if (p.any_flagged) RMS_LAUNCH(true, 0);
+        else RMS_LAUNCH(false, 0);
+    } else {
+        if (p.any_flagged) RMS_LAUNCH_P(true);
+        else RMS_LAUNCH_P(false);
+    }
+#undef RMS_LAUNCH_P
+#undef RMS_LAUNCH
+    return hipGetLastError();
+}
+
+template <int PREC>
+hipError_t launch_load(const rmsynth_plan_s& p, const ExecArgs& a)
+{
+    if (a.layout != RMSYNTH_LOS_MAJOR) return launch<LOAD_PLANE, PREC>(p, a);
+    return a.vec4 ? launch<LOAD_ROW4, PREC>(p, a) : launch<LOAD_ROW, PREC>(p, a);
+}
+
+}  // namespace
+
+hipError_t launch_synth_mirrored(const rmsynth_plan_s& p, const ExecArgs& a, int precision)
+{
+    if (precision == RMSYNTH_FP32) return launch_load<RMSYNTH_FP32>(p, a);
+    if (precision == RMSYNTH_SPLIT_FP16) return launch_load<RMSYNTH_SPLIT_FP16>(p, a);
+    return launch_load<RMSYNTH_SPLIT_BF16>(p, a);
+}
+
+hipError_t launch_mirror_tables(const rmsynth_plan_s& p, hipStream_t stream)
+{
+    const int nk = (p.nchan + KC - 1) / KC;
+    const int64_t n = std::max<int64_t>((int64_t)nk * 256, (int64_t)p.ftiles * p.nchan_pad);
+    hipLaunchKernelGGL(mirror_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
+                       p.d_b, p.d_w, p.nchan_pad, nk, p.ftiles, p.phi0, p.dphi, p.K, p.d_base, p.d_Tbf,
+                       p.d_Thf, p.d_Tf32);
+    return hipGetLastError();
+}

@@ -1,0 +1,38 @@
+"""The mirrored-pair transform (uniform phi grids) at the edges of its tiles:
+64 LOS, 256 phi (32 pairs per wave), 16 channels per K-step in quads, the three
+ways Q/U are read, every precision, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1810_06250_amd as rs
+from gpu_util import SCALE_TOL, dev32, host, note
+from synthetic import FREQ_MAJOR, LOS_MAJOR, make_small_cube
+
+pytestmark = pytest.mark.gpu
+
+# (nlos, nchan, nphi): one below, at and above each tile edge; nchan 4 n reads
+# quads, odd nchan single values; 15-17, 31-36 and 47-49 channels end the
+# K-loop after one, two and three steps and leave every remainder.
+EDGES = [(63, 15, 255), (64, 16, 256), (65, 17, 257), (1, 31, 511), (128, 32, 512), (3, 33, 513),
+         (66, 36, 300), (129, 47, 223), (64, 48, 225), (70, 49, 289), (5, 20, 40)]
+
+
+@pytest.mark.parametrize("prec", list(rs.PRECISIONS))
+@pytest.mark.parametrize("layout", [LOS_MAJOR, FREQ_MAJOR], ids=["los", "freq"])
+@pytest.mark.parametrize("shape", EDGES, ids=lambda s: "x".join(map(str, s)))
+def test_tile_edges(prec, layout, shape):
+    nlos, nchan, nphi = shape
+    note(f"mirrored {shape} layout={layout} {prec}")
+    c = make_small_cube(nlos, nchan, nphi, seed=nlos + 3 * nchan + nphi, nflag=nchan // 12, nsrc=nlos // 8 + 1)
+    plan = rs.Plan(c["lambda2"], c["weights"], c["phi"])
+    Q, U = np.float32(c["Q"]), np.float32(c["U"])
+    rq, ru = oracle.fdf(Q.astype(np.float64), U.astype(np.float64), c["lambda2"], c["weights"], c["phi"])
+    if layout == FREQ_MAJOR:
+        Q, U = np.ascontiguousarray(Q.T), np.ascontiguousarray(U.T)
+    Fq, Fu, Fa = plan.execute(dev32(Q), dev32(U), layout, rs.PRECISIONS[prec], want_abs=True)
+    Fq, Fu, Fa = host(Fq), host(Fu), host(Fa)
+    assert np.max(oracle.per_los_error(Fq, Fu, rq, ru)) <= SCALE_TOL[prec]
+    # |F| is the FP32 square root of the FP32 sum of squares of what is stored
+    np.testing.assert_allclose(Fa, np.hypot(Fq.astype(np.float64), Fu), rtol=4e-7, atol=0)
+    plan.close()
