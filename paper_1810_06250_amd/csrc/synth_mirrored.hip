@@ -25,21 +25,33 @@
 // only the packed data (8 KB per K-step, triple buffered).  Per K-step and
 // wave the split forms issue 24 MFMAs, 8 LDS reads of 16 bytes and the packing
 // of 4 channels of 64 LOS.
+//
+// What bounds it: the matrix cores, at the clock the power limit leaves them.
+// 65536 LOS x 2001 phi, bf16x3, no F stored: 0.56 ms with 400 channels, 1.07
+// with 800, 2.04 with 1600, so the K-loop alone issues 1300 TFLOP/s (a library
+// bf16 GEMM of 16384^3 reaches 1375 on the same card) and a tile's start and
+// end cost 12 % at 400 channels.  Storing F adds 1.5 of 10.9 ms at 1024^2 LOS.
+// Packing two K-steps between barriers (six LDS buffers) was 1-2 % slower;
+// centring a ragged last tile on what is left of the grid, so that waves with
+// no pairs skip the matrix work, gained nothing (the workgroup still waits for
+// its full waves).
 #include <float.h>
+
+#include <type_traits>
 
 #include "common.h"
 
 namespace {
 
-constexpr int MT = 64;             // LOS per tile
+constexpr int KC = kMirrorChan;      // channels per K-step
 constexpr int NH = kMirrorTile / 2;  // pairs per tile
-constexpr int KC = kMirrorChan;    // channels per K-step
-constexpr int STEP = 4 * MT * 2;   // uint4 of a packed K-step: [2 channel octets or quad pairs][4][MT]
+constexpr int64_t kSmallTiles = 128;  // see launch_mg
 constexpr int SR = kMirrorTile + 4;  // row stride (floats) of the epilogue's tile: conflict-free b128 rows
 
 enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2 };
 
 typedef const __attribute__((address_space(4))) f32x4_t* const_f4_ptr;
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int PREC>
 __device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& lo)
@@ -63,11 +75,12 @@ __device__ __forceinline__ f32x16_t mfma16(uint4 a, uint4 b, f32x16_t c)
 // ROW: LOS-major, any alignment; PLANE: frequency-major.
 // FLAGS: some channel has weight 0; its (zero) rotation then also clears
 // whatever the data hold there, NaN included.
+// MG: LOS groups (of 32) per tile; the results do not depend on it.
 // PEAKS 1: the epilogue also reduces |F|^2 of every LOS over each 64 phi and
 // writes one PeakPart per (LOS, 64 phi) for peak_merge_kernel, at
 // part[(64-phi block) * part_ld + LOS].  PEAKS 2: F is not stored; one PeakRec
 // each instead, for peak_merge_rec_kernel.
-template <int LOAD, int PREC, bool FLAGS, int PEAKS>
+template <int LOAD, int PREC, bool FLAGS, int PEAKS, int MG>
 __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     const float* __restrict__ Q, const float* __restrict__ U, int64_t nlos, int64_t ld, int nchan,
     const float2* __restrict__ base, const uint4* __restrict__ T, int nchan_pad, int nk, int nphi,
@@ -76,28 +89,36 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     PeakRec* __restrict__ rec)
 {
     constexpr bool F32 = PREC == RMSYNTH_FP32;
+    constexpr int MT = 32 * MG;      // LOS per tile
+    constexpr int STEP = 4 * MT * 2;  // uint4 of a packed K-step: [2 channel octets or quad pairs][4][MT]
     union Lds {
         uint4 a[3][STEP];
-        float f[PEAKS ? MT * SR : 1];
+        float f[MT * SR];
     };
     __shared__ Lds lds;
-    const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int64_t tm = tile / tiles_n;
-    const int tn = (int)(tile - tm * tiles_n);
-    const int64_t l0 = tm * MT;
+    // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
+    // L2: groups of 8 LOS tiles, one per XCD, whose phi tiles then follow one
+    // another on it (they read the same Q/U rows).  The whole chip so works on
+    // one stretch of the cube (1 % faster than an eighth of the cube per XCD).
+    const uint32_t grp = blockIdx.x / (8u * tiles_n), in_grp = blockIdx.x - grp * (8u * tiles_n);
+    const uint32_t mleft = gridDim.x / tiles_n - 8u * grp, wide = mleft < 8u ? mleft : 8u;
+    const int tn = (int)(in_grp / wide);
+    const int64_t l0 = (int64_t)(8u * grp + in_grp % wide) * MT;
     const int n0 = tn * kMirrorTile;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int half = lane >> 5, col = lane & 31;
 
-    // Pack role: LOS `lane` of the tile, channel quad `wave` of the K-step (so
-    // that the channel rotations are scalar loads).  Rows past the cube read
+    // Pack role: LOS `row` of the tile, channel quad `wave` of the K-step (so
+    // that the channel rotations are scalar loads; with 32 LOS both halves of
+    // the wave pack the same values).  Rows past the cube read
     // its last LOS; their outputs are never stored.  Channels past the end
     // read the last ones; their rotation is zero, and a non-finite value they
     // pick up there belongs to the same LOS, which it spoils anyway (or, in a
     // flagged channel, is cleared by FLAGS).
+    const int row = lane & (MT - 1);
     const int64_t left = nlos - 1 - l0;
-    const int lr = lane < left ? lane : (int)left;
+    const int lr = row < left ? row : (int)left;
     const float lsc = PREC == RMSYNTH_SPLIT_FP16 ? los_scale[l0 + lr] : 1.0f;
     const uint32_t voff = 4u * (LOAD == LOAD_PLANE ? (uint32_t)lr : (uint32_t)(lr * (int)ld));  // < 2^24
     const float* const Qt = LOAD == LOAD_PLANE ? Q + l0 : Q + l0 * ld;
@@ -165,7 +186,7 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     auto store_data = [&](int buf) __attribute__((always_inline)) {
         if (F32) {
             // [quad pair][x, y][quad of the pair][row]
-            uint4* const a = &lds.a[buf][(wave >> 1) * (4 * MT) + (wave & 1) * MT + lane];
+            uint4* const a = &lds.a[buf][(wave >> 1) * (4 * MT) + (wave & 1) * MT + row];
             a[0] = __builtin_bit_cast(uint4, f32x4_t{px[0], px[1], px[2], px[3]});
             a[2 * MT] = __builtin_bit_cast(uint4, f32x4_t{py[0], py[1], py[2], py[3]});
         } else {
@@ -175,7 +196,7 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
             split2<PREC>(py[0], py[1], yh.x, yl.x);
             split2<PREC>(py[2], py[3], yh.y, yl.y);
             // [octet][x hi, x lo, y hi, y lo][row], 8-byte halves
-            uint2* const a = reinterpret_cast<uint2*>(&lds.a[buf][(wave >> 1) * (4 * MT) + lane]) + (wave & 1);
+            uint2* const a = reinterpret_cast<uint2*>(&lds.a[buf][(wave >> 1) * (4 * MT) + row]) + (wave & 1);
             a[0] = xh;
             a[2 * MT] = xl;
             a[4 * MT] = yh;
@@ -195,18 +216,19 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     };
 
     // acc[g][s]: LOS group g (32 LOS), sums s = xc, ys, yc, xs.
-    f32x16_t acc[2][4];
+    f32x16_t acc[MG][4];
 #pragma unroll
-    for (int g = 0; g < 2; ++g)
+    for (int g = 0; g < MG; ++g)
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[g][s][v] = 0.0f;
 
-    auto mma = [&](const Frag& A, const Frag& B, int g) __attribute__((always_inline)) {
+    auto mma = [&](const Frag& A, const Frag& B, int g, auto&& midway) __attribute__((always_inline)) {
         if constexpr (F32) {
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
+                if (p == 1) midway();
                 const f32x4_t x = __builtin_bit_cast(f32x4_t, A.v[2 * p]);
                 const f32x4_t y = __builtin_bit_cast(f32x4_t, A.v[2 * p + 1]);
                 const f32x4_t c = __builtin_bit_cast(f32x4_t, B.v[2 * p]);
@@ -229,6 +251,7 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
             acc[g][3] = mfma16<PREC>(xl, sh, acc[g][3]);
             acc[g][0] = mfma16<PREC>(xh, cl, acc[g][0]);
             acc[g][1] = mfma16<PREC>(yh, sl, acc[g][1]);
+            midway();
             acc[g][2] = mfma16<PREC>(yh, cl, acc[g][2]);
             acc[g][3] = mfma16<PREC>(xh, sl, acc[g][3]);
             acc[g][0] = mfma16<PREC>(xh, ch, acc[g][0]);
@@ -258,43 +281,49 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     auto step = [&](const Frag& B, Frag& Bn, Data& R, int k) __attribute__((always_inline)) {
         const int bf = bc == 2 ? 0 : bc + 1;
         const int bn = bf == 2 ? 0 : bf + 1;
+        // The rotations of the next packing are loaded behind the step's last
+        // wait for LDS (scalar loads return out of order, so any later wait
+        // would cover them too) and ahead of its last matrix instructions.
+        auto next_rot = [&]() __attribute__((always_inline)) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_rot(k + 3 < nk ? k + 3 : nk - 1);
+            __builtin_amdgcn_sched_barrier(0);
+        };
         load_b(Bn, k + 1 < nk ? k + 1 : nk - 1);
-        load_a(A1, bc, 1);
+        if (MG == 2) load_a(A1, bc, 1);
         __builtin_amdgcn_sched_barrier(0);
-        mma(A0, B, 0);
+        mma(A0, B, 0, [] {});
 #pragma unroll
         for (int i = 0; i < 4; ++i) rotate1(R, i);
         store_data(bn);
         __builtin_amdgcn_sched_barrier(0);
         load_data(R, k + 4 < nk ? k + 4 : nk - 1);
         load_a(A0, bf, 0);
-        mma(A1, B, 1);
+        if (MG == 2) mma(A1, B, MG - 1, next_rot);
+        else next_rot();
         __builtin_amdgcn_sched_barrier(0);
-        load_rot(k + 3 < nk ? k + 3 : nk - 1);
         sync_next();
         bc = bf;
     };
 
     Data R0, R1;
     Frag B0, B1;
-    {
-        load_data(R0, 0);
-        load_data(R1, nk > 1 ? 1 : 0);
-        load_b(B0, 0);
-        load_rot(0);
+    load_data(R0, 0);
+    load_data(R1, nk > 1 ? 1 : 0);
+    load_rot(0);
+    load_b(B0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rotate1(R0, i);
-        store_data(0);
-        load_rot(nk > 1 ? 1 : 0);
+    for (int i = 0; i < 4; ++i) rotate1(R0, i);
+    store_data(0);
+    load_rot(nk > 1 ? 1 : 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rotate1(R1, i);
-        store_data(1);
-        load_data(R0, nk > 2 ? 2 : nk - 1);
-        load_data(R1, nk > 3 ? 3 : nk - 1);
-        load_rot(nk > 2 ? 2 : nk - 1);
-        sync_next();
-        load_a(A0, 0, 0);
-    }
+    for (int i = 0; i < 4; ++i) rotate1(R1, i);
+    store_data(1);
+    load_data(R0, nk > 2 ? 2 : nk - 1);
+    load_data(R1, nk > 3 ? 3 : nk - 1);
+    load_rot(nk > 2 ? 2 : nk - 1);
+    sync_next();
+    load_a(A0, 0, 0);
     int k = 0;
     for (; k + 1 < nk; k += 2) {
         step(B0, B1, R0, k);
@@ -307,7 +336,7 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         // Undo the per-LOS scale 2^e: multiply by 2^-e, formed from the
         // scale's exponent (exact; no division).
 #pragma unroll
-        for (int g = 0; g < 2; ++g)
+        for (int g = 0; g < MG; ++g)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int64_t l = l0 + 32 * g + 8 * (v >> 2) + 4 * half + (v & 3);
@@ -320,7 +349,7 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     // The sums become the outputs in place: Fq, Fu at +h in acc[g][0], acc[g][2],
     // at -h in acc[g][1], acc[g][3].
 #pragma unroll
-    for (int g = 0; g < 2; ++g)
+    for (int g = 0; g < MG; ++g)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const float xc = acc[g][0][v], ys = acc[g][1][v], yc = acc[g][2][v], xs = acc[g][3][v];
@@ -330,61 +359,66 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
             acc[g][3][v] = yc + xs;
         }
     const int cp = NH + 32 * wave + col, cm = NH - 1 - 32 * wave - col;  // columns of +h and -h
-    if constexpr (PEAKS != 2) {
-        const bool full = (l0 + MT <= nlos) && (n0 + kMirrorTile <= nphi);
-        const bool okp = n0 + cp < nphi, okm = n0 + cm < nphi;
+    // Outputs go through LDS (free once every wave has passed the last K-step's
+    // barrier), one quantity of the whole tile at a time, so that a store covers
+    // a row's 256 phi: rows of nphi floats are in general not 16-byte aligned,
+    // and the 128-byte pieces that one wave holds of a row would each touch two
+    // cache lines (1024^2 LOS x 400 ch x 2001 phi, bf16x3: 12.3 -> 10.9 ms with the
+    // tile order above; the non-temporal hint is 2 % of it).
+    float* const sm = lds.f;
+    auto put = [&](int g, int v, float p, float m) __attribute__((always_inline)) {
+        float* const r = sm + (32 * g + 8 * (v >> 2) + 4 * half + (v & 3)) * SR;
+        r[cp] = p;
+        r[cm] = m;
+    };
+    auto put_all = [&](auto&& value) __attribute__((always_inline)) {
 #pragma unroll
-        for (int g = 0; g < 2; ++g)
+        for (int g = 0; g < MG; ++g)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int64_t l = l0 + 32 * g + 8 * (v >> 2) + 4 * half + (v & 3);
-                const int64_t off = l * nphi + n0;
-                float* const fq = Fq + off;
-                float* const fu = Fu + off;
-                if (full) {
-                    fq[cp] = acc[g][0][v];
-                    fq[cm] = acc[g][1][v];
-                    fu[cp] = acc[g][2][v];
-                    fu[cm] = acc[g][3][v];
-                } else if (l < nlos) {
-                    if (okp) {
-                        fq[cp] = acc[g][0][v];
-                        fu[cp] = acc[g][2][v];
-                    }
-                    if (okm) {
-                        fq[cm] = acc[g][1][v];
-                        fu[cm] = acc[g][3][v];
-                    }
-                }
-                if (Fabs && l < nlos) {
-                    float* const fa = Fabs + off;
-                    const float a = acc[g][0][v], b = acc[g][2][v], c = acc[g][1][v], d = acc[g][3][v];
-                    if (okp) fa[cp] = sqrtf(a * a + b * b);
-                    if (okm) fa[cm] = sqrtf(c * c + d * d);
+                put(g, v, value(acc[g][0][v], acc[g][2][v], cp), value(acc[g][1][v], acc[g][3][v], cm));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    if constexpr (PEAKS != 2) {
+        const int nl = (int)(nlos - l0 < MT ? nlos - l0 : MT);
+        const int n4 = nphi - n0 - 4 * lane;  // phi left at this lane's first column
+        auto store_rows = [&](float* F) __attribute__((always_inline)) {
+            float* out = F + (l0 + wave) * nphi + n0 + 4 * lane;
+            const float* in = sm + wave * SR + 4 * lane;
+#pragma unroll 4
+            for (int i = wave; i < nl; i += 4, out += 4 * (int64_t)nphi, in += 4 * SR) {
+                const f32x4_t v = *reinterpret_cast<const f32x4_t*>(in);
+                if (n4 >= 4) {
+                    __builtin_nontemporal_store(v, reinterpret_cast<f32x4u_t*>(out));
+                } else {
+                    if (n4 > 0) out[0] = v.x;
+                    if (n4 > 1) out[1] = v.y;
+                    if (n4 > 2) out[2] = v.z;
                 }
             }
+        };
+        put_all([](float q, float, int) { return q; });
+        sync_next();
+        store_rows(Fq);
+        sync_next();
+        put_all([](float, float u, int) { return u; });
+        sync_next();
+        store_rows(Fu);
+        if (Fabs) {
+            sync_next();
+            put_all([](float q, float u, int) { return sqrtf(q * q + u * u); });
+            sync_next();
+            store_rows(Fabs);
+        }
+        if constexpr (PEAKS != 0) sync_next();
     }
     if constexpr (PEAKS != 0) {
-        // |F|^2 of the tile goes through LDS (free once every wave has passed
-        // the last K-step's barrier; columns past the grid: -1); thread
-        // (row `lane`, 64-phi block `wave`) scans its row in phi order (strict
-        // >: ties to the lower phi) and writes one record.  A |F|^2 that is
-        // not finite marks the record.
-        float* const sm = lds.f;
-        auto put = [&](int g, int v, float p, float m) __attribute__((always_inline)) {
-            float* const r = sm + (32 * g + 8 * (v >> 2) + 4 * half + (v & 3)) * SR;
-            r[cp] = p;
-            r[cm] = m;
-        };
-#pragma unroll
-        for (int g = 0; g < 2; ++g)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float a = acc[g][0][v], b = acc[g][2][v], c = acc[g][1][v], d = acc[g][3][v];
-                put(g, v, n0 + cp < nphi ? __builtin_fmaf(a, a, b * b) : -1.0f,
-                    n0 + cm < nphi ? __builtin_fmaf(c, c, d * d) : -1.0f);
-            }
-        __syncthreads();
+        // |F|^2 (columns past the grid: -1): thread (LOS `row`, 64-phi block
+        // `wave`) scans its row in phi order (strict >: ties to the lower phi)
+        // and writes one record.  A |F|^2 that is not finite marks the record.
+        put_all([&](float q, float u, int c) { return n0 + c < nphi ? __builtin_fmaf(q, q, u * u) : -1.0f; });
+        sync_next();
         float best = -1.0f;
         int bk = 0;
         bool bad = false;
@@ -392,10 +426,10 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         // two ends of the 64 (first, last); -1 where there is none.
         float prv = -1.0f, nxt = -1.0f, first = -1.0f, last = -1.0f;
         bool want_next = false;
-        const float* const row = sm + lane * SR + 64 * wave;
+        const float* const frow = sm + row * SR + 64 * wave;
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
-            const float4 m4 = reinterpret_cast<const float4*>(row)[q];
+            const float4 m4 = reinterpret_cast<const float4*>(frow)[q];
             const float mm[4] = {m4.x, m4.y, m4.z, m4.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -420,27 +454,21 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         }
         const int64_t l = l0 + lane;
         const int blk = 4 * tn + wave;
-        const bool mine = l < nlos && 64 * blk < nphi;
+        const bool mine = lane < MT && l < nlos && 64 * blk < nphi;
         const int idx = bad ? -2 : 64 * blk + bk;
         if constexpr (PEAKS == 1) {
             if (mine) part[blk * part_ld + l] = PeakPart{best, idx};
         } else {
             // Fq, then Fu, through the same LDS rows: each thread picks up the
             // value at its column.
-            __syncthreads();
-#pragma unroll
-            for (int g = 0; g < 2; ++g)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) put(g, v, acc[g][0][v], acc[g][1][v]);
-            __syncthreads();
-            const float pq = row[bk];
-            __syncthreads();
-#pragma unroll
-            for (int g = 0; g < 2; ++g)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) put(g, v, acc[g][2][v], acc[g][3][v]);
-            __syncthreads();
-            const float pu = row[bk];
+            sync_next();
+            put_all([](float q, float, int) { return q; });
+            sync_next();
+            const float pq = frow[bk];
+            sync_next();
+            put_all([](float, float u, int) { return u; });
+            sync_next();
+            const float pu = frow[bk];
             if (mine) rec[blk * part_ld + l] = PeakRec{best, idx, pq, pu, prv, nxt, first, last};
         }
     }
@@ -497,41 +525,52 @@ __global__ void mirror_tables_kernel(const double* __restrict__ bj, const float*
     }
 }
 
-template <int LOAD, int PREC>
+template <int LOAD, int PREC, int MG>
 hipError_t launch(const rmsynth_plan_s& p, const ExecArgs& a)
 {
     const int nk = (p.nchan + KC - 1) / KC;
-    const int64_t blocks = (a.nlos + MT - 1) / MT * p.ftiles;
+    const int64_t blocks = (a.nlos + 32 * MG - 1) / (32 * MG) * p.ftiles;
     if (blocks <= 0) return hipSuccess;
     const uint4* T = PREC == RMSYNTH_FP32 ? p.d_Tf32 : PREC == RMSYNTH_SPLIT_FP16 ? p.d_Thf : p.d_Tbf;
-#define RMS_LAUNCH(G, P)                                                                              \
-    hipLaunchKernelGGL((synth_mirrored_kernel<LOAD, PREC, G, P>), dim3((unsigned)blocks), dim3(256), 0,  \
-                       a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_base, T, p.nchan_pad, nk,        \
-                       p.nphi, p.ftiles, a.Fq, a.Fu, a.Fabs, a.los_scale, a.peak_part, a.peak_part_ld,  \
+#define RMS_LAUNCH(G, P)                                                                                \
+    hipLaunchKernelGGL((synth_mirrored_kernel<LOAD, PREC, G, P, MG>), dim3((unsigned)blocks), dim3(256),  \
+                       0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_base, T, p.nchan_pad, nk,      \
+                       p.nphi, p.ftiles, a.Fq, a.Fu, a.Fabs, a.los_scale, a.peak_part, a.peak_part_ld,   \
                        a.peak_rec)
-#define RMS_LAUNCH_P(G)                         \
-    do {                                        \
-        if (a.peak_rec) RMS_LAUNCH(G, 2);       \
-        else if (a.peak_part) RMS_LAUNCH(G, 1); \
-        else RMS_LAUNCH(G, 0);                  \
+#define RMS_LAUNCH_P(G)                                                               \
+    do {                                                                              \
+        if constexpr (PREC != RMSYNTH_FP32) { /* FP32: peaks are a kernel of their own */ \
+            if (a.peak_rec) RMS_LAUNCH(G, 2);                                         \
+            else if (a.peak_part) RMS_LAUNCH(G, 1);                                   \
+            else RMS_LAUNCH(G, 0);                                                    \
+        } else {                                                                      \
+            RMS_LAUNCH(G, 0);                                                         \
+        }                                                                             \
     } while (0)
-    if constexpr (PREC == RMSYNTH_FP32) {  // peaks are a kernel of their own
-        if (p.any_flagged) RMS_LAUNCH(true, 0);
-        else RMS_LAUNCH(false, 0);
-    } else {
-        if (p.any_flagged) RMS_LAUNCH_P(true);
-        else RMS_LAUNCH_P(false);
-    }
+    if (p.any_flagged) RMS_LAUNCH_P(true);
+    else RMS_LAUNCH_P(false);
 #undef RMS_LAUNCH_P
 #undef RMS_LAUNCH
     return hipGetLastError();
 }
 
+// Half-height tiles where full ones would leave half of the 256 CUs idle: such
+// a call is bound by the latency of one tile (64^2 LOS x 128 ch x 201 phi, 64
+// full tiles: bf16x3 12.7 -> 9.8 us, FP32 24.1 -> 15.8; 64 LOS x 400 x 2001, 8:
+// 19.4 -> 14.5).  At 256 full tiles both take the same time (26 us), at 512 the
+// half-height ones 10 % more.
+template <int LOAD, int PREC>
+hipError_t launch_mg(const rmsynth_plan_s& p, const ExecArgs& a)
+{
+    const int64_t full = (a.nlos + 63) / 64 * p.ftiles;
+    return full <= kSmallTiles ? launch<LOAD, PREC, 1>(p, a) : launch<LOAD, PREC, 2>(p, a);
+}
+
 template <int PREC>
 hipError_t launch_load(const rmsynth_plan_s& p, const ExecArgs& a)
 {
-    if (a.layout != RMSYNTH_LOS_MAJOR) return launch<LOAD_PLANE, PREC>(p, a);
-    return a.vec4 ? launch<LOAD_ROW4, PREC>(p, a) : launch<LOAD_ROW, PREC>(p, a);
+    if (a.layout != RMSYNTH_LOS_MAJOR) return launch_mg<LOAD_PLANE, PREC>(p, a);
+    return a.vec4 ? launch_mg<LOAD_ROW4, PREC>(p, a) : launch_mg<LOAD_ROW, PREC>(p, a);
 }
 
 }  // namespace

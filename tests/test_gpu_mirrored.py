@@ -11,6 +11,15 @@ from synthetic import FREQ_MAJOR, LOS_MAJOR, make_small_cube
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rs.load_library()
+
+
 # (nlos, nchan, nphi): one below, at and above each tile edge; nchan 4 n reads
 # quads, odd nchan single values; 15-17, 31-36 and 47-49 channels end the
 # K-loop after one, two and three steps and leave every remainder.
