@@ -45,7 +45,7 @@ void free_plan(rmsynth_plan_s* p)
     if (!p) return;
     free_plan(p->adj);
     void* bufs[] = {p->d_b, p->d_lambda2, p->d_w, p->d_phi, p->d_base, p->d_Tbf, p->d_Thf, p->d_Tf32,
-                    p->d_nufft_rot, p->d_nufft_off, p->d_nufft_ent,
+                    p->d_nufft_rot, p->d_nufft_blk, p->d_nufft_ent,
                     p->d_nufft_tw, p->d_nufft_deconv, p->d_kw, p->d_kbase, p->d_krot,
                     p->d_Kbf[0], p->d_Kbf[1], p->d_Khf[0], p->d_Khf[1], p->d_ew,
                     p->d_Ebf[0], p->d_Ebf[1], p->d_Ehf[0], p->d_Ehf[1]};

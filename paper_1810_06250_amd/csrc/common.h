@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+#include <vector>
+
 #include "launch_limits.h"
 #include "rmsynth.h"
 
@@ -76,17 +79,19 @@ struct rmsynth_plan_s {
     rmsynth_plan_s* adj;
     // NUFFT evaluation (uniform grids with nufft_n <= kNufftMaxGrid; nufft_n
     // = 0 otherwise): tables of nufft_plan.cpp.
-    int32_t nufft_n, nufft_kc, nufft_nocc;
+    int32_t nufft_n, nufft_kc, nufft_b1;
     float2* d_nufft_rot;    // [nchan]
-    int* d_nufft_off;       // [nocc + 1] first entry of each occupied grid point
-    int2* d_nufft_ent;      // [entries] ((channel << 13) | grid point, weight bits)
-    float2* d_nufft_tw;     // [n]
-    float* d_nufft_deconv;  // [nphi]
+    int2* d_nufft_blk;      // [n / 2^b1 / 64] first entry, entries per point
+    int2* d_nufft_ent;      // (channel, weight bits)
+    float2* d_nufft_tw;     // twiddle rows, pass by pass
+    float2* d_nufft_deconv;  // [nphi]
 };
 
 constexpr int kNufftWidth = 8;       // kernel width in grid cells
 constexpr int kNufftMaxGrid = 8192;  // largest grid (LDS: 8 bytes per point)
 constexpr int kNufftMaxChan = 4096;  // channels staged in LDS
+constexpr int kNufftListPad = 8;     // gridding lists shared by several threads: a multiple of this
+std::vector<std::pair<int, int>> nufft_passes(int n, int b1);  // (radix, NS) of the passes
 int build_nufft_tables(rmsynth_plan_s* p, const double* lambda2, const double* weights);
 size_t nufft_lds_bytes(const rmsynth_plan_s& p);
 hipError_t launch_nufft(const rmsynth_plan_s& p, const float* Q, const float* U, int64_t nlos,

@@ -10,22 +10,38 @@
 // with the "exponential of semicircle" kernel psi of width W grid cells
 // (Barnett, Magland & af Klinteberg 2019), an n-point FFT, and division of
 // mode m by the kernel's Fourier transform psi_hat(m).  The gridding weights
-// (a per-plan CSR list per grid point: the channels within the kernel's
-// reach), c_j's rotation, the twiddles and 1/psi_hat are plan-time tables
-// built on the host in FP64.
+// (per grid point, the channels within the kernel's reach), c_j's rotation,
+// the twiddles and 1/psi_hat are plan-time tables built on the host in FP64.
 //
-// One workgroup (256 threads) per LOS: the channels' c_j go to LDS, each
-// thread sums whole grid points from their lists of entries (a fixed order,
-// no atomics; only the points some channel reaches),
-// the FFT runs as in-place Stockham passes in LDS (radix 16, and one pass of
-// radix 2, 4 or 8 for the rest of log2 n; each pass reads its butterflies
-// into registers, meets a barrier, then writes), and the N wanted modes are
-// scaled and stored.
+// A band of lambda^2 occupies one stretch of the grid, often a small one.  The
+// plan rotates the grid so that the stretch starts at point 0 (a phase per
+// mode, kept with 1/psi_hat) and, when it fits the first n / 2^B1 points, only
+// those are gridded: a first FFT pass of radix 2^B1 would see one non-zero
+// input per butterfly and copy it to its 2^B1 outputs, so the next pass reads
+// its inputs straight from the short grid.
+//
+// T = n / 8 threads (16 to 512) per LOS, several LOS per workgroup of up to
+// 256 threads where T is less.  The channels' c_j go to LDS; each thread sums
+// grid points from their lists of entries (a fixed order, no atomics; the
+// entries of 64 neighbouring points are interleaved, so that a wave reads
+// them contiguously).  The FFT runs as Stockham passes of radix 8 or 16 in
+// registers, three for n / 2^B1 up to 4096, through LDS; the last one scales
+// its modes and stores them.
+//
+// What bounds it: VALU issue (64 % of the time at the first size below) and
+// the waits between the passes of a LOS.  Per launch, before (radix-16 passes
+// over the whole grid, one contiguous list of entries per point) and after:
+//   262144 LOS x 400 ch x 2001 phi, 1/8 of 4096 points    4.07 -> 2.66 ms
+//   262144 x 288 x 1201, 1/64 of 4096                     4.59 -> 1.88 ms
+//   262144 x 128 x 201, all of 512                        0.86 -> 0.40 ms
+//   65536 x 1024 x 4001, all of 8192                      3.34 -> 1.98 ms
+#include <type_traits>
+
 #include "common.h"
 
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 256;  // threads per workgroup where several LOS share one
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b)
 {
@@ -106,174 +122,316 @@ __device__ __forceinline__ void dft(float2* x)
     else dft16(x);
 }
 
-// LDS position of grid element i: the low four bits XOR-ed with the next
-// four, so that the strided accesses of the passes (stride R or R Ns
-// elements across a wave) fall on distinct banks; a permutation inside each
-// aligned block of 16 elements.
-__device__ __forceinline__ int swz(int i) { return i ^ ((i >> 4) & 15); }
+// LDS position of grid element i: the low five bits XOR-ed with bits 4 to 8, so
+// that the strided accesses of the passes fall on distinct banks; a
+// permutation inside each aligned block of 512 elements.
+__device__ __forceinline__ int swz(int i) { return i ^ ((i >> 4) & 31); }
 
-// One in-place Stockham pass of radix R on sub-transforms of length Ns: the
-// butterflies' inputs are read into registers, a barrier, then the outputs
-// are written (every thread's reads finish before any write).
-template <int R, int LOGN>
-__device__ __forceinline__ void stockham_pass(float2* grid, const float2* __restrict__ tw, int Ns, int t)
+// Radices (log2) of the passes over the 2^M points that are left after the
+// copying first one: at most 4, as radix 32 takes too many registers for
+// enough waves (4096 points as 8 x 16 x 32: 3.9 ms on the case above).
+template <int M>
+struct Radices {
+    static constexpr int count = M <= 4 ? 1 : M <= 8 ? 2 : M <= 12 ? 3 : 4;
+    static constexpr int log2r(int i)
+    {
+        return count == 1 ? M : count == 2 ? (i == 0 ? M / 2 : M - M / 2)
+               : count == 3 ? (i == 0 ? M / 3 : i == 1 ? (M - M / 3) / 2 : M - M / 3 - (M - M / 3) / 2)
+                            : (i < 3 ? 3 : M - 9);
+    }
+};
+
+// Butterfly j of a Stockham pass of radix R on sub-transforms of length NS:
+// inputs src(j, r) = element j + r n/R, twiddled by w^r, w = exp(-2 pi i k / (NS R)),
+// k = j mod NS, then an R-point DFT.  The pass's table holds w^1, w^2, w^3, w^4,
+// w^8, w^12 (those below R), NS values each, so that a wave reads neighbouring
+// ones; the other powers are one product.
+template <int R, int NS, class Src>
+__device__ __forceinline__ void butterfly(float2* v, int j, const float2* __restrict__ tw, Src&& src)
 {
-    constexpr int n = 1 << LOGN;
-    constexpr int NB = (n / R + kThreads - 1) / kThreads;
-    float2 v[NB][R];
-    const int tstep = n / (R * Ns);
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int j = t + kThreads * b;
-        if (j < n / R) {
-            const int k = j & (Ns - 1);
+    for (int r = 0; r < R; ++r) v[r] = src(j, r);
+    if constexpr (NS > 1) {
+        const float2* const w = tw + (j & (NS - 1));
+        float2 lo[4];
 #pragma unroll
-            for (int r = 0; r < R; ++r) v[b][r] = grid[swz(j + r * (n / R))];
-            if (Ns > 1) {
-                // w^r, w = exp(-2 pi i k / (Ns R)), from the table entries of
-                // w, w^2, w^4, w^8 and at most two products each.
-                float2 w[R];
-                w[1] = tw[(k * tstep) & (n - 1)];
-                if constexpr (R > 2) w[2] = tw[(2 * k * tstep) & (n - 1)];
-                if constexpr (R > 4) w[4] = tw[(4 * k * tstep) & (n - 1)];
-                if constexpr (R > 8) w[8] = tw[(8 * k * tstep) & (n - 1)];
-                if constexpr (R > 2) w[3] = cmul(w[1], w[2]);
-                if constexpr (R > 4) {
-                    w[5] = cmul(w[4], w[1]);
-                    w[6] = cmul(w[4], w[2]);
-                    w[7] = cmul(w[4], w[3]);
-                }
-                if constexpr (R > 8) {
+        for (int r = 1; r < (R < 4 ? R : 4); ++r) {
+            lo[r] = w[(r - 1) * NS];
+            v[r] = cmul(v[r], lo[r]);
+        }
 #pragma unroll
-                    for (int r = 9; r < 16; ++r) w[r] = cmul(w[8], w[r - 8]);
-                }
+        for (int q = 4; q < R; q += 4) {
+            const float2 hi = w[(2 + q / 4) * NS];
+            v[q] = cmul(v[q], hi);
 #pragma unroll
-                for (int r = 1; r < R; ++r) v[b][r] = cmul(v[b][r], w[r]);
+            for (int r = 1; r < 4; ++r) v[q + r] = cmul(v[q + r], cmul(hi, lo[r]));
+        }
+    }
+    dft<R>(v);
+}
+constexpr int table_rows(int R) { return R <= 4 ? R - 1 : 2 + R / 4; }
+
+// The passes from number I on, NS the sub-transform length reached.  The first
+// pass reads src (the short grid, or the grid itself); all but the last write
+// the grid; the last gives its modes to out(index, value).  The swizzle is
+// linear over XOR and the bits of j and r (NS or n/R times) do not overlap: an
+// element's place is that of j XOR a constant.
+template <int LOGN, int B1, int T, int I, int NS, class Src, class Out>
+__device__ __forceinline__ void fft_passes(float2* grid, const float2* __restrict__ tw, int t, Src&& src, Out&& out)
+{
+    using Rad = Radices<LOGN - B1>;
+    constexpr int n = 1 << LOGN, R = 1 << Rad::log2r(I);
+    constexpr int NB = (n / R + T - 1) / T;
+    constexpr bool all = n / R % T == 0;
+    if constexpr (I == Rad::count - 1) {
+        static_assert(NS * R == n, "passes cover log2 n");
+#pragma unroll 1
+        for (int b = 0; b < NB; ++b) {
+            const int j = t + T * b;
+            if (all || j < n / R) {
+                float2 v[R];
+                butterfly<R, NS>(v, j, tw, src);
+#pragma unroll
+                for (int r = 0; r < R; ++r) out(j + r * NS, v[r]);
             }
-            dft<R>(v[b]);
         }
-    }
-    __syncthreads();
+    } else {
+        // The first pass of a short grid writes elsewhere than it reads.  Any
+        // other is in place: every thread's reads finish before any write.
+        constexpr bool in_place = !(I == 0 && B1 > 0);
+        float2 v[NB][R];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int j = t + kThreads * b;
-        if (j < n / R) {
-            const int k = j & (Ns - 1);
-            const int base = (j - k) * R + k;
-#pragma unroll
-            for (int r = 0; r < R; ++r) grid[swz(base + r * Ns)] = v[b][r];
+        for (int b = 0; b < NB; ++b) {
+            const int j = t + T * b;
+            if (all || j < n / R) butterfly<R, NS>(v[b], j, tw, src);
         }
+        if (in_place) __syncthreads();
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int j = t + T * b;
+            if (all || j < n / R) {
+                const int k = j & (NS - 1);
+                const int base = swz((j - k) * R + k);
+#pragma unroll
+                for (int r = 0; r < R; ++r) grid[base ^ swz(r * NS)] = v[b][r];
+            }
+        }
+        __syncthreads();
+        constexpr int next = n >> Rad::log2r(I + 1);
+        fft_passes<LOGN, B1, T, I + 1, NS * R>(
+            grid, tw + (NS > 1 ? table_rows(R) * NS : 0), t,
+            [grid](int j, int r) { return grid[swz(j) ^ swz(r * next)]; }, out);
     }
-    __syncthreads();
 }
 
-template <int LOGN>
-__global__ __launch_bounds__(kThreads) void nufft_kernel(
-    const float* __restrict__ Q, const float* __restrict__ U, int64_t nlos, int nchan,
-    const float2* __restrict__ rot, int nocc, const int* __restrict__ off,
-    const int2* __restrict__ ent, const float2* __restrict__ tw, const float* __restrict__ deconv,
-    int N, int kc, float* __restrict__ Fq, float* __restrict__ Fu, float* __restrict__ Fabs)
+// One radix-8 butterfly per thread and pass up to 4096 points (16 points per
+// thread: 2.76 against 2.64 ms on the case above).
+constexpr int threads_per_los(int logn)
 {
-    constexpr int n = 1 << LOGN;
+    return logn >= 12 ? 512 : logn <= 7 ? 16 : 1 << (logn - 3);
+}
+
+// Threads that share a grid point's list.
+constexpr int grid_parts(int logn, int b1)
+{
+    return b1 && threads_per_los(logn) > (1 << (logn - b1)) ? threads_per_los(logn) >> (logn - b1) : 1;
+}
+
+// float2 of LDS per LOS: the grid, with the c_j behind it, or in it where the
+// short grid (behind both) is what gridding writes.
+inline int64_t lds_points(int logn, int b1, int nchan)
+{
+    const int64_t n = int64_t(1) << logn;
+    return b1 ? std::max<int64_t>(n, nchan) + (n >> b1) * grid_parts(logn, b1) : n + nchan;
+}
+
+template <int LOGN, int B1>
+__global__ __launch_bounds__(std::max(kThreads, threads_per_los(LOGN))) void nufft_kernel(
+    const float* __restrict__ Q, const float* __restrict__ U, int64_t nlos, int nchan,
+    const float2* __restrict__ rot, const int2* __restrict__ blk, const int2* __restrict__ ent,
+    const float2* __restrict__ tw, const float2* __restrict__ deconv, int N, int kc, int per_los,
+    float* __restrict__ Fq, float* __restrict__ Fu, float* __restrict__ Fabs)
+{
+    constexpr int n = 1 << LOGN, T = threads_per_los(LOGN), M = n >> B1;
     extern __shared__ float4 smem4[];
-    float2* grid = reinterpret_cast<float2*>(smem4);
-    float2* cb = grid + n;
-    const int t = threadIdx.x;
-    const int64_t l = blockIdx.x;
-    if (l >= nlos) return;  // uniform per workgroup
+    const int t = threadIdx.x & (T - 1);
+    // The LOS of the workgroup that this thread works on, the same over a wave
+    // (and then known to be, for scalar addresses) when T is at least 64.
+    int grp = threadIdx.x / T;
+    if (T >= 64) grp = __builtin_amdgcn_readfirstlane(grp);
+    const int64_t l = (int64_t)blockIdx.x * (blockDim.x / T) + grp;
+    const bool valid = l < nlos;
+    const int64_t lr = valid ? l : nlos - 1;  // spare groups redo the last LOS and store nothing
+    float2* const grid = reinterpret_cast<float2*>(smem4) + grp * per_los;
+    float2* const cb = B1 ? grid : grid + n;
+    float2* const g = B1 ? grid + (per_los - M * grid_parts(LOGN, B1)) : grid;
 
     // c_j = rot_j (Q_j + i U_j); flagged channels are in no gridding list.
-    const float* q = Q + l * nchan;
-    const float* u = U + l * nchan;
-    for (int j = t; j < nchan; j += kThreads) cb[j] = cmul(rot[j], make_float2(q[j], u[j]));
+    const float* q = Q + lr * nchan;
+    const float* u = U + lr * nchan;
+    for (int j = t; j < nchan; j += T) cb[j] = cmul(rot[j], make_float2(q[j], u[j]));
     __syncthreads();
     // Gridding: g_p = sum over the channels within reach of p of psi_jp c_j.
-    // Only the points some channel reaches have entries (a narrow band of
-    // lambda^2 occupies a small part of the grid): the others are zeroed, the
-    // occupied ones (occ[i], entries off[i] .. off[i + 1], packed
-    // (j << 13) | p with the weight's bits) summed in a fixed order.
-    for (int p = t; p < n; p += kThreads) grid[swz(p)] = make_float2(0.0f, 0.0f);
-    __syncthreads();
-    for (int i = t; i < nocc; i += kThreads) {
+    // Block p / 64 of points: its first entry and the entries per point (lists
+    // shorter than the block's longest end in entries of weight 0; a multiple
+    // of S).  S threads share a point's list where there are fewer points than
+    // threads.
+    constexpr int S = grid_parts(LOGN, B1);
+    static_assert(S == 1 || (B1 == 6 && kNufftListPad % S == 0), "whole shares of a list");
+    auto sum_entries = [&](const int2* e, int count) __attribute__((always_inline)) {
         float2 acc = make_float2(0.0f, 0.0f);
-        const int e1 = off[i + 1];
-        int pp = 0;
-        for (int e = off[i]; e < e1; ++e) {
-            const int2 en = ent[e];
-            pp = en.x & 8191;
+        auto add = [&](int2 en) __attribute__((always_inline)) {
             const float w = __int_as_float(en.y);
-            const float2 c = cb[en.x >> 13];
+            const float2 c = cb[en.x];
             acc.x = __builtin_fmaf(w, c.x, acc.x);
             acc.y = __builtin_fmaf(w, c.y, acc.y);
+        };
+        int i = 0;
+        for (; i + 4 <= count; i += 4) {
+            const int2 e0 = e[64 * i], e1 = e[64 * i + 64], e2 = e[64 * i + 128], e3 = e[64 * i + 192];
+            add(e0);
+            add(e1);
+            add(e2);
+            add(e3);
         }
-        grid[swz(pp)] = acc;
+        for (; i < count; ++i) add(e[64 * i]);
+        return acc;
+    };
+    if constexpr (S == 1) {
+        for (int p = t; p < M; p += T) {
+            const int2 b = blk[p >> 6];
+            const float2 acc = sum_entries(ent + b.x + (p & 63), b.y);
+            if (B1) g[p] = acc;
+            else g[swz(p)] = acc;
+        }
+    } else {
+        const int p = t & (M - 1), part = t / M;
+        const int2 b = blk[p >> 6];
+        const int each = b.y / S;
+        g[t] = sum_entries(ent + b.x + 64 * each * part + (p & 63), each);
+        __syncthreads();
+        if (t < M) {
+            float2 acc = g[t];
+#pragma unroll
+            for (int i = 1; i < S; ++i) acc = cadd(acc, g[t + i * M]);
+            g[t] = acc;
+        }
     }
     __syncthreads();
 
-    // Stockham FFT, G_m = sum_p g_p exp(-2 pi i m p / n): a pass of radix R
-    // on sub-transforms of length Ns reads src[j + r n/R], twiddles it by
-    // exp(-2 pi i r (j mod Ns) / (Ns R)), takes an R-point DFT and writes
-    // element r to (j / Ns) Ns R + (j mod Ns) + r Ns.  log2 n = 4 a + b: one
-    // pass of radix 2^b (if b > 0), then a passes of radix 16.
-    int Ns = 1;
-    constexpr int B = LOGN & 3;
-    if constexpr (B == 1) stockham_pass<2, LOGN>(grid, tw, Ns, t);
-    if constexpr (B == 2) stockham_pass<4, LOGN>(grid, tw, Ns, t);
-    if constexpr (B == 3) stockham_pass<8, LOGN>(grid, tw, Ns, t);
-    Ns = 1 << B;
-#pragma unroll 1
-    for (; Ns < n; Ns *= 16) stockham_pass<16, LOGN>(grid, tw, Ns, t);
+    // G_m = sum_p g_p exp(-2 pi i m p / n), F_k = deconv_k G_{(k - kc) mod n}.
+    float* const fq = Fq + lr * N;
+    float* const fu = Fu + lr * N;
+    float* const fa = Fabs ? Fabs + lr * N : nullptr;
+    constexpr int step = n >> Radices<LOGN - B1>::log2r(0);
+    auto src = [g](int j, int r) { return B1 ? g[(j >> B1) + r * (step >> B1)] : g[swz(j) ^ swz(r * step)]; };
+    auto at = [](auto* base, uint32_t k) -> decltype(auto) {  // base[k], 32-bit offset
+        using E = std::remove_pointer_t<decltype(base)>;
+        using C = std::conditional_t<std::is_const_v<E>, const char, char>;
+        return *reinterpret_cast<E*>(reinterpret_cast<C*>(base) + (uint32_t)sizeof(E) * k);
+    };
+    auto out = [=](int m, float2 x) __attribute__((always_inline)) {
+        const uint32_t k = (m + kc) & (n - 1);
+        if (valid && k < (uint32_t)N) {
+            const float2 d = at(deconv, k);
+            if (B1) x = cmul(x, d);
+            else x = make_float2(x.x * d.x, x.y * d.x);
+            __builtin_nontemporal_store(x.x, &at(fq, k));
+            __builtin_nontemporal_store(x.y, &at(fu, k));
+            if (fa) at(fa, k) = sqrtf(x.x * x.x + x.y * x.y);
+        }
+    };
+    fft_passes<LOGN, B1, T, 0, 1 << B1>(grid, tw, t, src, out);
+}
 
-    // F_k = (2 pi / n) G_{(k - kc) mod n} / psi_hat(k - kc).
-    float* fq = Fq + l * N;
-    float* fu = Fu + l * N;
-    for (int k = t; k < N; k += kThreads) {
-        const float2 g = grid[swz((k - kc) & (n - 1))];
-        const float d = deconv[k];
-        const float a = g.x * d, b = g.y * d;
-        fq[k] = a;
-        fu[k] = b;
-        if (Fabs) Fabs[l * N + k] = sqrtf(a * a + b * b);
+template <int M>
+void add_passes(int ns, std::vector<std::pair<int, int>>& out)
+{
+    for (int i = 0; i < Radices<M>::count; ++i) {
+        out.push_back({1 << Radices<M>::log2r(i), ns});
+        ns <<= Radices<M>::log2r(i);
     }
+}
+
+int log2_of(int n)
+{
+    int l = 0;
+    while ((1 << l) < n) ++l;
+    return l;
 }
 
 }  // namespace
 
+std::vector<std::pair<int, int>> nufft_passes(int n, int b1)
+{
+    std::vector<std::pair<int, int>> v;
+    switch (log2_of(n) - b1) {
+        case 4: add_passes<4>(1 << b1, v); break;
+        case 5: add_passes<5>(1 << b1, v); break;
+        case 6: add_passes<6>(1 << b1, v); break;
+        case 7: add_passes<7>(1 << b1, v); break;
+        case 8: add_passes<8>(1 << b1, v); break;
+        case 9: add_passes<9>(1 << b1, v); break;
+        case 10: add_passes<10>(1 << b1, v); break;
+        case 11: add_passes<11>(1 << b1, v); break;
+        case 12: add_passes<12>(1 << b1, v); break;
+        default: add_passes<13>(1 << b1, v); break;
+    }
+    return v;
+}
+
 size_t nufft_lds_bytes(const rmsynth_plan_s& p)
 {
-    return (size_t)((p.nufft_n + p.nchan) * (int64_t)sizeof(float2));
+    return (size_t)lds_points(log2_of(p.nufft_n), p.nufft_b1, p.nchan) * sizeof(float2);
 }
 
 hipError_t launch_nufft(const rmsynth_plan_s& p, const float* Q, const float* U, int64_t nlos,
                         float* Fq, float* Fu, float* Fabs, hipStream_t s)
 {
-    const size_t lds = nufft_lds_bytes(p);
-    int logn = 0;
-    while ((1 << logn) < p.nufft_n) ++logn;
+    const int logn = log2_of(p.nufft_n);
+    const int T = threads_per_los(logn);
+    const size_t each = nufft_lds_bytes(p);
+    // LOS per workgroup: 256 threads' worth, within 40 KB of LDS (four
+    // workgroups on a CU) unless one LOS alone takes more.
+    const int64_t per = std::min<int64_t>(std::max(1, kThreads / T), std::max<int64_t>(1, (int64_t)(40960 / each)));
+    const int64_t max_los = max_items(per, per * T);
     for (int64_t l0 = 0; l0 < nlos;) {
-        const int64_t n = std::min<int64_t>(nlos - l0, max_blocks(kThreads));
+        const int64_t n = std::min<int64_t>(nlos - l0, max_los);
         const float* q = Q + l0 * p.nchan;
         const float* u = U + l0 * p.nchan;
         float* fq = Fq + l0 * p.nphi;
         float* fu = Fu + l0 * p.nphi;
         float* fa = Fabs ? Fabs + l0 * p.nphi : nullptr;
-#define RMS_NUFFT(L)                                                                                  \
-    hipLaunchKernelGGL(nufft_kernel<L>, dim3((unsigned)n), dim3(kThreads), lds, s, q, u, n, p.nchan,    \
-                       p.d_nufft_rot, p.nufft_nocc, p.d_nufft_off, p.d_nufft_ent, p.d_nufft_tw,        \
-                       p.d_nufft_deconv, p.nphi, p.nufft_kc, fq, fu, fa)
+#define RMS_NUFFT(L, B)                                                                               \
+    hipLaunchKernelGGL((nufft_kernel<L, B>), dim3((unsigned)((n + per - 1) / per)),                     \
+                       dim3((unsigned)(per * T)), (size_t)per * each, s, q, u, n, p.nchan, p.d_nufft_rot,  \
+                       p.d_nufft_blk, p.d_nufft_ent, p.d_nufft_tw, p.d_nufft_deconv, p.nphi, p.nufft_kc,   \
+                       (int)(each / sizeof(float2)), fq, fu, fa)
+#define RMS_NUFFT_3(L)                      \
+    do {                                    \
+        if (p.nufft_b1 == 3) RMS_NUFFT(L, 3); \
+        else RMS_NUFFT(L, 0);               \
+    } while (0)
+#define RMS_NUFFT_6(L)                      \
+    do {                                    \
+        if (p.nufft_b1 == 6) RMS_NUFFT(L, 6); \
+        else RMS_NUFFT_3(L);                \
+    } while (0)
         switch (logn) {
-            case 4: RMS_NUFFT(4); break;
-            case 5: RMS_NUFFT(5); break;
-            case 6: RMS_NUFFT(6); break;
-            case 7: RMS_NUFFT(7); break;
-            case 8: RMS_NUFFT(8); break;
-            case 9: RMS_NUFFT(9); break;
-            case 10: RMS_NUFFT(10); break;
-            case 11: RMS_NUFFT(11); break;
-            case 12: RMS_NUFFT(12); break;
-            case 13: RMS_NUFFT(13); break;
+            case 4: RMS_NUFFT(4, 0); break;
+            case 5: RMS_NUFFT(5, 0); break;
+            case 6: RMS_NUFFT(6, 0); break;
+            case 7: RMS_NUFFT_3(7); break;
+            case 8: RMS_NUFFT_3(8); break;
+            case 9: RMS_NUFFT_3(9); break;
+            case 10: RMS_NUFFT_6(10); break;
+            case 11: RMS_NUFFT_6(11); break;
+            case 12: RMS_NUFFT_6(12); break;
+            case 13: RMS_NUFFT_6(13); break;
             default: return hipErrorInvalidValue;
         }
+#undef RMS_NUFFT_6
+#undef RMS_NUFFT_3
 #undef RMS_NUFFT
         if (hipError_t e = hipGetLastError()) return e;
         l0 += n;

@@ -3,20 +3,28 @@
 //   n        grid size: the smallest power of two >= max(2 nphi, 16);
 //   kc       index of the grid's centre phi_c = phi_0 + kc dphi, kc = nphi / 2;
 //   rot_j    K w_j exp(-2i a_j phi_c) (the factor c_j = rot_j P_j);
-//   entries  for every grid point p in order, the channels j (w_j > 0) whose
-//            kernel reaches it, periodic distance d = x_p - x_j wrapped to
+//   lists    for every grid point p, the channels j (w_j > 0) whose kernel
+//            reaches it, periodic distance d = x_p - x_j wrapped to
 //            [-pi, pi), |d| < alpha, with weight psi(d); x_p = 2 pi p / n,
-//            x_j = 2 a_j dphi mod 2 pi; packed ((j << 13) | p, bits of
-//            psi(d)); only grid points with entries are listed, off[i] the
-//            first entry of the i-th of them;
-//   tw_t     exp(-2 pi i t / n);
-//   deconv_k (2 pi / n) / psi_hat(k - kc), psi_hat by 512-point Gauss-Legendre
-//            quadrature of int psi(t) cos(m t) dt over [-alpha, alpha];
+//            x_j = 2 a_j dphi mod 2 pi;
+//   b1, p0   the stretch of grid points with lists, cut at its widest gap,
+//            starts at p0; b1 = 6 or 3 when it fits n / 2^b1 points (of at
+//            least 16), else 0 and p0 = 0;
+//   blk, ent the lists of points p0 + i (mod n), i < n / 2^b1, in blocks of 64
+//            points: blk = (first entry, entries per point), entry e of point
+//            i at first + 64 e + i mod 64, (j, bits of psi(d)), filled up
+//            with weight 0 to the block's longest list, a multiple of
+//            kNufftListPad for b1 = 6;
+//   tw       twiddle rows of the FFT passes (nufft.hip);
+//   deconv_k (2 pi / n) / psi_hat(m) exp(-2 pi i m p0 / n), m = k - kc, psi_hat
+//            by 512-point Gauss-Legendre quadrature of int psi(t) cos(m t) dt
+//            over [-alpha, alpha];
 // psi(t) = exp(beta (sqrt(1 - (t / alpha)^2) - 1)), alpha = W pi / n,
 // beta = 2.30 W, W = kNufftWidth grid cells (Barnett, Magland &
 // af Klinteberg, SIAM J. Sci. Comput. 41, 2019).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -95,40 +103,76 @@ int build_nufft_tables(rmsynth_plan_s* p, const double* lambda2, const double* w
             if (std::fabs(d) < alpha) lists[pp].push_back({j, (float)psi(d)});
         }
     }
-    std::vector<int> off;
-    std::vector<int2> ent;
-    for (int pp = 0; pp < n; ++pp) {
-        if (lists[pp].empty()) continue;
-        off.push_back((int)ent.size());
-        for (auto& e : lists[pp]) {
-            float wt = e.second;
-            int bits;
-            std::memcpy(&bits, &wt, sizeof bits);
-            ent.push_back(make_int2((e.first << 13) | pp, bits));
+    // The widest cyclic run of empty points ends where the stretch starts.
+    int p0 = 0, gap = 0;
+    for (int pp = 0, run = 0; pp < 2 * n; ++pp) {
+        if (lists[pp % n].empty()) {
+            if (++run > gap && run <= n) {
+                gap = run;
+                p0 = (pp + 1) % n;
+            }
+        } else {
+            run = 0;
         }
     }
-    const int nocc = (int)off.size();
-    off.push_back((int)ent.size());
-    std::vector<float2> tw(n);
-    for (int t = 0; t < n; ++t)
-        tw[t] = make_float2((float)std::cos(2.0 * M_PI * t / n), (float)(-std::sin(2.0 * M_PI * t / n)));
+    const int span = n - gap;
+    int b1 = 0;
+    if (span <= (n >> 6) && (n >> 6) >= 16) b1 = 6;
+    else if (span <= (n >> 3) && (n >> 3) >= 16) b1 = 3;
+    if (!b1) p0 = 0;
+    // Filling entries name a channel of the point itself (or, for a point
+    // without any, one of non-zero weight), so that they add 0 unless that
+    // channel is not finite and spoils the line of sight anyway.
+    int any = 0;
+    while (any < p->nchan - 1 && !(weights[any] > 0.0)) ++any;
+    std::vector<int2> blk, ent;
+    const int points = n >> b1;
+    for (int i0 = 0; i0 < points; i0 += 64) {
+        size_t longest = 0;
+        for (int i = i0; i < i0 + 64 && i < points; ++i) longest = std::max(longest, lists[(p0 + i) % n].size());
+        if (b1 == 6) longest = (longest + kNufftListPad - 1) / kNufftListPad * kNufftListPad;
+        blk.push_back(make_int2((int)ent.size(), (int)longest));
+        for (size_t e = 0; e < longest; ++e)
+            for (int i = i0; i < i0 + 64; ++i) {
+                int2 v = make_int2(any, 0);
+                if (i < points) {
+                    const auto& li = lists[(p0 + i) % n];
+                    if (e < li.size()) {
+                        v.x = li[e].first;
+                        std::memcpy(&v.y, &li[e].second, sizeof v.y);
+                    } else if (!li.empty()) {
+                        v.x = li.back().first;
+                    }
+                }
+                ent.push_back(v);
+            }
+    }
+    // Rows of w^r, r = 1, 2, 3, 4, 8, 12, of each pass with NS > 1, in order.
+    std::vector<float2> tw;
+    for (const auto& [R, NS] : nufft_passes(n, b1))
+        for (int r = 1; NS > 1 && r < R; r += r < 4 ? 1 : 4)
+            for (int k = 0; k < NS; ++k) {
+                const double ang = 2.0 * M_PI * r * k / ((double)NS * R);
+                tw.push_back(make_float2((float)std::cos(ang), (float)(-std::sin(ang))));
+            }
     std::vector<double> gx, gw;
     gauss_legendre(512, gx, gw);
-    std::vector<float> deconv(p->nphi);
+    std::vector<float2> deconv(p->nphi);
     for (int32_t k = 0; k < p->nphi; ++k) {
         const double m = (double)(k - kc);
         double s = 0.0;
         for (size_t i = 0; i < gx.size(); ++i)
             s += gw[i] * std::exp(beta * (std::sqrt(1.0 - gx[i] * gx[i]) - 1.0)) * std::cos(m * alpha * gx[i]);
-        deconv[k] = (float)((2.0 * M_PI / n) / (alpha * s));
+        const double d = (2.0 * M_PI / n) / (alpha * s), ang = 2.0 * M_PI * std::fmod(m * p0, (double)n) / n;
+        deconv[k] = make_float2((float)(d * std::cos(ang)), (float)(-d * std::sin(ang)));
     }
     if (int rc = upload(&p->d_nufft_rot, rot)) return rc;
-    if (int rc = upload(&p->d_nufft_off, off)) return rc;
+    if (int rc = upload(&p->d_nufft_blk, blk)) return rc;
     if (int rc = upload(&p->d_nufft_ent, ent)) return rc;
     if (int rc = upload(&p->d_nufft_tw, tw)) return rc;
     if (int rc = upload(&p->d_nufft_deconv, deconv)) return rc;
     p->nufft_n = n;
     p->nufft_kc = kc;
-    p->nufft_nocc = nocc;
+    p->nufft_b1 = b1;
     return RMSYNTH_OK;
 }
