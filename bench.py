@@ -65,7 +65,7 @@ def paper_context():
 # keyed by (workload, precision, sha256 prefix of the kernel sources they were
 # taken on).  A changed kernel source reports null until counters are retaken.
 KERNEL_SRC = [os.path.join(ROOT, "paper_1810_06250_amd", "csrc", f)
-              for f in ("synth_factored.hip", "common.h")]
+              for f in ("synth_mirrored.hip", "common.h")]
 TRAFFIC = {
     ("c3", "bf16x3", "c091c886c2c0df0f"): 2.0 * 2395509.8 * 1024 + 1.0 * 17044737.2 * 1024,
 }
@@ -185,7 +185,7 @@ def time_path(rs, plan, cube, prec, Fq, Fu, pk, steps, warmup, fused=False):
 
 
 def plan_uniform(phi):
-    """The library takes the factored (fused-peaks) kernels on uniform grids."""
+    """The library takes the mirrored-pair (fused-peaks) kernels on uniform grids."""
     phi = np.asarray(phi, dtype=np.float64)
     if phi.size < 2:
         return True

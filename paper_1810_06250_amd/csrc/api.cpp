@@ -46,8 +46,7 @@ void free_plan(rmsynth_plan_s* p)
     free_plan(p->adj);
     void* bufs[] = {p->d_b, p->d_lambda2, p->d_w, p->d_phi, p->d_base, p->d_Tbf, p->d_Thf, p->d_Tf32,
                     p->d_nufft_rot, p->d_nufft_blk, p->d_nufft_ent,
-                    p->d_nufft_tw, p->d_nufft_deconv, p->d_kw, p->d_kbase, p->d_krot,
-                    p->d_Kbf[0], p->d_Kbf[1], p->d_Khf[0], p->d_Khf[1], p->d_ew,
+                    p->d_nufft_tw, p->d_nufft_deconv, p->d_kbase, p->d_krot, p->d_ew,
                     p->d_Ebf[0], p->d_Ebf[1], p->d_Ehf[0], p->d_Ehf[1]};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
@@ -92,7 +91,7 @@ int build_mirror_tables(rmsynth_plan_s* p)
 }
 
 // The explicit split phase table of a plan whose axes are not uniform (the
-// factored tables do not apply), when it fits kEtabMaxBytes; larger plans keep
+// mirrored and folded tables do not apply), when it fits kEtabMaxBytes; larger plans keep
 // the per-element phase generator.
 int build_etable(rmsynth_plan_s* p)
 {
@@ -156,33 +155,32 @@ int build_adjoint_plan(rmsynth_plan_s* p, const double* lambda2, const double* p
         return rms_hip_fail(e, "rmsynth_plan: hipMemcpy (adjoint)");
     q->uniform = detect_uniform(hgrid.data(), q->nphi, amax, &q->phi0, &q->dphi);
     if (q->uniform) return build_mirror_tables(q);
-    // A uniform phi grid makes the contracted axis uniform: the channel-factored
-    // tables then replace per-element phase generation (same phase tolerance,
-    // now over every output lambda^2).
+    // A uniform phi grid makes the contracted axis uniform: the folded form
+    // (same phase tolerance, now over every output lambda^2).
     double gmax = 0.0, phi0 = 0.0, dphi = 0.0;
     for (int32_t j = 0; j < p->nchan; ++j) gmax = std::max(gmax, std::fabs(hgrid[j]));
-    if (p->nphi < 3 * kKTile || !detect_uniform(phi, p->nphi, gmax, &phi0, &dphi)) return build_etable(q);
+    if (!detect_uniform(phi, p->nphi, gmax, &phi0, &dphi)) return build_etable(q);
     q->cuniform = true;
     q->kb0 = phi0 / M_PI;
     q->kdb = dphi / M_PI;
-    {
-        constexpr int kc = 8, kts = kKTile / kc;  // K-step of the factored kernel
-        const int nk = (q->nchan + kc - 1) / kc;
-        q->kpad = ((nk + kts - 1) / kts * kts - nk) * kc;
-    }
-    const size_t nT = (size_t)(kKTile / 4) * q->nphi_pad;
-    if ((e = hipMalloc(&q->d_kw, sizeof(float2) * q->nchan_pad)) != hipSuccess ||
-        (e = hipMalloc(&q->d_kbase, sizeof(float2) * q->nphi_pad)) != hipSuccess ||
+    // As few K-tiles as kFoldTile allows, of equal length, an even number of
+    // K-steps each.
+    const int ntile = (q->nchan + kFoldTile - 1) / kFoldTile;
+    const int len = (int)round_up((q->nchan + ntile - 1) / ntile, 2 * kMirrorChan);
+    q->ksteps = len / kMirrorChan;
+    q->kpad = ntile * len - q->nchan;
+    q->ftiles = (int32_t)((q->nphi + kMirrorTile - 1) / kMirrorTile);
+    const size_t nT = (size_t)q->ksteps * 4 * q->nphi_pad;
+    if ((e = hipMalloc(&q->d_kbase, sizeof(float2) * q->nphi_pad)) != hipSuccess ||
         (e = hipMalloc(&q->d_krot, sizeof(float2) * q->nphi_pad)) != hipSuccess ||
-        (e = hipMalloc(&q->d_Kbf[0], sizeof(uint4) * nT)) != hipSuccess ||
-        (e = hipMalloc(&q->d_Kbf[1], sizeof(uint4) * nT)) != hipSuccess ||
-        (e = hipMalloc(&q->d_Khf[0], sizeof(uint4) * nT)) != hipSuccess ||
-        (e = hipMalloc(&q->d_Khf[1], sizeof(uint4) * nT)) != hipSuccess)
+        (e = hipMalloc(&q->d_Tbf, sizeof(uint4) * nT)) != hipSuccess ||
+        (e = hipMalloc(&q->d_Thf, sizeof(uint4) * nT)) != hipSuccess ||
+        (e = hipMalloc(&q->d_Tf32, sizeof(uint4) * nT)) != hipSuccess)
         return rms_fail(RMSYNTH_ENOMEM, "rmsynth_plan: hipMalloc (adjoint tables): %s", hipGetErrorString(e));
     hipStream_t s = nullptr;
     if ((e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking)) != hipSuccess)
         return rms_hip_fail(e, "rmsynth_plan: hipStreamCreate");
-    e = launch_kfactor_tables(*q, s);
+    e = launch_fold_tables(*q, s);
     hipError_t e2 = hipStreamSynchronize(s);
     (void)hipStreamDestroy(s);
     if (e != hipSuccess) return rms_hip_fail(e, "rmsynth_plan: adjoint-table kernel");
@@ -377,10 +375,10 @@ WsLayout ws_layout(const rmsynth_plan_s* p, Mode mode, int32_t precision, int64_
     WsLayout w;
     if (precision == RMSYNTH_SPLIT_FP16) w.scales = scale_bytes(n);
     if (mode == Mode::ExecutePeaks && fused_peaks(p, precision))
-        w.parts = region(n, factored_peak_parts(*p) * (int64_t)sizeof(PeakPart));
+        w.parts = region(n, peak_parts(*p) * (int64_t)sizeof(PeakPart));
     if (mode == Mode::Search) {
         if (fused_peaks(p, precision)) {
-            w.recs = region(n, factored_peak_parts(*p) * (int64_t)sizeof(PeakRec));
+            w.recs = region(n, peak_parts(*p) * (int64_t)sizeof(PeakRec));
         } else {
             w.fq = region(n, (int64_t)p->nphi * 4);
             w.fu = w.fq;
@@ -421,7 +419,7 @@ int batch_size(const rmsynth_plan_s* p, Mode mode, int32_t precision, int64_t nl
 // launches whose grids stay within the dispatch limit (tiles of at least 64
 // LOS of 256 threads).  ld is the call's row stride (LOS-major: nchan) or
 // plane stride (frequency-major: the call's nlos).  With parts or recs the
-// factored kernels also write their per-tile peaks, laid out [part][n].
+// kernels with tables also write their peaks per 64 phi, laid out [part][n].
 int run_execute(const rmsynth_plan_s* p, const float* Q, const float* U, int64_t l0, int64_t n,
                 int64_t ld, int32_t layout, int32_t precision, float* Fq, float* Fu, float* Fabs,
                 float* scales, PeakPart* parts, PeakRec* recs, hipStream_t stream, const char* who)
@@ -457,10 +455,8 @@ int run_execute(const rmsynth_plan_s* p, const float* Q, const float* U, int64_t
             if (e != hipSuccess) return rms_hip_fail(e, who);
         }
         hipError_t e;
-        if (p->uniform) e = launch_synth_mirrored(*p, a, precision);
+        if (p->uniform || p->cuniform) e = launch_synth_mirrored(*p, a, precision);
         else if (precision == RMSYNTH_FP32) e = launch_synth_fp32(*p, a);
-        else if (p->cuniform && layout == RMSYNTH_LOS_MAJOR && !parts && !recs)
-            e = launch_synth_kfactored(*p, a, precision);
         else if (p->etab) e = launch_synth_etable(*p, a, precision);
         else e = launch_synth_split(*p, a, precision);
         if (e != hipSuccess) return rms_hip_fail(e, who);

@@ -37,7 +37,7 @@ struct rmsynth_plan_s {
     // Mirrored-pair tables (synth_mirrored.hip), present when the phi grid is
     // uniform (phi_k = phi_0 + k dphi), in tiles of kMirrorTile phi:
     //   d_base [ftiles][nchan_pad] float2  K w_j (cos, sin)(2 a_j phi_c), phi_c the tile's centre
-    //   d_T{bf,hf,32} [K-steps][4][4][64] uint4: (cos, sin)(2 a_j (i + 1/2) dphi) of 16
+    //   d_T{bf,hf,f32} [K-steps][4][4][64] uint4: (cos, sin)(2 a_j (i + 1/2) dphi) of 16
     //                   channels x 128 pairs in MFMA operand order, split into 16-bit
     //                   hi/lo (bfloat16, half) or FP32
     bool uniform;
@@ -48,19 +48,19 @@ struct rmsynth_plan_s {
     uint4* d_Thf;
     uint4* d_Tf32;
     bool any_flagged;    // some channel has weight 0
-    // Channel-factored tables (synth_factored.hip, KF), present when the
-    // contracted axis is uniform, b_j = kb0 + j kdb, and the output grid is
-    // not (the adjoint plan of a uniform phi grid).  K-tiles of kKTile
-    // channels, the lowest one starting kpad channels below channel 0:
-    //   d_kw    [nchan_pad] float2  (w_j, 0)
-    //   d_kbase [nphi_pad]  float2  K (cos, sin)(2 pi (kb0 - kpad kdb) g_k)
-    //   d_krot  [nphi_pad]  float2  (cos, sin)(2 pi kKTile kdb g_k)
-    //   d_K{bf,hf}[hi/lo] [kKTile/4][nphi_pad] uint4: 4 channels x (cos, sin)
-    //                   of 2 pi i kdb g_k, i = 0 .. kKTile-1, split into hi/lo
+    // Folded tables (synth_mirrored.hip, FOLD), present when the contracted axis
+    // is uniform, b_j = kb0 + j kdb, and the output grid is not (the adjoint
+    // plan of a uniform phi grid).  K-tiles of ksteps K-steps (an even number),
+    // the lowest one starting kpad channels below channel 0; d_T{bf,hf,f32} then
+    // hold [ksteps][nphi_pad/64][4][64] uint4 (fold_tables_kernel) and
+    //   d_kbase [nphi_pad] float2  K (cos, sin)(2 pi b g) of the lowest K-tile's centre
+    //   d_krot  [nphi_pad] float2  (cos, sin)(2 pi L kdb g), L channels per K-tile
     bool cuniform;
     double kb0, kdb;
-    int32_t kpad;
-    // Explicit split phase table (synth_factored.hip, ET), present when
+    int32_t kpad, ksteps;
+    float2* d_kbase;
+    float2* d_krot;
+    // Explicit split phase table (synth_table.hip), present when
     // neither axis is uniform and the table fits kEtabMaxBytes:
     //   d_ew [nchan_pad] float2  (K w_j, 0)
     //   d_E{bf,hf}[hi/lo] [nchan_pad/4][nphi_pad] uint4: 4 channels x (cos, sin)
@@ -69,11 +69,6 @@ struct rmsynth_plan_s {
     float2* d_ew;
     uint4* d_Ebf[2];
     uint4* d_Ehf[2];
-    float2* d_kw;
-    float2* d_kbase;
-    float2* d_krot;
-    uint4* d_Kbf[2];
-    uint4* d_Khf[2];
     // The adjoint transform's plan (axes exchanged, see build_adjoint_plan);
     // owned, NULL inside an adjoint plan itself.
     rmsynth_plan_s* adj;
@@ -97,10 +92,10 @@ size_t nufft_lds_bytes(const rmsynth_plan_s& p);
 hipError_t launch_nufft(const rmsynth_plan_s& p, const float* Q, const float* U, int64_t nlos,
                         float* Fq, float* Fu, float* Fabs, hipStream_t s);
 
-constexpr int kFactorTile = 128;  // phi per tile of the factored kernels
+constexpr int kTableTile = 128;   // phi per tile of the phase-table kernel
 constexpr int kMirrorTile = 256;  // phi per tile of the mirrored-pair kernels
 constexpr int kMirrorChan = 16;   // channels per K-step of the mirrored-pair kernels
-constexpr int kKTile = 96;        // channels per K-tile of the channel-factored form
+constexpr int kFoldTile = 256;    // most channels per K-tile of the folded form
 constexpr size_t kEtabMaxBytes = size_t(256) << 20;  // largest explicit phase table (4 arrays)
 
 constexpr int kChanPad = 32;    // channel padding granule (largest K-step)
@@ -246,9 +241,9 @@ struct ExecArgs {
     float* Fu;
     float* Fabs;
     float* los_scale;  // FP16 split: per-LOS scale [nlos] in the workspace
-    PeakPart* peak_part;  // factored kernels: per-(LOS, half phi tile) peaks, or NULL;
+    PeakPart* peak_part;  // fused peaks: per-(LOS, 64 phi) records, or NULL;
     int64_t peak_part_ld; // record (h, l) at peak_part[h * peak_part_ld + l]
-    PeakRec* peak_rec;    // factored kernels, F not stored (Fq = Fu = NULL): full
+    PeakRec* peak_rec;    // fused peaks, F not stored (Fq = Fu = NULL): full
                           // records at peak_rec[h * peak_part_ld + l], or NULL
     hipStream_t stream;
 };
@@ -258,8 +253,7 @@ hipError_t launch_synth_split(const rmsynth_plan_s& p, const ExecArgs& a, int pr
 hipError_t launch_synth_mirrored(const rmsynth_plan_s& p, const ExecArgs& a, int precision);
 hipError_t launch_los_scale(const rmsynth_plan_s& p, const ExecArgs& a);
 hipError_t launch_mirror_tables(const rmsynth_plan_s& p, hipStream_t s);
-hipError_t launch_kfactor_tables(const rmsynth_plan_s& p, hipStream_t s);
-hipError_t launch_synth_kfactored(const rmsynth_plan_s& p, const ExecArgs& a, int precision);
+hipError_t launch_fold_tables(const rmsynth_plan_s& p, hipStream_t s);
 hipError_t launch_etable(const rmsynth_plan_s& p, hipStream_t s);
 hipError_t launch_synth_etable(const rmsynth_plan_s& p, const ExecArgs& a, int precision);
 hipError_t launch_peaks(const rmsynth_plan_s& p, const float* Fq, const float* Fu, int64_t nlos,
@@ -268,9 +262,9 @@ hipError_t launch_peaks(const rmsynth_plan_s& p, const float* Fq, const float* F
 hipError_t launch_rmsf(const rmsynth_plan_s& p, float* re, float* im, hipStream_t s);
 hipError_t launch_peak_angle(const rmsynth_plan_s& p, const float* phi_pk, const float* q_pk,
                              const float* u_pk, int64_t nlos, float* chi0, hipStream_t s);
-// Fused peaks of the factored kernels: records per LOS (one per half phi
-// tile), and the merge of the records into the rmsynth_peaks outputs.
-int factored_peak_parts(const rmsynth_plan_s& p);
+// Fused peaks of the split kernels with tables: records per LOS (one per 64
+// phi), and the merge of the records into the rmsynth_peaks outputs.
+int peak_parts(const rmsynth_plan_s& p);
 hipError_t launch_peak_merge(const rmsynth_plan_s& p, const PeakPart* part, int64_t nlos,
                              const float* Fq, const float* Fu, int32_t* idx, float* phi_pk,
                              float* amp, float* q_pk, float* u_pk, hipStream_t s);

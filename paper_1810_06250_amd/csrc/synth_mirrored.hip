@@ -12,6 +12,18 @@
 // depend on the tile and are a plan-time table (FP64 argument reduction) that
 // stays in every XCD's L2.  The nchan x nphi phase matrix is never formed.
 //
+// The folded form (FOLD) is the same idea on the other axis: plans whose
+// contracted axis is uniform, b_c = b_0 + c db, and whose output grid g is not
+// (the adjoint transform on a uniform phi grid, the phi_k being contracted).
+// In K-tiles of L contracted channels centred on b_J (half way between two),
+// the channels at b_J +- h, h = (i + 1/2) db, enter as S = X+ + X- and
+// D = X+ - X-:
+//   F_g = K sum_J exp(-2 pi i b_J g) sum_i (S_i cos - i D_i sin)(2 pi h_i g),
+// half the multiply-adds again.  The cos/sin table does not depend on J; the
+// K-tiles run from the top down and the accumulators are multiplied by
+// exp(-2 pi i L db g) before each (Horner's rule), K exp(-2 pi i b_0' g) of the
+// lowest tile's centre b_0' in the epilogue.
+//
 // The sums run on the matrix cores with FP32 accumulation, in one of
 //   FP32   v_mfma_f32_32x32x2_f32 on FP32 operands,
 //   split  v_mfma_f32_32x32x16_{bf16,f16} on x = hi + lo in 16 bits each,
@@ -48,7 +60,7 @@ constexpr int NH = kMirrorTile / 2;  // pairs per tile
 constexpr int64_t kSmallTiles = 128;  // see launch_mg
 constexpr int SR = kMirrorTile + 4;  // row stride (floats) of the epilogue's tile: conflict-free b128 rows
 
-enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2 };
+enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2, FOLD = 3 };
 
 typedef const __attribute__((address_space(4))) f32x4_t* const_f4_ptr;
 typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
@@ -73,6 +85,10 @@ __device__ __forceinline__ f32x16_t mfma16(uint4 a, uint4 b, f32x16_t c)
 
 // LOAD: how Q/U are read.  ROW4: LOS-major rows of 16-byte aligned quads;
 // ROW: LOS-major, any alignment; PLANE: frequency-major.
+// FOLD: the folded form (LOS-major, any alignment; no flags, no peaks): T is its
+// table, nk the K-steps of all K-tiles, ksteps those of one, pad the zero
+// channels below channel 0, kbase and krot the K exp(-2 pi i b_0' g) and
+// exp(-2 pi i L db g) per output as (cos, sin).
 // FLAGS: some channel has weight 0; its (zero) rotation then also clears
 // whatever the data hold there, NaN included.
 // MG: LOS groups (of 32) per tile; the results do not depend on it.
@@ -86,8 +102,10 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     const float2* __restrict__ base, const uint4* __restrict__ T, int nchan_pad, int nk, int nphi,
     int tiles_n, float* __restrict__ Fq, float* __restrict__ Fu, float* __restrict__ Fabs,
     const float* __restrict__ los_scale, PeakPart* __restrict__ part, int64_t part_ld,
-    PeakRec* __restrict__ rec)
+    PeakRec* __restrict__ rec, int ksteps, int pad, const float2* __restrict__ kbase,
+    const float2* __restrict__ krot)
 {
+    static_assert(LOAD != FOLD || (PEAKS == 0 && !FLAGS), "the folded form has no peaks and no flags");
     constexpr bool F32 = PREC == RMSYNTH_FP32;
     constexpr int MT = 32 * MG;      // LOS per tile
     constexpr int STEP = 4 * MT * 2;  // uint4 of a packed K-step: [2 channel octets or quad pairs][4][MT]
@@ -124,7 +142,22 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     const float* const Qt = LOAD == LOAD_PLANE ? Q + l0 : Q + l0 * ld;
     const float* const Ut = LOAD == LOAD_PLANE ? U + l0 : U + l0 * ld;
     const_f4_ptr bt = (const_f4_ptr)(base + (int64_t)tn * nchan_pad);
-    const uint4* const Tw = T + wave * 256 + lane;
+    // FOLD: eight lanes share a LOS row, lane cc the pair cc of the K-step, rows
+    // rq + 32 i: a wave's load covers 8 rows x 32 contiguous bytes.
+    const int cc = t & 7, rq = t >> 3;
+    uint32_t frow[MG];
+    float fsc[MG];
+    if constexpr (LOAD == FOLD) {
+#pragma unroll
+        for (int i = 0; i < MG; ++i) {
+            const int r = rq + 32 * i < left ? rq + 32 * i : (int)left;
+            frow[i] = 4u * (uint32_t)(r * (int)ld);
+            fsc[i] = PREC == RMSYNTH_SPLIT_FP16 ? los_scale[l0 + r] : 1.0f;
+        }
+    }
+    // Table columns of this wave: [K-step][64-output block][4][64 lanes].
+    const uint4* const Tw = T + (LOAD == FOLD ? 4 * tn + wave : wave) * 256 + lane;
+    const int tstep = LOAD == FOLD ? 1024 * tiles_n : 1024;
 
     struct Data {
         float q[4], u[4];
@@ -134,7 +167,49 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     };
     f32x4_t rot[2];  // (cos, sin) K w_j of the quad to be packed next
 
+    // FOLD: K-tile and K-step within it of the current step, and of the K-step d
+    // further on (at most one K-tile away, or clamped to the last; d is passed
+    // where the other forms pass a K-step's number).
+    int cj = 0, ck = 0;
+    auto ahead = [&](int d, int& j, int& kk) __attribute__((always_inline)) {
+        j = cj;
+        kk = ck + d;
+        if (kk >= ksteps) {
+            kk -= ksteps;
+            --j;
+        }
+        if (j < 0) {
+            j = 0;
+            kk = ksteps - 1;
+        }
+    };
+    auto pair_channels = [&](int d, int& jp, int& jm) __attribute__((always_inline)) {
+        int J, kk;
+        ahead(d, J, kk);
+        const int mid = J * ksteps * KC - pad + ksteps * (KC / 2);
+        jp = mid + kk * (KC / 2) + cc;
+        jm = mid - 1 - kk * (KC / 2) - cc;
+    };
     auto load_data = [&](Data& R, int k) __attribute__((always_inline)) {
+        if constexpr (LOAD == FOLD) {
+            // q, u [0, 1]: the pair's upper channel, [2, 3]: its lower one, of
+            // rows i; channels past either end are cleared when packed.
+            int jp, jm;
+            pair_channels(k, jp, jm);
+            const uint32_t op = 4u * (uint32_t)(jp < 0 ? 0 : jp < nchan ? jp : nchan - 1);
+            const uint32_t om = 4u * (uint32_t)(jm < 0 ? 0 : jm < nchan ? jm : nchan - 1);
+#pragma unroll
+            for (int i = 0; i < MG; ++i) {
+                auto at = [&](const float* b, uint32_t o) {
+                    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b) + (frow[i] + o));
+                };
+                R.q[i] = at(Qt, op);
+                R.u[i] = at(Ut, op);
+                R.q[2 + i] = at(Qt, om);
+                R.u[2 + i] = at(Ut, om);
+            }
+            return;
+        }
         const int j0 = k * KC + 4 * wave;
         if (LOAD == LOAD_ROW4) {
             const int j = j0 < nchan ? j0 : nchan - 4;
@@ -153,19 +228,39 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         }
     };
     auto load_rot = [&](int k) __attribute__((always_inline)) {
+        if (LOAD == FOLD) return;
         const int at = (k * KC + 4 * wave) >> 1;
         rot[0] = bt[at];
         rot[1] = bt[at + 1];
     };
     auto load_b = [&](Frag& B, int k) __attribute__((always_inline)) {
-        const uint4* p = Tw + (int64_t)k * (4 * 256);
+        if constexpr (LOAD == FOLD) {
+            int j;
+            ahead(k, j, k);
+        }
+        const uint4* p = Tw + (int64_t)k * tstep;
 #pragma unroll
         for (int i = 0; i < 4; ++i) B.v[i] = p[64 * i];
     };
     // Rotate and pack the quad: FP32 as float4 x, y of quad `wave`; split as
     // the 8-byte half of the channel octet's x hi, x lo, y hi, y lo.
     float px[4], py[4];
-    auto rotate1 = [&](const Data& R, int i) __attribute__((always_inline)) {
+    auto rotate1 = [&](const Data& R, int i, int k) __attribute__((always_inline)) {
+        if constexpr (LOAD == FOLD) {
+            // i < MG: S, D of row i as px = (Sx, Dy), py = (Sy, -Dx)
+            if (i >= MG) return;
+            const float sc = fsc[i];
+            int jp, jm;
+            pair_channels(k, jp, jm);
+            const bool okp = (uint32_t)jp < (uint32_t)nchan, okm = (uint32_t)jm < (uint32_t)nchan;
+            const float xp = okp ? R.q[i] * sc : 0.0f, xm = okm ? R.q[2 + i] * sc : 0.0f;
+            const float yp = okp ? R.u[i] * sc : 0.0f, ym = okm ? R.u[2 + i] * sc : 0.0f;
+            px[2 * i] = xp + xm;
+            px[2 * i + 1] = yp - ym;
+            py[2 * i] = yp + ym;
+            py[2 * i + 1] = xm - xp;
+            return;
+        }
         const f32x4_t rr = rot[i >> 1];
         const float rc = (i & 1) ? rr.z : rr.x;
         const float rs = (i & 1) ? rr.w : rr.y;
@@ -184,6 +279,28 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         py[i] = yr;
     };
     auto store_data = [&](int buf) __attribute__((always_inline)) {
+        if constexpr (LOAD == FOLD) {
+            // rows Re: (Sx, Dy), Im: (Sy, -Dx) against columns (cos, sin).  Split:
+            // [pair quad][Re hi, Re lo, Im hi, Im lo][row], one dword per pair;
+            // FP32: [pair quad][Re, Im][cos part, sin part][row], one float each.
+#pragma unroll
+            for (int i = 0; i < MG; ++i) {
+                uint32_t* const a = reinterpret_cast<uint32_t*>(&lds.a[buf][(cc >> 2) * (4 * MT) + rq + 32 * i]) + (cc & 3);
+                uint32_t w[4];
+                if (F32) {
+                    w[0] = __float_as_uint(px[2 * i]);
+                    w[1] = __float_as_uint(px[2 * i + 1]);
+                    w[2] = __float_as_uint(py[2 * i]);
+                    w[3] = __float_as_uint(py[2 * i + 1]);
+                } else {
+                    split2<PREC>(px[2 * i], px[2 * i + 1], w[0], w[1]);
+                    split2<PREC>(py[2 * i], py[2 * i + 1], w[2], w[3]);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[4 * MT * e] = w[e];
+            }
+            return;
+        }
         if (F32) {
             // [quad pair][x, y][quad of the pair][row]
             uint4* const a = &lds.a[buf][(wave >> 1) * (4 * MT) + (wave & 1) * MT + row];
@@ -215,7 +332,8 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         }
     };
 
-    // acc[g][s]: LOS group g (32 LOS), sums s = xc, ys, yc, xs.
+    // acc[g][s]: LOS group g (32 LOS), sums s = xc, ys, yc, xs (FOLD: with Re, Im
+    // for x, y and the wave's two blocks of 32 columns for c, s).
     f32x16_t acc[MG][4];
 #pragma unroll
     for (int g = 0; g < MG; ++g)
@@ -223,6 +341,18 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         for (int s = 0; s < 4; ++s)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[g][s][v] = 0.0f;
+
+    // (re, im) <- (re + i im)(r.x - i r.y), few elements at a time: done all at
+    // once the accumulators would need a second set of registers.
+    auto turn = [](f32x16_t& re, f32x16_t& im, float2 r) __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float a = re[v], b = im[v];
+            re[v] = __builtin_fmaf(a, r.x, b * r.y);
+            im[v] = __builtin_fmaf(b, r.x, -(a * r.y));
+            if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
 
     auto mma = [&](const Frag& A, const Frag& B, int g, auto&& midway) __attribute__((always_inline)) {
         if constexpr (F32) {
@@ -278,6 +408,7 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     // loads and stores stay in bounds and are never used.
     Frag A0, A1;
     int bc = 0;
+    auto next = [&](int k, int d) { return LOAD == FOLD ? d : k + d < nk ? k + d : nk - 1; };
     auto step = [&](const Frag& B, Frag& Bn, Data& R, int k) __attribute__((always_inline)) {
         const int bf = bc == 2 ? 0 : bc + 1;
         const int bn = bf == 2 ? 0 : bf + 1;
@@ -286,50 +417,73 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         // would cover them too) and ahead of its last matrix instructions.
         auto next_rot = [&]() __attribute__((always_inline)) {
             __builtin_amdgcn_sched_barrier(0);
-            load_rot(k + 3 < nk ? k + 3 : nk - 1);
+            load_rot(next(k, 3));
             __builtin_amdgcn_sched_barrier(0);
         };
-        load_b(Bn, k + 1 < nk ? k + 1 : nk - 1);
+        load_b(Bn, next(k, 1));
         if (MG == 2) load_a(A1, bc, 1);
         __builtin_amdgcn_sched_barrier(0);
         mma(A0, B, 0, [] {});
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rotate1(R, i);
+        for (int i = 0; i < 4; ++i) rotate1(R, i, next(k, 2));
         store_data(bn);
         __builtin_amdgcn_sched_barrier(0);
-        load_data(R, k + 4 < nk ? k + 4 : nk - 1);
+        load_data(R, next(k, 4));
         load_a(A0, bf, 0);
         if (MG == 2) mma(A1, B, MG - 1, next_rot);
         else next_rot();
         __builtin_amdgcn_sched_barrier(0);
         sync_next();
         bc = bf;
+        if (LOAD == FOLD && ++ck == ksteps) {
+            ck = 0;
+            --cj;
+        }
     };
 
     Data R0, R1;
     Frag B0, B1;
+    if (LOAD == FOLD) cj = nk / ksteps - 1;
     load_data(R0, 0);
-    load_data(R1, nk > 1 ? 1 : 0);
+    load_data(R1, next(0, 1));
     load_rot(0);
     load_b(B0, 0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) rotate1(R0, i);
+    for (int i = 0; i < 4; ++i) rotate1(R0, i, 0);
     store_data(0);
-    load_rot(nk > 1 ? 1 : 0);
+    load_rot(next(0, 1));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) rotate1(R1, i);
+    for (int i = 0; i < 4; ++i) rotate1(R1, i, next(0, 1));
     store_data(1);
-    load_data(R0, nk > 2 ? 2 : nk - 1);
-    load_data(R1, nk > 3 ? 3 : nk - 1);
-    load_rot(nk > 2 ? 2 : nk - 1);
+    load_data(R0, next(0, 2));
+    load_data(R1, next(0, 3));
+    load_rot(next(0, 2));
     sync_next();
     load_a(A0, 0, 0);
-    int k = 0;
-    for (; k + 1 < nk; k += 2) {
-        step(B0, B1, R0, k);
-        step(B1, B0, R1, k + 1);
+    if constexpr (LOAD == FOLD) {
+        // The outputs of this lane: columns 64 wave + col (Re, Im in acc[g][0],
+        // acc[g][2]) and 32 further (acc[g][3], acc[g][1]).  Before each K-tile
+        // acc <- r acc (the first time on zeros); ksteps is even.
+        const float2 r0 = krot[n0 + 64 * wave + col], r1 = krot[n0 + 64 * wave + 32 + col];
+        for (int k = 0; k < nk; k += 2) {
+            if (ck == 0) {
+#pragma unroll
+                for (int g = 0; g < MG; ++g) {
+                    turn(acc[g][0], acc[g][2], r0);
+                    turn(acc[g][3], acc[g][1], r1);
+                }
+            }
+            step(B0, B1, R0, k);
+            step(B1, B0, R1, k + 1);
+        }
+    } else {
+        int k = 0;
+        for (; k + 1 < nk; k += 2) {
+            step(B0, B1, R0, k);
+            step(B1, B0, R1, k + 1);
+        }
+        if (k < nk) step(B0, B1, R0, k);
     }
-    if (k < nk) step(B0, B1, R0, k);
 
     // Epilogue.  Rows of this lane: 32 g + 8 (v >> 2) + 4 half + (v & 3).
     if (PREC == RMSYNTH_SPLIT_FP16) {
@@ -346,8 +500,21 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
                 for (int s = 0; s < 4; ++s) acc[g][s][v] *= inv;
             }
     }
-    // The sums become the outputs in place: Fq, Fu at +h in acc[g][0], acc[g][2],
-    // at -h in acc[g][1], acc[g][3].
+    // The sums become the outputs in place: Fq, Fu of column cp in acc[g][0],
+    // acc[g][2], of column cm in acc[g][1], acc[g][3].
+    const int cp = LOAD == FOLD ? 64 * wave + col : NH + 32 * wave + col;            // +h
+    const int cm = LOAD == FOLD ? 64 * wave + 32 + col : NH - 1 - 32 * wave - col;  // -h
+    if constexpr (LOAD == FOLD) {
+        const float2 b0 = kbase[n0 + cp], b1 = kbase[n0 + cm];
+#pragma unroll
+        for (int g = 0; g < MG; ++g) {
+            turn(acc[g][0], acc[g][2], b0);
+            turn(acc[g][3], acc[g][1], b1);
+            const f32x16_t re = acc[g][3];
+            acc[g][3] = acc[g][1];
+            acc[g][1] = re;
+        }
+    } else {
 #pragma unroll
     for (int g = 0; g < MG; ++g)
 #pragma unroll
@@ -358,7 +525,7 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
             acc[g][2][v] = yc - xs;
             acc[g][3][v] = yc + xs;
         }
-    const int cp = NH + 32 * wave + col, cm = NH - 1 - 32 * wave - col;  // columns of +h and -h
+    }
     // Outputs go through LDS (free once every wave has passed the last K-step's
     // barrier), one quantity of the whole tile at a time, so that a store covers
     // a row's 256 phi: rows of nphi floats are in general not 16-byte aligned,
@@ -525,10 +692,62 @@ __global__ void mirror_tables_kernel(const double* __restrict__ bj, const float*
     }
 }
 
+// Tables of the folded form (FP64 argument reduction, FP32 sin/cos):
+//   T[K-step][64-output block][4][lane], (c, s) = (cos, sin)(2 pi (i + 1/2) db g)
+//   of the 8 pairs of the K-step: split: hi, lo of (c, s) of the pair quad
+//   lane >> 5 for output lane & 31, then for output 32 + (lane & 31); FP32: for
+//   each pair quad the same two outputs, c for lanes 0-31, s for lanes 32-63;
+//   kbase = K (cos, sin)(2 pi b_0' g), krot = (cos, sin)(2 pi L db g).
+__global__ void fold_tables_kernel(const double* __restrict__ grid, int nphi_pad, int ksteps, double b0c,
+                                   double db, double K, float2* __restrict__ kbase,
+                                   float2* __restrict__ krot, uint4* __restrict__ Tbf,
+                                   uint4* __restrict__ Thf, uint4* __restrict__ Tf32)
+{
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx < (int64_t)ksteps * nphi_pad) {  // 64 lanes per 64-output block
+        const int kk = (int)(idx / nphi_pad), at = (int)(idx % nphi_pad), lane = at & 63;
+        const int64_t o = 4 * (idx - lane) + lane;
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+            const double g = grid[at - lane + 32 * cb + (lane & 31)];
+            float c[4], s[4];
+            uint32_t h[4], l[4];
+            auto phase = [&](int quad) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    phase_cos_sin(((double)(8 * kk + 4 * quad + e) + 0.5) * db * g, c[e], s[e]);
+            };
+            phase(lane >> 5);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) split2_bf16(c[e], s[e], h[e], l[e]);
+            Tbf[o + 64 * (2 * cb)] = make_uint4(h[0], h[1], h[2], h[3]);
+            Tbf[o + 64 * (2 * cb + 1)] = make_uint4(l[0], l[1], l[2], l[3]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) split2_f16(c[e], s[e], h[e], l[e]);
+            Thf[o + 64 * (2 * cb)] = make_uint4(h[0], h[1], h[2], h[3]);
+            Thf[o + 64 * (2 * cb + 1)] = make_uint4(l[0], l[1], l[2], l[3]);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                phase(p);
+                const f32x4_t v = lane < 32 ? f32x4_t{c[0], c[1], c[2], c[3]} : f32x4_t{s[0], s[1], s[2], s[3]};
+                Tf32[o + 64 * (2 * p + cb)] = __builtin_bit_cast(uint4, v);
+            }
+        }
+    }
+    if (idx < nphi_pad) {
+        float c, s;
+        phase_cos_sin(b0c * grid[idx], c, s);
+        kbase[idx] = make_float2((float)K * c, (float)K * s);
+        phase_cos_sin((double)(ksteps * KC) * db * grid[idx], c, s);
+        krot[idx] = make_float2(c, s);
+    }
+}
+
 template <int LOAD, int PREC, int MG>
 hipError_t launch(const rmsynth_plan_s& p, const ExecArgs& a)
 {
-    const int nk = (p.nchan + KC - 1) / KC;
+    // Folded: K-tiles of ksteps K-steps, kpad channels below channel 0.
+    const int nk = LOAD == FOLD ? (p.nchan + p.kpad) / KC : (p.nchan + KC - 1) / KC;
     const int64_t blocks = (a.nlos + 32 * MG - 1) / (32 * MG) * p.ftiles;
     if (blocks <= 0) return hipSuccess;
     const uint4* T = PREC == RMSYNTH_FP32 ? p.d_Tf32 : PREC == RMSYNTH_SPLIT_FP16 ? p.d_Thf : p.d_Tbf;
@@ -536,10 +755,10 @@ hipError_t launch(const rmsynth_plan_s& p, const ExecArgs& a)
     hipLaunchKernelGGL((synth_mirrored_kernel<LOAD, PREC, G, P, MG>), dim3((unsigned)blocks), dim3(256),  \
                        0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_base, T, p.nchan_pad, nk,      \
                        p.nphi, p.ftiles, a.Fq, a.Fu, a.Fabs, a.los_scale, a.peak_part, a.peak_part_ld,   \
-                       a.peak_rec)
+                       a.peak_rec, p.ksteps, p.kpad, p.d_kbase, p.d_krot)
 #define RMS_LAUNCH_P(G)                                                               \
     do {                                                                              \
-        if constexpr (PREC != RMSYNTH_FP32) { /* FP32: peaks are a kernel of their own */ \
+        if constexpr (PREC != RMSYNTH_FP32 && LOAD != FOLD) { /* elsewhere peaks are a kernel of their own */ \
             if (a.peak_rec) RMS_LAUNCH(G, 2);                                         \
             else if (a.peak_part) RMS_LAUNCH(G, 1);                                   \
             else RMS_LAUNCH(G, 0);                                                    \
@@ -547,8 +766,12 @@ hipError_t launch(const rmsynth_plan_s& p, const ExecArgs& a)
             RMS_LAUNCH(G, 0);                                                         \
         }                                                                             \
     } while (0)
-    if (p.any_flagged) RMS_LAUNCH_P(true);
-    else RMS_LAUNCH_P(false);
+    if constexpr (LOAD != FOLD) {
+        if (p.any_flagged) RMS_LAUNCH_P(true);
+        else RMS_LAUNCH_P(false);
+    } else {
+        RMS_LAUNCH_P(false);  // adjoint plans weight every channel 1
+    }
 #undef RMS_LAUNCH_P
 #undef RMS_LAUNCH
     return hipGetLastError();
@@ -569,6 +792,7 @@ hipError_t launch_mg(const rmsynth_plan_s& p, const ExecArgs& a)
 template <int PREC>
 hipError_t launch_load(const rmsynth_plan_s& p, const ExecArgs& a)
 {
+    if (p.cuniform) return launch_mg<FOLD, PREC>(p, a);
     if (a.layout != RMSYNTH_LOS_MAJOR) return launch_mg<LOAD_PLANE, PREC>(p, a);
     return a.vec4 ? launch_mg<LOAD_ROW4, PREC>(p, a) : launch_mg<LOAD_ROW, PREC>(p, a);
 }
@@ -588,6 +812,17 @@ hipError_t launch_mirror_tables(const rmsynth_plan_s& p, hipStream_t stream)
     const int64_t n = std::max<int64_t>((int64_t)nk * 256, (int64_t)p.ftiles * p.nchan_pad);
     hipLaunchKernelGGL(mirror_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
                        p.d_b, p.d_w, p.nchan_pad, nk, p.ftiles, p.phi0, p.dphi, p.K, p.d_base, p.d_Tbf,
+                       p.d_Thf, p.d_Tf32);
+    return hipGetLastError();
+}
+
+hipError_t launch_fold_tables(const rmsynth_plan_s& p, hipStream_t stream)
+{
+    // centre of the lowest K-tile: channel -kpad + L/2 - 1/2
+    const double b0c = p.kb0 + (0.5 * p.ksteps * KC - 0.5 - p.kpad) * p.kdb;
+    const int64_t n = (int64_t)p.ksteps * p.nphi_pad;
+    hipLaunchKernelGGL(fold_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
+                       p.d_phi, p.nphi_pad, p.ksteps, b0c, p.kdb, p.K, p.d_kbase, p.d_krot, p.d_Tbf,
                        p.d_Thf, p.d_Tf32);
     return hipGetLastError();
 }

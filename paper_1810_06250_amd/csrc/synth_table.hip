@@ -1,22 +1,7 @@
-// Split-precision contraction against a phase table, for plans whose output
-// grid is not uniform (uniform output grids: synth_mirrored.hip).
-//
-// KF: the contracted axis is uniform (the adjoint transform on a uniform phi
-// grid, where the phi_k are the contracted "channels" b_j = b_0 + j db).  With
-// K-tiles of KT = 96 channels starting at j_J = J KT - P (P channels of zero
-// padding below channel 0 make the top K-tile full), j = j_J + i,
-//   exp(-2 pi i b_j g_k) = base_k r_k^J T'_{i,k},  base_k = exp(-2 pi i (b_0 - P db) g_k),
-//   r_k = exp(-2 pi i KT db g_k),  T'_{i,k} = exp(-2 pi i i db g_k),
-// so F_k = K base_k sum_J r_k^J S_J(k) with S_J the contraction of K-tile J
-// against the table T' (KT x nphi, tile-independent).  The K-tiles are taken
-// from the top down and the accumulators are multiplied by r_k before each
-// new K-tile (Horner's rule), K base_k in the epilogue; the data are only
-// split, not rotated.  KT is a multiple of three K-steps, so every K-tile
-// starts at the same point of the loop's register rotation.
-//
-// ET: neither axis is uniform; the plan holds the whole split phase matrix (a
-// plan-time table of nchan x nphi entries, capped in size), the B tiles are
-// read from it, and the data are only weighted (K w_j).
+// Split-precision contraction against a stored phase table, for plans neither
+// of whose axes is uniform (else synth_mirrored.hip): the plan holds the whole
+// split phase matrix (nchan x nphi entries, capped in size), the B tiles are
+// read from it, and the data are only weighted (K w_j) and split.
 //
 // Contraction: v_mfma_f32_32x32x16_{bf16,f16}, hi*hi + hi*lo + lo*hi with FP32
 // accumulation.  Real form of eqs. (15)-(16): A rows (x', y') and (y', -x')
@@ -35,18 +20,14 @@
 // busy.  Q/U loads run two K-steps ahead of their use.
 #include <float.h>
 
-#include <type_traits>
-
 #include "common.h"
 
 namespace {
 
 constexpr int MT = 128;          // LOS per tile
-constexpr int NT = kFactorTile;  // phi per tile
+constexpr int NT = kTableTile;  // phi per tile
 constexpr int KC = 8;            // channels per K-step
 constexpr int NQ = KC / 4;       // channel quads per K-step
-constexpr int KTS = kKTile / KC;  // K-steps per K-tile (KF)
-static_assert(KTS % 3 == 0, "a K-tile holds whole blocks of three K-steps");
 
 struct ABuf {
     uint4 a_hi[NQ][MT];
@@ -104,27 +85,22 @@ __device__ __forceinline__ f32x16_t mfma16(uint4 a, uint4 b, f32x16_t c)
 // peak_merge_kernel, at part[half tile * part_ld + LOS].
 // PEAKS 2: F is not stored; the epilogue writes one PeakRec per (LOS, half
 // tile) instead, at rec[half tile * part_ld + LOS], for peak_merge_rec_kernel.
-// KF: base holds (w_j, 0) per channel, Thi/Tlo hold T' as [KT/4][ldT] quads,
-// kbase and krot the K base_k and r_k per output (LOS-major input, no peaks).
-// Otherwise (ET) Thi/Tlo hold the phase table, [nchan/4][ldT] quads, and base
-// (K w_j, 0) per channel.
-template <int LAYOUT, bool FP16, bool FAST, bool FLAGS, int PEAKS, bool KF>
-__global__ __launch_bounds__(256, 2) void synth_factored_kernel(
+// base holds (K w_j, 0) per channel, Thi/Tlo the phase table, [nchan/4][ldT]
+// quads.
+template <int LAYOUT, bool FP16, bool FAST, bool FLAGS, int PEAKS>
+__global__ __launch_bounds__(256, 2) void synth_table_kernel(
     const float* __restrict__ Q, const float* __restrict__ U, int64_t nlos, int64_t ld,
     int nchan, const float2* __restrict__ base, const uint4* __restrict__ Thi,
     const uint4* __restrict__ Tlo, int nchan_pad, int nk, int nphi, int tiles_n,
     float* __restrict__ Fq, float* __restrict__ Fu, float* __restrict__ Fabs,
     const float* __restrict__ los_scale, PeakPart* __restrict__ part, int64_t part_ld,
-    PeakRec* __restrict__ rec, uint32_t neg_hi, const float2* __restrict__ kbase,
-    const float2* __restrict__ krot, int ldT)
+    PeakRec* __restrict__ rec, uint32_t neg_hi, int ldT)
 {
-    static_assert(!KF || (PEAKS == 0 && LAYOUT == RMSYNTH_LOS_MAJOR), "KF: LOS-major, no peaks");
     // Triple-buffered A tiles (packed data) and T tiles (phase table), in one
     // block so that the epilogue can reuse all of it.
     struct Lds {
         ABuf a[3];
         BBuf b[3];
-        float2 krot[KF ? NT : 1];  // KF: r_k of the tile's outputs
     };
     __shared__ Lds lds;
     ABuf* const abuf = lds.a;
@@ -148,68 +124,26 @@ __global__ __launch_bounds__(256, 2) void synth_factored_kernel(
     // FP16: per-LOS power-of-two scale that keeps both halves of the split in
     // half precision's normal range; undone exactly in the epilogue.
     const float lsc = FP16 ? los_scale[lr] : 1.0f;
-    // KF on rows that allow no 16-byte loads (COAL): eight lanes share a LOS
-    // row, lane cc reading channel cc of the K-step, rows rq + 32 i (i < 4),
-    // so that a wave's load covers 8 rows x 32 contiguous bytes.  The KF
-    // plans (adjoint plans) have unit weights and no flagged channel, so
-    // nothing is weighted or rotated.  Loads take the tile's first row as a
-    // uniform base and a 32-bit byte offset (128 rows: far below 2^32); rows
-    // past the cube read the last LOS.
-    constexpr bool COAL = KF && !FAST;
-    const int cc = t & 7, rq = t >> 3;
-    const float* Qt = Q + (COAL ? l0 * ld : 0);
-    const float* Ut = U + (COAL ? l0 * ld : 0);
-    const uint32_t crow0 = (uint32_t)(rq * ld * 4), crow_step = (uint32_t)(32 * ld * 4);
-    const uint32_t crow_last = (uint32_t)(((nlos - 1 - l0) < MT ? (nlos - 1 - l0) : MT - 1) * ld * 4);
-    float csc[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t g = l0 + rq + 32 * i;
-        csc[i] = COAL && FP16 ? los_scale[g < nlos ? g : nlos - 1] : 1.0f;
-    }
     const_f4_ptr bt = (const_f4_ptr)base;
-    // KF: the K-step contracted at position k of the loop.  K-tile J covers
-    // K-steps J KTS - pad .. (J + 1) KTS - pad - 1; the full K-tiles come
-    // first, from the top down, then the valid K-steps of K-tile 0.
-    const int ntile = (nk + KTS - 1) / KTS;
-    const int pad = ntile * KTS - nk;
-    const int kfull = (ntile - 1) * KTS;
-    auto ks_of = [&](int k) {
-        if (!KF) return k;
-        const int top = (ntile - 1 - k / KTS) * KTS - pad + k % KTS;
-        return k < kfull ? top : k - kfull;  // a select: no branch around the loads
-    };
-
     // Q/U and channel rotations of one K-step (4 channels of this thread),
     // held in registers; three sets rotate (see the K-loop below).
-    struct RegsRot {
+    struct Regs {
         float q[4], u[4];
         f32x4_t rot[2];  // K w_j (cos, sin) of theta_{j,k0}, 2 channels per vector
         uint4 th, tl;    // this thread's 16-byte share of the K-step's T tile
     };
-    struct RegsCoal {    // COAL: nothing to rotate
-        float q[4], u[4];
-        uint4 th, tl;
-    };
-    using Regs = typename std::conditional<COAL, RegsCoal, RegsRot>::type;
     Regs R0, R1, R2;
 
     auto gload_rot = [&](Regs& R, int k) __attribute__((always_inline)) {
-        if constexpr (!COAL) {
-            const int ks = ks_of(k);
-            const int j0 = ks * KC + 4 * hh;
-            R.rot[0] = bt[(j0 >> 1)];
-            R.rot[1] = bt[(j0 >> 1) + 1];
-        }
+        const int j0 = k * KC + 4 * hh;
+        R.rot[0] = bt[(j0 >> 1)];
+        R.rot[1] = bt[(j0 >> 1) + 1];
     };
     auto gload_vec = [&](Regs& R, int k) __attribute__((always_inline)) {
-        const int ks = ks_of(k);
-        const int j0 = ks * KC + 4 * hh;
-        if (!KF) {
-            const int64_t at = (int64_t)(ks * NQ + (t >> 7)) * ldT + n0 + (t & 127);
-            R.th = Thi[at];
-            R.tl = Tlo[at];
-        }
+        const int j0 = k * KC + 4 * hh;
+        const int64_t at = (int64_t)(k * NQ + (t >> 7)) * ldT + n0 + (t & 127);
+        R.th = Thi[at];
+        R.tl = Tlo[at];
         if (FAST) {
             if (LAYOUT == RMSYNTH_LOS_MAJOR) {
                 const float4 a = *reinterpret_cast<const float4*>(Q + lr * ld + j0);
@@ -222,21 +156,6 @@ __global__ __launch_bounds__(256, 2) void synth_factored_kernel(
                     R.q[i] = Q[(int64_t)(j0 + i) * ld + lr];
                     R.u[i] = U[(int64_t)(j0 + i) * ld + lr];
                 }
-            }
-        } else if (COAL) {
-            // Channels past the end load the last one (in bounds) and read as 0;
-            // no branch, which keeps the register sets in registers.
-            const int j = ks * KC + cc;
-            const bool ok = j < nchan;
-            const uint32_t jb = 4u * (uint32_t)(ok ? j : nchan - 1);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t ro = crow0 + i * crow_step;
-                const uint32_t off = (ro < crow_last ? ro : crow_last) + jb;
-                const float a = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Qt) + off);
-                const float b = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ut) + off);
-                R.q[i] = ok ? a : 0.0f;
-                R.u[i] = ok ? b : 0.0f;
             }
         } else {
 #pragma unroll
@@ -258,48 +177,27 @@ __global__ __launch_bounds__(256, 2) void synth_factored_kernel(
     // Channel i of the thread's 4: rotate, split.
     uint32_t hi[4], lo[4];
     auto pack1 = [&](const Regs& R, int i) __attribute__((always_inline)) {
-        if constexpr (COAL) {
-            split2<FP16>(R.q[i] * csc[i], R.u[i] * csc[i], hi[i], lo[i]);
-        } else {
-            const f32x4_t rr = R.rot[i >> 1];
-            const float rc = (i & 1) ? rr.z : rr.x;
-            const float rs = (i & 1) ? rr.w : rr.y;
-            float xr = __builtin_fmaf(R.q[i], rc, R.u[i] * rs);
-            float yr = __builtin_fmaf(R.u[i], rc, -(R.q[i] * rs));
-            if (FLAGS) {
-                const bool flagged = ((__float_as_uint(rc) | __float_as_uint(rs)) << 1) == 0u;
-                xr = flagged ? 0.0f : xr;
-                yr = flagged ? 0.0f : yr;
-            }
-            if (FP16) {
-                xr *= lsc;
-                yr *= lsc;
-            }
-            split2<FP16>(xr, yr, hi[i], lo[i]);
+        const f32x4_t rr = R.rot[i >> 1];
+        const float rc = (i & 1) ? rr.z : rr.x;
+        const float rs = (i & 1) ? rr.w : rr.y;
+        float xr = __builtin_fmaf(R.q[i], rc, R.u[i] * rs);
+        float yr = __builtin_fmaf(R.u[i], rc, -(R.q[i] * rs));
+        if (FLAGS) {
+            const bool flagged = ((__float_as_uint(rc) | __float_as_uint(rs)) << 1) == 0u;
+            xr = flagged ? 0.0f : xr;
+            yr = flagged ? 0.0f : yr;
         }
+        if (FP16) {
+            xr *= lsc;
+            yr *= lsc;
+        }
+        split2<FP16>(xr, yr, hi[i], lo[i]);
     };
     auto store_t = [&](BBuf& b, const Regs& R) __attribute__((always_inline)) {
         (&b.b_hi[0][0])[t] = R.th;
         (&b.b_lo[0][0])[t] = R.tl;
     };
-    // KF: the T' tile of the K-step at position k, loaded in the K-step that
-    // stores it (T' is small and stays in L2), which keeps it out of the
-    // register sets that hold loads two K-steps ahead.
-    auto load_tk = [&](Regs& R, int k) __attribute__((always_inline)) {
-        const int ks = ks_of(k < nk ? k : nk - 1);
-        const int64_t at = (int64_t)(((ks + pad) % KTS) * NQ + (t >> 7)) * ldT + n0 + (t & 127);
-        R.th = Thi[at];
-        R.tl = Tlo[at];
-    };
     auto store_a = [&](ABuf& b) __attribute__((always_inline)) {
-        if constexpr (COAL) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                reinterpret_cast<uint32_t*>(&b.a_hi[cc >> 2][rq + 32 * i])[cc & 3] = hi[i];
-                reinterpret_cast<uint32_t*>(&b.a_lo[cc >> 2][rq + 32 * i])[cc & 3] = lo[i];
-            }
-            return;
-        }
         b.a_hi[hh][la] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
         b.a_lo[hh][la] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
     };
@@ -396,30 +294,10 @@ __global__ __launch_bounds__(256, 2) void synth_factored_kernel(
     // stored).
     Frag F;
     int bc = 0;  // buffer of K-step k; (bc + 1) % 3 and (bc + 2) % 3 follow
-    // KF: acc <- r acc (complex, Re in acc[g][0], Im in acc[g][1]) before
-    // each K-tile after the first, r_k of this lane's two output columns read
-    // from the tile's copy in LDS (written before the prologue's barrier), so
-    // that they hold no registers across the loop.
-    auto rotate_acc = [&]() __attribute__((always_inline)) {
-        float2 rr[2];
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) rr[cb] = lds.krot[64 * wc + 32 * cb + (lane & 31)];
-#pragma unroll
-        for (int g = 0; g < 2; ++g)
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float a = acc[g][0][cb][v], b = acc[g][1][cb][v];
-                    acc[g][0][cb][v] = __builtin_fmaf(a, rr[cb].x, b * rr[cb].y);
-                    acc[g][1][cb][v] = __builtin_fmaf(b, rr[cb].x, -(a * rr[cb].y));
-                }
-    };
     auto step = [&](Regs& Rp, Regs& Rl, int k) __attribute__((always_inline)) {
         const int bf = bc == 2 ? 0 : bc + 1;
         const int bn = bf == 2 ? 0 : bf + 1;
         const int kl = k + 4 < nk ? k + 4 : nk - 1;
-        if (KF) load_tk(Rp, k + 2);
         gload_vec(Rl, kl);
         __builtin_amdgcn_sched_barrier(0);
         mma(abuf[bc], F, Rp);
@@ -443,35 +321,27 @@ __global__ __launch_bounds__(256, 2) void synth_factored_kernel(
     // Prologue: K-steps 0 and 1 packed into buffers 0 and 1, K-steps 2 and 3
     // loading into R0 and R2, the first fragments of K-step 0 read after the
     // barrier.
-    if (KF && t < NT) lds.krot[t] = krot[n0 + t];
     gload(R0, 0);
     gload(R1, nk > 1 ? 1 : 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) pack1(R0, i);
     store_a(abuf[0]);
-    if (KF) load_tk(R0, 0);
     store_t(bbuf[0], R0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) pack1(R1, i);
     store_a(abuf[1]);
-    if (KF) load_tk(R1, nk > 1 ? 1 : 0);
     store_t(bbuf[1], R1);
     gload(R0, nk > 2 ? 2 : nk - 1);
     gload(R2, nk > 3 ? 3 : nk - 1);
     sync_next();
     load_frag(F, abuf[0], bbuf[0]);
 
-    // KF: a K-tile boundary (every KTS K-steps, a multiple of three) falls at
-    // the top of a block of three K-steps or at the tail; the accumulators
-    // are rotated there.
     int k = 0;
     for (; k + 2 < nk; k += 3) {
-        if (KF && k > 0 && k % KTS == 0) rotate_acc();
         step(R0, R1, k);
         step(R2, R0, k + 1);
         step(R1, R2, k + 2);
     }
-    if (KF && k < nk && k > 0 && k % KTS == 0) rotate_acc();
     if (k < nk) step(R0, R1, k);
     if (k + 1 < nk) step(R2, R0, k + 1);
 
@@ -509,21 +379,6 @@ __global__ __launch_bounds__(256, 2) void synth_factored_kernel(
                     }
                 }
             }
-    }
-    if constexpr (KF) {
-        // F = K base_k (sum over K-tiles), base_k K = (c, s) meaning c - i s.
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            const float2 bk = kbase[nc + 32 * cb];
-#pragma unroll
-            for (int g = 0; g < 2; ++g)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float a = acc[g][0][cb][v], b = acc[g][1][cb][v];
-                    acc[g][0][cb][v] = __builtin_fmaf(a, bk.x, b * bk.y);
-                    acc[g][1][cb][v] = __builtin_fmaf(b, bk.x, -(a * bk.y));
-                }
-        }
     }
     if constexpr (PEAKS != 2) {
 #pragma unroll
@@ -794,72 +649,9 @@ __global__ __launch_bounds__(256) void los_scale_kernel(const float* __restrict_
     scale[l] = __builtin_ldexpf(1.0f, e);
 }
 
-// The channel-factored form (KF): LOS-major input, F stored, no peaks.
+// Any layout, with or without the fused peaks.
 template <bool FP16>
-hipError_t launch_kf(const rmsynth_plan_s& p, const ExecArgs& a)
-{
-    const int tiles_n = (p.nphi + NT - 1) / NT;
-    const int nk = (p.nchan + KC - 1) / KC;
-    const int64_t tiles_m = (a.nlos + MT - 1) / MT;
-    const int64_t blocks = tiles_m * tiles_n;
-    if (blocks <= 0) return hipSuccess;
-    const uint4* Thi = FP16 ? p.d_Khf[0] : p.d_Kbf[0];
-    const uint4* Tlo = FP16 ? p.d_Khf[1] : p.d_Kbf[1];
-    const bool fast = p.nchan % KC == 0 && a.vec4;
-    // KF plans (adjoint plans) weight every channel 1: the flag-free forms.
-    if (p.any_flagged) return hipErrorInvalidValue;
-#define RMS_LAUNCH_KF(F, G)                                                                              \
-    hipLaunchKernelGGL((synth_factored_kernel<RMSYNTH_LOS_MAJOR, FP16, F, G, 0, true>), dim3((unsigned)blocks),  \
-                       dim3(256), 0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_kw, Thi, Tlo,        \
-                       p.nchan_pad, nk, p.nphi, tiles_n, a.Fq, a.Fu, a.Fabs, a.los_scale, nullptr,       \
-                       (int64_t)0, nullptr, 0x80000000u, p.d_kbase, p.d_krot, p.nphi_pad)
-    if (fast) RMS_LAUNCH_KF(true, false);
-    else RMS_LAUNCH_KF(false, false);
-#undef RMS_LAUNCH_KF
-    return hipGetLastError();
-}
-
-// Tables of the channel-factored form (FP64 argument reduction, FP32 sin/cos):
-//   T'[i/4][k] (4 channels x (cos, sin)(2 pi i db g_k), split), kbase_k, krot_k,
-//   kw_j = (w_j, 0).
-__global__ void kfactor_tables_kernel(const double* __restrict__ g, const float* __restrict__ wj,
-                                      int nphi_pad, int nchan_pad, double b0, double db, int kpad,
-                                      double K,
-                                      float2* __restrict__ kw, float2* __restrict__ kbase,
-                                      float2* __restrict__ krot, uint4* __restrict__ bf_hi,
-                                      uint4* __restrict__ bf_lo, uint4* __restrict__ hf_hi,
-                                      uint4* __restrict__ hf_lo)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nT = (int64_t)(kKTile / 4) * nphi_pad;
-    if (idx < nT) {
-        const int quad = (int)(idx / nphi_pad), k = (int)(idx % nphi_pad);
-        uint32_t bh[4], bl[4], hh[4], hl[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            float c, sn;
-            phase_cos_sin((double)(4 * quad + e) * db * g[k], c, sn);
-            split2_bf16(c, sn, bh[e], bl[e]);
-            split2_f16(c, sn, hh[e], hl[e]);
-        }
-        bf_hi[idx] = make_uint4(bh[0], bh[1], bh[2], bh[3]);
-        bf_lo[idx] = make_uint4(bl[0], bl[1], bl[2], bl[3]);
-        hf_hi[idx] = make_uint4(hh[0], hh[1], hh[2], hh[3]);
-        hf_lo[idx] = make_uint4(hl[0], hl[1], hl[2], hl[3]);
-    }
-    if (idx < nphi_pad) {
-        float c, sn;
-        phase_cos_sin((b0 - (double)kpad * db) * g[idx], c, sn);
-        kbase[idx] = make_float2((float)K * c, (float)K * sn);
-        phase_cos_sin((double)kKTile * db * g[idx], c, sn);
-        krot[idx] = make_float2(c, sn);
-    }
-    if (idx < nchan_pad) kw[idx] = make_float2(wj[idx], 0.0f);
-}
-
-// The explicit-table form (ET): any layout, with or without the fused peaks.
-template <bool FP16>
-hipError_t launch_et(const rmsynth_plan_s& p, const ExecArgs& a)
+hipError_t launch_t(const rmsynth_plan_s& p, const ExecArgs& a)
 {
     const int tiles_n = (p.nphi + NT - 1) / NT;
     const int nk = (p.nchan + KC - 1) / KC;
@@ -869,32 +661,32 @@ hipError_t launch_et(const rmsynth_plan_s& p, const ExecArgs& a)
     const uint4* Thi = FP16 ? p.d_Ehf[0] : p.d_Ebf[0];
     const uint4* Tlo = FP16 ? p.d_Ehf[1] : p.d_Ebf[1];
     const bool fast = p.nchan % KC == 0 && (a.layout != RMSYNTH_LOS_MAJOR || a.vec4);
-#define RMS_LAUNCH_ET(L, F, G, P)                                                                        \
-    hipLaunchKernelGGL((synth_factored_kernel<L, FP16, F, G, P, false>), dim3((unsigned)blocks), dim3(256),  \
+#define RMS_LAUNCH(L, F, G, P)                                                                        \
+    hipLaunchKernelGGL((synth_table_kernel<L, FP16, F, G, P>), dim3((unsigned)blocks), dim3(256),  \
                        0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_ew, Thi, Tlo, p.nchan_pad, nk,  \
                        p.nphi, tiles_n, a.Fq, a.Fu, a.Fabs, a.los_scale, a.peak_part, a.peak_part_ld,    \
-                       a.peak_rec, 0x80000000u, nullptr, nullptr, p.nphi_pad)
-#define RMS_LAUNCH_ET_P(L, F, G)                      \
+                       a.peak_rec, 0x80000000u, p.nphi_pad)
+#define RMS_LAUNCH_P(L, F, G)                      \
     do {                                              \
-        if (a.peak_rec) RMS_LAUNCH_ET(L, F, G, 2);    \
-        else if (a.peak_part) RMS_LAUNCH_ET(L, F, G, 1); \
-        else RMS_LAUNCH_ET(L, F, G, 0);               \
+        if (a.peak_rec) RMS_LAUNCH(L, F, G, 2);    \
+        else if (a.peak_part) RMS_LAUNCH(L, F, G, 1); \
+        else RMS_LAUNCH(L, F, G, 0);               \
     } while (0)
-#define RMS_LAUNCH_ET_G(L, F)                            \
+#define RMS_LAUNCH_G(L, F)                            \
     do {                                                 \
-        if (p.any_flagged) RMS_LAUNCH_ET_P(L, F, true);  \
-        else RMS_LAUNCH_ET_P(L, F, false);               \
+        if (p.any_flagged) RMS_LAUNCH_P(L, F, true);  \
+        else RMS_LAUNCH_P(L, F, false);               \
     } while (0)
     if (a.layout == RMSYNTH_LOS_MAJOR) {
-        if (fast) RMS_LAUNCH_ET_G(RMSYNTH_LOS_MAJOR, true);
-        else RMS_LAUNCH_ET_G(RMSYNTH_LOS_MAJOR, false);
+        if (fast) RMS_LAUNCH_G(RMSYNTH_LOS_MAJOR, true);
+        else RMS_LAUNCH_G(RMSYNTH_LOS_MAJOR, false);
     } else {
-        if (fast) RMS_LAUNCH_ET_G(RMSYNTH_FREQ_MAJOR, true);
-        else RMS_LAUNCH_ET_G(RMSYNTH_FREQ_MAJOR, false);
+        if (fast) RMS_LAUNCH_G(RMSYNTH_FREQ_MAJOR, true);
+        else RMS_LAUNCH_G(RMSYNTH_FREQ_MAJOR, false);
     }
-#undef RMS_LAUNCH_ET_G
-#undef RMS_LAUNCH_ET_P
-#undef RMS_LAUNCH_ET
+#undef RMS_LAUNCH_G
+#undef RMS_LAUNCH_P
+#undef RMS_LAUNCH
     return hipGetLastError();
 }
 
@@ -931,7 +723,7 @@ __global__ void etable_kernel(const double* __restrict__ bj, const double* __res
 
 hipError_t launch_synth_etable(const rmsynth_plan_s& p, const ExecArgs& a, int precision)
 {
-    return precision == RMSYNTH_SPLIT_FP16 ? launch_et<true>(p, a) : launch_et<false>(p, a);
+    return precision == RMSYNTH_SPLIT_FP16 ? launch_t<true>(p, a) : launch_t<false>(p, a);
 }
 
 hipError_t launch_etable(const rmsynth_plan_s& p, hipStream_t stream)
@@ -944,26 +736,11 @@ hipError_t launch_etable(const rmsynth_plan_s& p, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_synth_kfactored(const rmsynth_plan_s& p, const ExecArgs& a, int precision)
-{
-    return precision == RMSYNTH_SPLIT_FP16 ? launch_kf<true>(p, a) : launch_kf<false>(p, a);
-}
-
-hipError_t launch_kfactor_tables(const rmsynth_plan_s& p, hipStream_t stream)
-{
-    const int64_t nT = (int64_t)(kKTile / 4) * p.nphi_pad;
-    const int64_t n = std::max<int64_t>(nT, std::max(p.nphi_pad, p.nchan_pad));
-    hipLaunchKernelGGL(kfactor_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                       p.d_phi, p.d_w, p.nphi_pad, p.nchan_pad, p.kb0, p.kdb, p.kpad, p.K, p.d_kw, p.d_kbase,
-                       p.d_krot, p.d_Kbf[0], p.d_Kbf[1], p.d_Khf[0], p.d_Khf[1]);
-    return hipGetLastError();
-}
-
 hipError_t launch_los_scale(const rmsynth_plan_s& p, const ExecArgs& a)
 {
-    // The factored and explicit-table kernels fold K into the data they
+    // The kernels with tables fold K into the data they
     // split; the per-element split kernel applies it in the epilogue, so its
-    // scale ignores K (K = 1 in the channel-factored adjoint plans).
+    // scale ignores K (K = 1 in the folded adjoint plans).
     const float k = (p.uniform || p.etab) ? (float)p.K : 1.0f;
     if (a.layout == RMSYNTH_LOS_MAJOR)
         hipLaunchKernelGGL(los_scale_kernel<RMSYNTH_LOS_MAJOR>, dim3((unsigned)((a.nlos + 3) / 4)),
@@ -976,7 +753,7 @@ hipError_t launch_los_scale(const rmsynth_plan_s& p, const ExecArgs& a)
     return hipGetLastError();
 }
 
-int factored_peak_parts(const rmsynth_plan_s& p)
+int peak_parts(const rmsynth_plan_s& p)
 {
     return p.uniform ? (p.nphi + 63) / 64 : 2 * ((p.nphi + NT - 1) / NT);
 }
@@ -990,7 +767,7 @@ hipError_t launch_peak_merge(const rmsynth_plan_s& p, const PeakPart* part, int6
     for (int64_t l0 = 0; l0 < nlos;) {
         const int64_t n = nlos - l0 < max_items(256, 256) ? nlos - l0 : max_items(256, 256);
         hipLaunchKernelGGL(peak_merge_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           part + l0, factored_peak_parts(p), n, nlos, p.nphi, p.d_phi, Fq + l0 * p.nphi,
+                           part + l0, peak_parts(p), n, nlos, p.nphi, p.d_phi, Fq + l0 * p.nphi,
                            Fu + l0 * p.nphi, idx + l0, phi_pk ? phi_pk + l0 : nullptr,
                            amp ? amp + l0 : nullptr, q_pk ? q_pk + l0 : nullptr,
                            u_pk ? u_pk + l0 : nullptr);
@@ -1008,7 +785,7 @@ hipError_t launch_peak_merge_rec(const rmsynth_plan_s& p, const PeakRec* rec, in
     for (int64_t l0 = 0; l0 < nlos;) {
         const int64_t n = nlos - l0 < max_items(256, 256) ? nlos - l0 : max_items(256, 256);
         hipLaunchKernelGGL(peak_merge_rec_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           rec + l0, factored_peak_parts(p), n, rec_ld, p.nphi, p.d_phi, idx + l0,
+                           rec + l0, peak_parts(p), n, rec_ld, p.nphi, p.d_phi, idx + l0,
                            phi_pk ? phi_pk + l0 : nullptr, amp ? amp + l0 : nullptr,
                            q_pk ? q_pk + l0 : nullptr, u_pk ? u_pk + l0 : nullptr,
                            phi_fit ? phi_fit + l0 : nullptr, amp_fit ? amp_fit + l0 : nullptr);

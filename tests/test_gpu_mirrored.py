@@ -45,3 +45,29 @@ def test_tile_edges(prec, layout, shape):
     # |F| is the FP32 square root of the FP32 sum of squares of what is stored
     np.testing.assert_allclose(Fa, np.hypot(Fq.astype(np.float64), Fu), rtol=4e-7, atol=0)
     plan.close()
+
+
+@pytest.mark.parametrize("prec", list(rs.PRECISIONS))
+@pytest.mark.parametrize("nlos,nchan,nphi", [(1, 3, 2), (31, 40, 31), (33, 255, 32), (64, 256, 33), (65, 257, 255),
+                                             (63, 64, 256), (66, 100, 257), (40, 130, 513), (9000, 70, 300)])
+def test_folded_adjoint_edges(prec, nlos, nchan, nphi):
+    """The adjoint on a uniform phi grid folds pairs of phi in K-tiles of at most
+    256 (whole multiples of 32, padded below phi_0), 64 LOS x 256 channels per
+    workgroup (32 LOS when there are few): one, two and three K-tiles with
+    every remainder, against the direct FP64 sum.  Errors are taken relative
+    to max(max |P|, sqrt(sum |C|^2)), the bound of a sum of independent
+    products."""
+    note(f"folded adjoint {nlos} x {nchan} x {nphi} {prec}")
+    c = make_small_cube(2, nchan, 3, seed=nphi)
+    phi = np.linspace(-90.0, 95.0, nphi)
+    rng = np.random.default_rng(nlos + nphi)
+    C = np.float32(rng.standard_normal((2, nlos, nphi)))
+    plan = rs.Plan(c["lambda2"], c["weights"], phi)
+    Pq, Pu = plan.adjoint(dev32(C[0]), dev32(C[1]), rs.PRECISIONS[prec])
+    pick = np.unique(np.r_[0:min(nlos, 70), max(0, nlos - 70):nlos])
+    D = C[:, pick].astype(np.float64)
+    rq, ru = oracle.adjoint(D[0], D[1], c["lambda2"], c["weights"], phi)
+    err = np.hypot(host(Pq)[pick] - rq, host(Pu)[pick] - ru).max(1)
+    size = np.maximum(np.hypot(rq, ru).max(1), np.sqrt((D ** 2).sum((0, 2))))
+    assert np.max(err / size) <= SCALE_TOL[prec]
+    plan.close()
