@@ -28,20 +28,54 @@ hipError_t mlp_launch_head_wgrad(const float* g, const _Float16* H2, int h2, int
                                  float* gW3, float* gb3, float* part, hipStream_t s);
 hipError_t mlp_launch_colsum(const float* X, int64_t M, int64_t N, float alpha, float* out,
                              float* part, hipStream_t s);
-hipError_t mlp_launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr,
-                           float beta1, float beta2, float eps, float bc1, float bc2, hipStream_t s);
-hipError_t mlp_launch_weights16(const float* p, int64_t nW1, int64_t nb1, int64_t nW2, int64_t nb2,
-                                int64_t nW3, _Float16* w16, hipStream_t s);
+// The internal parameter block: W1 [h1][nin_pad] | b1 | W2 [h2][h1] | b2 | W3 [2][h2] | b3.
+struct ParamLayout {
+    int nin_pad, h1, h2;
+    int64_t nW1, nW2, nW3;
+    __host__ __device__ int64_t np() const { return nW1 + h1 + nW2 + h2 + nW3 + 2; }
+};
+// Half copies of the parameters p: w16 (W1 | W2 | W3, row-major) and, unless
+// frag is NULL, the MFMA fragments of W1, W2 and W2 transposed (nW1 + 2 nW2
+// halves; fragment (n / 32, k / 16) of a matrix with rows n and contracted
+// axis k is 64 uint4, lane l holding row n & 31 = l & 31, columns 8 (l >> 5)
+// .. + 7 of the 16).
+hipError_t mlp_launch_halves(const ParamLayout& L, const float* p, _Float16* w16, uint4* frag,
+                             hipStream_t s);
+// One Adam step, and the half copies of its result.
+hipError_t mlp_launch_adam(const ParamLayout& L, float* p, const float* g, float* m, float* v, float lr,
+                           float beta1, float beta2, float eps, float bc1, float bc2, _Float16* w16,
+                           uint4* frag, hipStream_t s);
+// Forward and backward of a batch in two launches (mlp_train.hip): gradient of
+// the mean loss into grad, laid out as the parameter block with W1 rows of ld1
+// (nin_pad, or the 2 nchan of the canonical vector), and the mean loss.
+// X, H1, D1, D2 are scratch for whole 32-row blocks of the batch; part holds
+// mlp_rows_part_floats floats, plane plane_floats (split batches).
+struct MlpTrainArgs {
+    ParamLayout L;
+    const float *Q, *U;
+    int64_t batch;
+    int nchan;
+    const float* chan_w;
+    const uint4* frag;
+    const float* p;
+    const _Float16* W3;
+    float phi_scale;
+    const float *phi_label, *det_label;
+    _Float16 *X, *H1, *D1, *D2;
+    float *part, *plane;
+    int64_t plane_floats;
+    float* grad;
+    int64_t ld1;
+    float* loss;
+};
+bool mlp_rows_supported(int h1, int h2, int nin_pad);
+int64_t mlp_rows_part_floats(int h1, int h2);
+hipError_t mlp_launch_rows(const MlpTrainArgs& a, hipStream_t s);
 hipError_t mlp_launch_mean(const float* x, int64_t n, float* out, hipStream_t s);
 // Fused inference (hidden widths 256 and 256 only): phi_hat and score per LOS.
-// It reads W1 and W2 from a copy in MFMA-fragment order of
-// mlp_fused_frag_uint4(nin_pad) uint4, made from the half weights by
-// mlp_launch_frag16 (W1 [256][nin_pad], W2 [256][256]).  unit_w: every channel
-// weight is 1 (the weights are then not read).
+// It reads W1 and W2 from their fragments (mlp_launch_halves).  unit_w: every
+// channel weight is 1 (the weights are then not read).
 bool mlp_fused_supported(int h1, int h2, int nin_pad);
-int64_t mlp_fused_frag_uint4(int nin_pad);
-hipError_t mlp_launch_frag16(const _Float16* W1, const _Float16* W2, int nin_pad, uint4* frag,
-                             hipStream_t s);
 hipError_t mlp_launch_infer_fused(const float* Q, const float* U, int64_t nlos, int nchan,
                                   const float* w, int nin_pad, const uint4* frag, const float* b1,
                                   const float* b2, const _Float16* W3, const float* b3,

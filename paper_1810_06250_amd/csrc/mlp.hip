@@ -12,23 +12,13 @@
 // gradient of the batch SUM so that half-precision dz stays in the normal
 // range; weight gradients are scaled by 1/batch in FP32.
 #include "mlp.h"
+#include "mlp_device.h"
 
 #include <algorithm>
 
 namespace {
 
 typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
-
-// FP32 to half, the FP32 value rounded first: the empty asm keeps the
-// compiler from fusing the multiply or add that produced x and the
-// conversion into one mixed-precision FMA (a single rounding from the exact
-// result), so every half below is the nearest half to an FP32 number, in the
-// training kernels and in fused inference alike.
-__device__ __forceinline__ _Float16 half_of(float x)
-{
-    asm volatile("" : "+v"(x));
-    return (_Float16)x;
-}
 
 // ----------------------------------------------------------------- input
 // One wave per row.  Rows b < nvalid: x = [w Q | w U] / rms (half), columns
@@ -302,31 +292,6 @@ __global__ void reduce_split_kernel(const float* __restrict__ part, int nsplit, 
     C[(int64_t)blockIdx.y * ldc + n] = alpha * s;
 }
 
-// Adam (Kingma & Ba, bias-corrected) on the FP32 master parameters.
-__global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g,
-                            float* __restrict__ m, float* __restrict__ v, int64_t n, float lr,
-                            float beta1, float beta2, float eps, float bc1, float bc2)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = beta1 * m[i] + (1.0f - beta1) * gi;
-    const float vi = beta2 * v[i] + (1.0f - beta2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
-}
-
-// Half copies of W1, W2, W3 (the parameter block with its biases removed).
-__global__ void weights16_kernel(const float* __restrict__ p, int64_t nW1, int64_t nb1,
-                                 int64_t nW2, int64_t nb2, int64_t nW3, _Float16* __restrict__ w16)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nW1) w16[i] = (_Float16)p[i];
-    else if (i < nW1 + nW2) w16[i] = (_Float16)p[i + nb1];
-    else if (i < nW1 + nW2 + nW3) w16[i] = (_Float16)p[i + nb1 + nb2];
-}
-
 // Mean of n values in one workgroup, fixed summation order.
 __global__ __launch_bounds__(256) void mean_kernel(const float* __restrict__ x, int64_t n,
                                                    float* __restrict__ out)
@@ -351,7 +316,7 @@ __global__ __launch_bounds__(256) void mean_kernel(const float* __restrict__ x, 
 // (mostly from L2/MALL) two chunks ahead of their use, normalises and rounds
 // them to half on their way into LDS, and feeds layer 1; layer 2 reads the
 // half h1 tile from LDS; the head reduces over lanes and waves.  Weights come
-// in MFMA-fragment order (frag16_kernel), so each fragment is one contiguous
+// in MFMA-fragment order, so each fragment is one contiguous
 // 1 KB read per wave, two K-chunks ahead of its use.  No activation leaves
 // the CU.  Three workgroups share a CU (46 KB of LDS, at most 168 VGPRs
 // each), so that loads of one overlap the matrix work of the others.
@@ -361,22 +326,6 @@ __global__ __launch_bounds__(256) void mean_kernel(const float* __restrict__ x, 
 constexpr int FR = 64;                 // LOS per workgroup
 constexpr int FH = 256;                // hidden width
 constexpr int FHS = FH + 8;            // LDS row stride of h1 (halves)
-
-// Fragment order of an N x K half matrix W (row n at W + n ldw): fragment
-// (b, s) covers rows 32 b .. + 31 and columns 16 s .. + 15 and is 64 uint4,
-// lane l holding row 32 b + (l & 31), columns 16 s + 8 (l >> 5) .. + 7 (the
-// B operand of v_mfma_f32_32x32x16_f16), at out[(b K/16 + s) 64 + l].
-__global__ void frag16_kernel(const _Float16* __restrict__ W, int64_t N, int64_t K, int64_t ldw,
-                              uint4* __restrict__ out)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t ks = K / 16;
-    if (i >= (N / 32) * ks * 64) return;
-    const int l = (int)(i & 63);
-    const int64_t f = i >> 6, b = f / ks, sl = f - b * ks;
-    const int64_t n = 32 * b + (l & 31), k = 16 * sl + 8 * (l >> 5);
-    out[i] = *reinterpret_cast<const uint4*>(W + n * ldw + k);
-}
 
 template <bool VEC, bool UNITW>
 __global__ __launch_bounds__(256, 3) void infer_fused_kernel(
@@ -961,22 +910,6 @@ hipError_t mlp_launch_colsum(const float* X, int64_t M, int64_t N, float alpha, 
     return hipGetLastError();
 }
 
-hipError_t mlp_launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr,
-                           float beta1, float beta2, float eps, float bc1, float bc2, hipStream_t s)
-{
-    hipLaunchKernelGGL(adam_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, p, g, m, v, n, lr,
-                       beta1, beta2, eps, bc1, bc2);
-    return hipGetLastError();
-}
-
-hipError_t mlp_launch_weights16(const float* p, int64_t nW1, int64_t nb1, int64_t nW2, int64_t nb2,
-                                int64_t nW3, _Float16* w16, hipStream_t s)
-{
-    hipLaunchKernelGGL(weights16_kernel, dim3(blocks_for(nW1 + nW2 + nW3, 256)), dim3(256), 0, s, p,
-                       nW1, nb1, nW2, nb2, nW3, w16);
-    return hipGetLastError();
-}
-
 hipError_t mlp_launch_mean(const float* x, int64_t n, float* out, hipStream_t s)
 {
     hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, s, x, n, out);
@@ -984,20 +917,6 @@ hipError_t mlp_launch_mean(const float* x, int64_t n, float* out, hipStream_t s)
 }
 
 bool mlp_fused_supported(int h1, int h2, int nin_pad) { return h1 == FH && h2 == FH && nin_pad % GK == 0; }
-
-int64_t mlp_fused_frag_uint4(int nin_pad) { return (int64_t)FH * nin_pad / 8 + (int64_t)FH * FH / 8; }
-
-hipError_t mlp_launch_frag16(const _Float16* W1, const _Float16* W2, int nin_pad, uint4* frag,
-                             hipStream_t s)
-{
-    const int64_t n1 = (int64_t)FH * nin_pad / 8, n2 = (int64_t)FH * FH / 8;
-    hipLaunchKernelGGL(frag16_kernel, dim3(blocks_for(n1, 256)), dim3(256), 0, s, W1, (int64_t)FH,
-                       (int64_t)nin_pad, (int64_t)nin_pad, frag);
-    if (hipError_t e = hipGetLastError()) return e;
-    hipLaunchKernelGGL(frag16_kernel, dim3(blocks_for(n2, 256)), dim3(256), 0, s, W2, (int64_t)FH,
-                       (int64_t)FH, (int64_t)FH, frag + n1);
-    return hipGetLastError();
-}
 
 hipError_t mlp_launch_infer_fused(const float* Q, const float* U, int64_t nlos, int nchan,
                                   const float* w, int nin_pad, const uint4* frag, const float* b1,

@@ -29,8 +29,8 @@ struct rmsynth_mlp_s {
     float* d_m = nullptr;
     float* d_v = nullptr;
     _Float16* d_w16 = nullptr;   // W1 | W2 | W3 as half
-    uint4* d_wfrag = nullptr;    // W1 | W2 as half in MFMA-fragment order (fused inference)
-    bool frag_stale = true;      // d_wfrag not yet rebuilt from the current half weights
+    uint4* d_wfrag = nullptr;    // W1 | W2 | W2 transposed as half in MFMA-fragment order
+                                 // (networks whose kernels read it, else NULL)
     float* d_part = nullptr;     // partial sums of the column reductions
     float* d_wpart = nullptr;    // split-K partial sums of the weight gradients
     int64_t wpart_floats = 0;
@@ -44,6 +44,7 @@ struct rmsynth_mlp_s {
     int64_t off_b2() const { return nW1 + h1 + nW2; }
     int64_t off_W3() const { return nW1 + h1 + nW2 + h2; }
     int64_t off_b3() const { return nW1 + h1 + nW2 + h2 + nW3; }
+    ParamLayout layout() const { return ParamLayout{nin_pad, h1, h2, nW1, nW2, nW3}; }
     int64_t canonical_size() const { return (int64_t)h1 * nin + h1 + nW2 + h2 + nW3 + 2; }
 };
 
@@ -114,14 +115,16 @@ int ensure_rows(rmsynth_mlp_s* m, int64_t rows, bool train)
     }
     if (bwd) {
         m->cap_bwd = 0;
-        if ((e = alloc(m->Z1, rows * m->h1)) != hipSuccess ||
-            (e = alloc(m->Z2, rows * m->h2)) != hipSuccess ||
-            (e = alloc(m->D2, rows * m->h2)) != hipSuccess ||
+        // FP32 intermediates leave the chip on the separate kernels only.
+        const int64_t wide = mlp_rows_supported(m->h1, m->h2, m->nin_pad) ? 0 : rows;
+        if ((e = alloc(m->Z1, wide * m->h1)) != hipSuccess ||
+            (e = alloc(m->Z2, wide * m->h2)) != hipSuccess ||
+            (e = alloc(m->D2, wide * m->h2)) != hipSuccess ||
             (e = alloc(m->D2h, rows * m->h2)) != hipSuccess ||
-            (e = alloc(m->D1, rows * m->h1)) != hipSuccess ||
+            (e = alloc(m->D1, wide * m->h1)) != hipSuccess ||
             (e = alloc(m->D1h, rows * m->h1)) != hipSuccess ||
-            (e = alloc(m->lossb, rows)) != hipSuccess ||
-            (e = alloc(m->gout, 2 * rows)) != hipSuccess)
+            (e = alloc(m->lossb, wide)) != hipSuccess ||
+            (e = alloc(m->gout, 2 * wide)) != hipSuccess)
             return rms_fail(RMSYNTH_ENOMEM, "network gradients (%lld rows): %s", (long long)rows,
                             hipGetErrorString(e));
         m->cap_bwd = rows;
@@ -149,12 +152,40 @@ hipError_t forward(rmsynth_mlp_s* m, const float* Q, const float* U, int64_t nva
                            m->H2, m->h2, s);
 }
 
-// Gradient of the mean loss into m->d_g (internal layout); loss (device) optional.
+// Gradient of the mean loss; loss (device) optional.  With grad NULL it goes to
+// m->d_g (internal layout), else to grad (canonical layout).
 int gradient(rmsynth_mlp_s* m, const float* Q, const float* U, int64_t B, const float* phi,
-             const float* det, float* loss, hipStream_t s, const char* who)
+             const float* det, float* grad, float* loss, hipStream_t s, const char* who)
 {
     const int64_t rows = round_up(B, 64);
     if (int rc = ensure_rows(m, rows, true)) return rc;
+    if (mlp_rows_supported(m->h1, m->h2, m->nin_pad)) {
+        MlpTrainArgs a{};
+        a.L = m->layout();
+        a.Q = Q;
+        a.U = U;
+        a.batch = B;
+        a.nchan = m->nchan;
+        a.chan_w = m->d_chw;
+        a.frag = m->d_wfrag;
+        a.p = m->d_p;
+        a.W3 = W3h(m);
+        a.phi_scale = m->phi_scale;
+        a.phi_label = phi;
+        a.det_label = det;
+        a.X = m->X;
+        a.H1 = m->H1;
+        a.D1 = m->D1h;
+        a.D2 = m->D2h;
+        a.part = m->d_part;
+        a.plane = m->d_wpart;
+        a.plane_floats = m->wpart_floats;
+        a.grad = grad ? grad : m->d_g;
+        a.ld1 = grad ? m->nin : m->nin_pad;
+        a.loss = loss;
+        hipError_t e = mlp_launch_rows(a, s);
+        return e == hipSuccess ? RMSYNTH_OK : rms_hip_fail(e, who);
+    }
     const float inv_b = 1.0f / (float)B;
     hipError_t e = forward(m, Q, U, B, rows, true, s);
     if (e == hipSuccess)
@@ -178,17 +209,23 @@ int gradient(rmsynth_mlp_s* m, const float* Q, const float* U, int64_t B, const 
                                   m->d_g, m->nin_pad, m->d_wpart, m->wpart_floats, s);
     if (e == hipSuccess) e = mlp_launch_colsum(m->D1, B, m->h1, inv_b, m->d_g + m->off_b1(), m->d_part, s);
     if (e == hipSuccess && loss) e = mlp_launch_mean(m->lossb, B, loss, s);
+    // Canonical layout: W1 rows without their padding, then the rest as is.
+    if (e == hipSuccess && grad) {
+        e = hipMemcpy2DAsync(grad, sizeof(float) * m->nin, m->d_g, sizeof(float) * m->nin_pad,
+                             sizeof(float) * m->nin, m->h1, hipMemcpyDeviceToDevice, s);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(grad + (int64_t)m->h1 * m->nin, m->d_g + m->nW1,
+                               sizeof(float) * (m->np - m->nW1), hipMemcpyDeviceToDevice, s);
+    }
     if (e != hipSuccess) return rms_hip_fail(e, who);
     return RMSYNTH_OK;
 }
 
-// Half copies of the weights after every parameter change; the fragment-order
-// copy for fused inference is rebuilt lazily, by the next inference call on
-// its own stream (training steps do not need it).
+// Half copies of the weights after a parameter change (a training step writes
+// them itself).
 hipError_t refresh_half(rmsynth_mlp_s* m, hipStream_t s)
 {
-    m->frag_stale = true;
-    return mlp_launch_weights16(m->d_p, m->nW1, m->h1, m->nW2, m->h2, m->nW3, m->d_w16, s);
+    return mlp_launch_halves(m->layout(), m->d_p, m->d_w16, m->d_wfrag, s);
 }
 
 // Internal <-> canonical layout of a parameter-shaped vector (host).
@@ -285,10 +322,12 @@ int create(int32_t nchan, int32_t h1, int32_t h2, const float* weights, float ph
         (e = hipMalloc(&m->d_p, pb)) != hipSuccess || (e = hipMalloc(&m->d_g, pb)) != hipSuccess ||
         (e = hipMalloc(&m->d_m, pb)) != hipSuccess || (e = hipMalloc(&m->d_v, pb)) != hipSuccess ||
         (e = hipMalloc(&m->d_w16, sizeof(_Float16) * (m->nW1 + m->nW2 + m->nW3))) != hipSuccess ||
-        (mlp_fused_supported(h1, h2, m->nin_pad) &&
-         (e = hipMalloc(&m->d_wfrag, sizeof(uint4) * mlp_fused_frag_uint4(m->nin_pad))) != hipSuccess) ||
-        (e = hipMalloc(&m->d_part, sizeof(float) * mlp_reduce_part_floats(
-                                       std::max<int64_t>(std::max(h1, h2), 2 * (int64_t)h2 + 2)))) != hipSuccess ||
+        ((mlp_fused_supported(h1, h2, m->nin_pad) || mlp_rows_supported(h1, h2, m->nin_pad)) &&
+         (e = hipMalloc(&m->d_wfrag, sizeof(_Float16) * (m->nW1 + 2 * m->nW2))) != hipSuccess) ||
+        (e = hipMalloc(&m->d_part, sizeof(float) * (mlp_rows_supported(h1, h2, m->nin_pad)
+                                       ? mlp_rows_part_floats(h1, h2)
+                                       : mlp_reduce_part_floats(std::max<int64_t>(
+                                             std::max(h1, h2), 2 * (int64_t)h2 + 2))))) != hipSuccess ||
         (e = hipMalloc(&m->d_wpart, sizeof(float) * (m->wpart_floats = mlp_wgrad_part_floats(
                                         std::max(m->nW1, m->nW2))))) != hipSuccess) {
         free_mlp(m);
@@ -393,15 +432,8 @@ int rmsynth_mlp_grad(rmsynth_mlp_t m, const float* Q, const float* U, int64_t ba
     if (int rc = check_batch(m, Q, U, batch, phi_label, det_label, "rmsynth_mlp_grad")) return rc;
     if (!grad) return rms_fail(RMSYNTH_EINVAL, "rmsynth_mlp_grad: grad is NULL");
     hipStream_t s = (hipStream_t)stream;
-    if (int rc = gradient(m, Q, U, batch, phi_label, det_label, loss, s, "rmsynth_mlp_grad"))
+    if (int rc = gradient(m, Q, U, batch, phi_label, det_label, grad, loss, s, "rmsynth_mlp_grad"))
         return rc;
-    // Canonical layout: W1 rows without their padding, then the rest as is.
-    hipError_t e = hipMemcpy2DAsync(grad, sizeof(float) * m->nin, m->d_g, sizeof(float) * m->nin_pad,
-                                    sizeof(float) * m->nin, m->h1, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(grad + (int64_t)m->h1 * m->nin, m->d_g + m->nW1,
-                           sizeof(float) * (m->np - m->nW1), hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return rms_hip_fail(e, "rmsynth_mlp_grad copy");
     return rms_ok();
 }
 
@@ -414,15 +446,14 @@ int rmsynth_mlp_train_step(rmsynth_mlp_t m, const float* Q, const float* U, int6
     if (!(lr > 0.0f) || !std::isfinite(lr))
         return rms_fail(RMSYNTH_EINVAL, "rmsynth_mlp_train_step: lr=%g", (double)lr);
     hipStream_t s = (hipStream_t)stream;
-    if (int rc = gradient(m, Q, U, batch, phi_label, det_label, loss, s, "rmsynth_mlp_train_step"))
+    if (int rc = gradient(m, Q, U, batch, phi_label, det_label, nullptr, loss, s, "rmsynth_mlp_train_step"))
         return rc;
     const double b1 = 0.9, b2 = 0.999;
     const int64_t t = m->step + 1;
     const float bc1 = (float)(1.0 - std::pow(b1, (double)t));
     const float bc2 = (float)(1.0 - std::pow(b2, (double)t));
-    hipError_t e = mlp_launch_adam(m->d_p, m->d_g, m->d_m, m->d_v, m->np, lr, (float)b1, (float)b2,
-                                   1e-8f, bc1, bc2, s);
-    if (e == hipSuccess) e = refresh_half(m, s);
+    hipError_t e = mlp_launch_adam(m->layout(), m->d_p, m->d_g, m->d_m, m->d_v, lr, (float)b1, (float)b2,
+                                   1e-8f, bc1, bc2, m->d_w16, m->d_wfrag, s);
     if (e != hipSuccess) return rms_hip_fail(e, "rmsynth_mlp_train_step");
     m->step = t;
     return rms_ok();
@@ -439,13 +470,7 @@ int rmsynth_mlp_infer(rmsynth_mlp_t m, const float* Q, const float* U, int64_t n
     hipStream_t s = (hipStream_t)stream;
     if (mlp_fused_supported(m->h1, m->h2, m->nin_pad)) {
         // One pass over the cube, no activation buffers.
-        hipError_t e = hipSuccess;
-        if (m->frag_stale) {
-            e = mlp_launch_frag16(W1h(m), W2h(m), m->nin_pad, m->d_wfrag, s);
-            if (e != hipSuccess) return rms_hip_fail(e, "rmsynth_mlp_infer");
-            m->frag_stale = false;
-        }
-        e = mlp_launch_infer_fused(Q, U, nlos, m->nchan, m->d_chw, m->nin_pad,
+        hipError_t e = mlp_launch_infer_fused(Q, U, nlos, m->nchan, m->d_chw, m->nin_pad,
                                               m->d_wfrag, m->d_p + m->off_b1(),
                                               m->d_p + m->off_b2(), W3h(m), m->d_p + m->off_b3(),
                                               m->phi_scale, phi_hat, score,
