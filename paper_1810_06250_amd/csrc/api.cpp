@@ -46,8 +46,7 @@ void free_plan(rmsynth_plan_s* p)
     free_plan(p->adj);
     void* bufs[] = {p->d_b, p->d_lambda2, p->d_w, p->d_phi, p->d_base, p->d_Tbf, p->d_Thf, p->d_Tf32,
                     p->d_nufft_rot, p->d_nufft_blk, p->d_nufft_ent,
-                    p->d_nufft_tw, p->d_nufft_deconv, p->d_kbase, p->d_krot, p->d_ew,
-                    p->d_Ebf[0], p->d_Ebf[1], p->d_Ehf[0], p->d_Ehf[1]};
+                    p->d_nufft_tw, p->d_nufft_deconv, p->d_kbase, p->d_krot};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     delete p;
@@ -90,29 +89,29 @@ int build_mirror_tables(rmsynth_plan_s* p)
     return RMSYNTH_OK;
 }
 
-// The explicit split phase table of a plan whose axes are not uniform (the
+// The phase table of a plan whose axes are not uniform (the
 // mirrored and folded tables do not apply), when it fits kEtabMaxBytes; larger plans keep
 // the per-element phase generator.
 int build_etable(rmsynth_plan_s* p)
 {
-    const size_t nE = (size_t)(p->nchan_pad / 4) * p->nphi_pad;
-    if (nE * sizeof(uint4) * 4 > kEtabMaxBytes) return RMSYNTH_OK;
+    const size_t nE = (size_t)(p->nchan_pad / 2) * p->nphi_pad;  // uint4 of each form
+    if (nE * sizeof(uint4) * 2 > kEtabMaxBytes) return RMSYNTH_OK;
     hipError_t e;
-    if ((e = hipMalloc(&p->d_ew, sizeof(float2) * p->nchan_pad)) != hipSuccess ||
-        (e = hipMalloc(&p->d_Ebf[0], sizeof(uint4) * nE)) != hipSuccess ||
-        (e = hipMalloc(&p->d_Ebf[1], sizeof(uint4) * nE)) != hipSuccess ||
-        (e = hipMalloc(&p->d_Ehf[0], sizeof(uint4) * nE)) != hipSuccess ||
-        (e = hipMalloc(&p->d_Ehf[1], sizeof(uint4) * nE)) != hipSuccess)
+    if ((e = hipMalloc(&p->d_base, sizeof(float2) * p->nchan_pad)) != hipSuccess ||
+        (e = hipMalloc(&p->d_Tbf, sizeof(uint4) * nE)) != hipSuccess ||
+        (e = hipMalloc(&p->d_Thf, sizeof(uint4) * nE)) != hipSuccess ||
+        (e = hipMalloc(&p->d_Tf32, sizeof(uint4) * nE)) != hipSuccess)
         return rms_fail(RMSYNTH_ENOMEM, "rmsynth_plan: hipMalloc (phase table): %s", hipGetErrorString(e));
     hipStream_t s = nullptr;
     if ((e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking)) != hipSuccess)
         return rms_hip_fail(e, "rmsynth_plan: hipStreamCreate");
-    e = launch_etable(*p, s);
+    e = launch_phase_table(*p, s);
     hipError_t e2 = hipStreamSynchronize(s);
     (void)hipStreamDestroy(s);
     if (e != hipSuccess) return rms_hip_fail(e, "rmsynth_plan: phase-table kernel");
     if (e2 != hipSuccess) return rms_hip_fail(e2, "rmsynth_plan: phase-table kernel");
     p->etab = true;
+    p->ftiles = (int32_t)((p->nphi + kMirrorTile - 1) / kMirrorTile);
     return RMSYNTH_OK;
 }
 
@@ -455,9 +454,8 @@ int run_execute(const rmsynth_plan_s* p, const float* Q, const float* U, int64_t
             if (e != hipSuccess) return rms_hip_fail(e, who);
         }
         hipError_t e;
-        if (p->uniform || p->cuniform) e = launch_synth_mirrored(*p, a, precision);
+        if (p->uniform || p->cuniform || p->etab) e = launch_synth_mirrored(*p, a, precision);
         else if (precision == RMSYNTH_FP32) e = launch_synth_fp32(*p, a);
-        else if (p->etab) e = launch_synth_etable(*p, a, precision);
         else e = launch_synth_split(*p, a, precision);
         if (e != hipSuccess) return rms_hip_fail(e, who);
         b0 += m;

@@ -60,15 +60,11 @@ struct rmsynth_plan_s {
     int32_t kpad, ksteps;
     float2* d_kbase;
     float2* d_krot;
-    // Explicit split phase table (synth_table.hip), present when
-    // neither axis is uniform and the table fits kEtabMaxBytes:
-    //   d_ew [nchan_pad] float2  (K w_j, 0)
-    //   d_E{bf,hf}[hi/lo] [nchan_pad/4][nphi_pad] uint4: 4 channels x (cos, sin)
-    //                   of 2 pi b_j phi_k, split into hi/lo
+    // Phase table (synth_mirrored.hip, TAB), present when neither axis is
+    // uniform and its split forms fit kEtabMaxBytes: d_base [nchan_pad] holds
+    // (K w_j, 0), d_T{bf,hf,f32} [nchan_pad/8][nphi_pad/64][4][64] uint4 the
+    // cos and sin of 2 pi b_j phi_k (phase_table_kernel).
     bool etab;
-    float2* d_ew;
-    uint4* d_Ebf[2];
-    uint4* d_Ehf[2];
     // The adjoint transform's plan (axes exchanged, see build_adjoint_plan);
     // owned, NULL inside an adjoint plan itself.
     rmsynth_plan_s* adj;
@@ -92,11 +88,10 @@ size_t nufft_lds_bytes(const rmsynth_plan_s& p);
 hipError_t launch_nufft(const rmsynth_plan_s& p, const float* Q, const float* U, int64_t nlos,
                         float* Fq, float* Fu, float* Fabs, hipStream_t s);
 
-constexpr int kTableTile = 128;   // phi per tile of the phase-table kernel
 constexpr int kMirrorTile = 256;  // phi per tile of the mirrored-pair kernels
 constexpr int kMirrorChan = 16;   // channels per K-step of the mirrored-pair kernels
 constexpr int kFoldTile = 256;    // most channels per K-tile of the folded form
-constexpr size_t kEtabMaxBytes = size_t(256) << 20;  // largest explicit phase table (4 arrays)
+constexpr size_t kEtabMaxBytes = size_t(256) << 20;  // largest phase table, both split forms
 
 constexpr int kChanPad = 32;    // channel padding granule (largest K-step)
 constexpr int kPhiPad = 256;    // phi padding granule (largest phi tile)
@@ -254,8 +249,7 @@ hipError_t launch_synth_mirrored(const rmsynth_plan_s& p, const ExecArgs& a, int
 hipError_t launch_los_scale(const rmsynth_plan_s& p, const ExecArgs& a);
 hipError_t launch_mirror_tables(const rmsynth_plan_s& p, hipStream_t s);
 hipError_t launch_fold_tables(const rmsynth_plan_s& p, hipStream_t s);
-hipError_t launch_etable(const rmsynth_plan_s& p, hipStream_t s);
-hipError_t launch_synth_etable(const rmsynth_plan_s& p, const ExecArgs& a, int precision);
+hipError_t launch_phase_table(const rmsynth_plan_s& p, hipStream_t s);
 hipError_t launch_peaks(const rmsynth_plan_s& p, const float* Fq, const float* Fu, int64_t nlos,
                         int32_t* idx, float* phi_pk, float* amp, float* q_pk, float* u_pk,
                         hipStream_t s);

@@ -149,6 +149,103 @@ __global__ void peak_fit_kernel(const float* __restrict__ Fq, const float* __res
     if (amp_fit) amp_fit[l] = af;
 }
 
+// Merge the peaks per 64 phi of each LOS (in phi order, ties to the
+// earlier one, i.e. the lower phi index), then read Fq, Fu at the peak: the
+// same results as peaks_kernel on the stored outputs.
+__global__ void peak_merge_kernel(const PeakPart* __restrict__ part, int nparts, int64_t nlos,
+                                  int64_t part_ld, int nphi, const double* __restrict__ phik,
+                                  const float* __restrict__ Fq, const float* __restrict__ Fu,
+                                  int32_t* __restrict__ idx, float* __restrict__ phi_pk,
+                                  float* __restrict__ amp, float* __restrict__ q_pk,
+                                  float* __restrict__ u_pk)
+{
+    const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (l >= nlos) return;
+    float best = -1.0f;
+    int bi = -1;
+    bool bad = false;
+    for (int t = 0; t < nparts; ++t) {
+        const PeakPart p = part[t * part_ld + l];
+        bad |= p.idx == -2;
+        if (p.m > best) {
+            best = p.m;
+            bi = p.idx;
+        }
+    }
+    if (bad || bi < 0 || bi >= nphi) {
+        idx[l] = -1;
+        const float nan = __builtin_nanf("");
+        if (phi_pk) phi_pk[l] = nan;
+        if (amp) amp[l] = nan;
+        if (q_pk) q_pk[l] = nan;
+        if (u_pk) u_pk[l] = nan;
+    } else {
+        idx[l] = bi;
+        if (phi_pk) phi_pk[l] = (float)phik[bi];
+        if (amp) amp[l] = sqrtf(best);
+        if (q_pk) q_pk[l] = Fq[l * nphi + bi];
+        if (u_pk) u_pk[l] = Fu[l * nphi + bi];
+    }
+}
+
+// Merge of full records (the transform stored no F): the peak as in
+// peak_merge_kernel, Fq and Fu at the peak from its record, and the sub-grid
+// fit through |F| at idx - 1, idx, idx + 1, a neighbour across a 64-phi
+// boundary being the adjacent record's first or last value.
+__global__ void peak_merge_rec_kernel(const PeakRec* __restrict__ rec, int nparts, int64_t nlos,
+                                      int64_t rec_ld, int nphi, const double* __restrict__ phik,
+                                      int32_t* __restrict__ idx, float* __restrict__ phi_pk,
+                                      float* __restrict__ amp, float* __restrict__ q_pk,
+                                      float* __restrict__ u_pk, float* __restrict__ phi_fit,
+                                      float* __restrict__ amp_fit)
+{
+    const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (l >= nlos) return;
+    float best = -1.0f;
+    int bi = -1, bt = -1;
+    bool bad = false;
+    for (int t = 0; t < nparts; ++t) {
+        const PeakRec& r = rec[t * rec_ld + l];
+        const float m = r.m;
+        bad |= r.idx == -2;
+        if (m > best) {
+            best = m;
+            bi = r.idx;
+            bt = t;
+        }
+    }
+    const float nan = __builtin_nanf("");
+    if (bad || bi < 0 || bi >= nphi) {
+        idx[l] = -1;
+        if (phi_pk) phi_pk[l] = nan;
+        if (amp) amp[l] = nan;
+        if (q_pk) q_pk[l] = nan;
+        if (u_pk) u_pk[l] = nan;
+        if (phi_fit) phi_fit[l] = nan;
+        if (amp_fit) amp_fit[l] = nan;
+        return;
+    }
+    const PeakRec r = rec[bt * rec_ld + l];
+    idx[l] = bi;
+    if (phi_pk) phi_pk[l] = (float)phik[bi];
+    if (amp) amp[l] = sqrtf(best);
+    if (q_pk) q_pk[l] = r.q;
+    if (u_pk) u_pk[l] = r.u;
+    if (phi_fit || amp_fit) {
+        float mp = r.prv, mn = r.nxt;
+        if (mp < 0.0f && bt > 0) mp = rec[(bt - 1) * rec_ld + l].last;
+        if (mn < 0.0f && bt + 1 < nparts) mn = rec[(bt + 1) * rec_ld + l].first;
+        const double y0 = mp >= 0.0f ? __builtin_sqrt((double)mp) : __builtin_nan("");
+        const double y2 = mn >= 0.0f ? __builtin_sqrt((double)mn) : __builtin_nan("");
+        const double x0 = bi > 0 ? phik[bi - 1] : __builtin_nan("");
+        const double x2 = bi + 1 < nphi ? phik[bi + 1] : __builtin_nan("");
+        float pf, af;
+        parabola_vertex(x0, y0, phik[bi], __builtin_sqrt((double)best), x2, y2, &pf, &af);
+        if (phi_fit) phi_fit[l] = pf;
+        if (amp_fit) amp_fit[l] = af;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_peak_fit(const rmsynth_plan_s& p, const float* Fq, const float* Fu,
@@ -205,4 +302,43 @@ hipError_t launch_rmsf(const rmsynth_plan_s& p, float* re, float* im, hipStream_
     hipLaunchKernelGGL(rmsf_kernel, dim3(blocks), dim3(256), 0, s, p.d_b, p.d_w, p.nchan, p.d_phi,
                        p.nphi, (float)p.K, re, im);
     return hipGetLastError();
+}
+
+int peak_parts(const rmsynth_plan_s& p) { return (p.nphi + 63) / 64; }
+
+hipError_t launch_peak_merge(const rmsynth_plan_s& p, const PeakPart* part, int64_t nlos,
+                             const float* Fq, const float* Fu, int32_t* idx, float* phi_pk,
+                             float* amp, float* q_pk, float* u_pk, hipStream_t s)
+{
+    // Records are laid out [part][nlos]: a batch of LOS reads them with the
+    // full nlos as stride, through the part_ld argument.
+    for (int64_t l0 = 0; l0 < nlos;) {
+        const int64_t n = nlos - l0 < max_items(256, 256) ? nlos - l0 : max_items(256, 256);
+        hipLaunchKernelGGL(peak_merge_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                           part + l0, peak_parts(p), n, nlos, p.nphi, p.d_phi, Fq + l0 * p.nphi,
+                           Fu + l0 * p.nphi, idx + l0, phi_pk ? phi_pk + l0 : nullptr,
+                           amp ? amp + l0 : nullptr, q_pk ? q_pk + l0 : nullptr,
+                           u_pk ? u_pk + l0 : nullptr);
+        if (hipError_t e = hipGetLastError()) return e;
+        l0 += n;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_peak_merge_rec(const rmsynth_plan_s& p, const PeakRec* rec, int64_t rec_ld,
+                                 int64_t nlos, int32_t* idx, float* phi_pk, float* amp,
+                                 float* q_pk, float* u_pk, float* phi_fit, float* amp_fit,
+                                 hipStream_t s)
+{
+    for (int64_t l0 = 0; l0 < nlos;) {
+        const int64_t n = nlos - l0 < max_items(256, 256) ? nlos - l0 : max_items(256, 256);
+        hipLaunchKernelGGL(peak_merge_rec_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                           rec + l0, peak_parts(p), n, rec_ld, p.nphi, p.d_phi, idx + l0,
+                           phi_pk ? phi_pk + l0 : nullptr, amp ? amp + l0 : nullptr,
+                           q_pk ? q_pk + l0 : nullptr, u_pk ? u_pk + l0 : nullptr,
+                           phi_fit ? phi_fit + l0 : nullptr, amp_fit ? amp_fit + l0 : nullptr);
+        if (hipError_t e = hipGetLastError()) return e;
+        l0 += n;
+    }
+    return hipSuccess;
 }

@@ -24,6 +24,10 @@
 // exp(-2 pi i L db g) before each (Horner's rule), K exp(-2 pi i b_0' g) of the
 // lowest tile's centre b_0' in the epilogue.
 //
+// The table form (TAB) serves grids where neither axis is uniform: the plan
+// holds cos and sin of the whole phase matrix (capped in size), the data are
+// only weighted, and F = sum_j (x + iy)(c - is) takes the full four products.
+//
 // The sums run on the matrix cores with FP32 accumulation, in one of
 //   FP32   v_mfma_f32_32x32x2_f32 on FP32 operands,
 //   split  v_mfma_f32_32x32x16_{bf16,f16} on x = hi + lo in 16 bits each,
@@ -47,6 +51,10 @@
 // centring a ragged last tile on what is left of the grid, so that waves with
 // no pairs skip the matrix work, gained nothing (the workgroup still waits for
 // its full waves).
+// Folded, 262144 LOS x 2001 phi -> 400 channels (padded to 512), bf16x3: 3.15 ms
+// (6.02 with 96-phi K-tiles and no folding); table form, 131072 x 400 x 2001:
+// 2.16 ms (2.32 with 128 x 128 tiles fed through LDS), 65536 in FP32 3.13 ms
+// (3.81 with the phases generated per element).
 #include <float.h>
 
 #include <type_traits>
@@ -60,7 +68,7 @@ constexpr int NH = kMirrorTile / 2;  // pairs per tile
 constexpr int64_t kSmallTiles = 128;  // see launch_mg
 constexpr int SR = kMirrorTile + 4;  // row stride (floats) of the epilogue's tile: conflict-free b128 rows
 
-enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2, FOLD = 3 };
+enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2, FOLD = 3, TAB_ROW = 4, TAB_PLANE = 5 };
 
 typedef const __attribute__((address_space(4))) f32x4_t* const_f4_ptr;
 typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
@@ -89,6 +97,8 @@ __device__ __forceinline__ f32x16_t mfma16(uint4 a, uint4 b, f32x16_t c)
 // table, nk the K-steps of all K-tiles, ksteps those of one, pad the zero
 // channels below channel 0, kbase and krot the K exp(-2 pi i b_0' g) and
 // exp(-2 pi i L db g) per output as (cos, sin).
+// TAB_ROW, TAB_PLANE: the table form, LOS-major (any alignment) and
+// frequency-major: K-steps of 8 channels, base holds (K w_j, 0).
 // FLAGS: some channel has weight 0; its (zero) rotation then also clears
 // whatever the data hold there, NaN included.
 // MG: LOS groups (of 32) per tile; the results do not depend on it.
@@ -107,6 +117,12 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
 {
     static_assert(LOAD != FOLD || (PEAKS == 0 && !FLAGS), "the folded form has no peaks and no flags");
     constexpr bool F32 = PREC == RMSYNTH_FP32;
+    constexpr bool TAB = LOAD == TAB_ROW || LOAD == TAB_PLANE;
+    // Columns of T are outputs (else mirrored pairs of them); K-steps then
+    // contract 8 pairs or channels, as (cos, sin) neighbours.
+    constexpr bool COLS = LOAD == FOLD || TAB;
+    constexpr bool OCT = LOAD == FOLD || LOAD == TAB_ROW;  // eight lanes share a row
+    constexpr bool PLANE = LOAD == LOAD_PLANE || LOAD == TAB_PLANE;
     constexpr int MT = 32 * MG;      // LOS per tile
     constexpr int STEP = 4 * MT * 2;  // uint4 of a packed K-step: [2 channel octets or quad pairs][4][MT]
     union Lds {
@@ -138,16 +154,16 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     const int64_t left = nlos - 1 - l0;
     const int lr = row < left ? row : (int)left;
     const float lsc = PREC == RMSYNTH_SPLIT_FP16 ? los_scale[l0 + lr] : 1.0f;
-    const uint32_t voff = 4u * (LOAD == LOAD_PLANE ? (uint32_t)lr : (uint32_t)(lr * (int)ld));  // < 2^24
-    const float* const Qt = LOAD == LOAD_PLANE ? Q + l0 : Q + l0 * ld;
-    const float* const Ut = LOAD == LOAD_PLANE ? U + l0 : U + l0 * ld;
-    const_f4_ptr bt = (const_f4_ptr)(base + (int64_t)tn * nchan_pad);
-    // FOLD: eight lanes share a LOS row, lane cc the pair cc of the K-step, rows
-    // rq + 32 i: a wave's load covers 8 rows x 32 contiguous bytes.
+    const uint32_t voff = 4u * (PLANE ? (uint32_t)lr : (uint32_t)(lr * (int)ld));  // < 2^24
+    const float* const Qt = PLANE ? Q + l0 : Q + l0 * ld;
+    const float* const Ut = PLANE ? U + l0 : U + l0 * ld;
+    const_f4_ptr bt = (const_f4_ptr)(TAB ? base : base + (int64_t)tn * nchan_pad);
+    // OCT: eight lanes share a LOS row, lane cc the pair or channel cc of the
+    // K-step, rows rq + 32 i: a wave's load covers 8 rows x 32 contiguous bytes.
     const int cc = t & 7, rq = t >> 3;
     uint32_t frow[MG];
     float fsc[MG];
-    if constexpr (LOAD == FOLD) {
+    if constexpr (OCT) {
 #pragma unroll
         for (int i = 0; i < MG; ++i) {
             const int r = rq + 32 * i < left ? rq + 32 * i : (int)left;
@@ -156,8 +172,8 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         }
     }
     // Table columns of this wave: [K-step][64-output block][4][64 lanes].
-    const uint4* const Tw = T + (LOAD == FOLD ? 4 * tn + wave : wave) * 256 + lane;
-    const int tstep = LOAD == FOLD ? 1024 * tiles_n : 1024;
+    const uint4* const Tw = T + (COLS ? 4 * tn + wave : wave) * 256 + lane;
+    const int tstep = COLS ? 1024 * tiles_n : 1024;
 
     struct Data {
         float q[4], u[4];
@@ -210,6 +226,26 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
             }
             return;
         }
+        if constexpr (LOAD == TAB_ROW) {
+            // q, u [i]: rows i; q[2]: the channel's weight (0 past the end).
+            const int jw = 8 * k + cc, j = jw < nchan ? jw : nchan - 1;
+            R.q[2] = base[jw].x;
+#pragma unroll
+            for (int i = 0; i < MG; ++i) {
+                R.q[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Qt) + (frow[i] + 4u * (uint32_t)j));
+                R.u[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ut) + (frow[i] + 4u * (uint32_t)j));
+            }
+            return;
+        }
+        if constexpr (LOAD == TAB_PLANE) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int jw = 8 * k + 2 * wave + i, j = jw < nchan ? jw : nchan - 1;
+                R.q[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Qt + (int64_t)j * ld) + voff);
+                R.u[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ut + (int64_t)j * ld) + voff);
+            }
+            return;
+        }
         const int j0 = k * KC + 4 * wave;
         if (LOAD == LOAD_ROW4) {
             const int j = j0 < nchan ? j0 : nchan - 4;
@@ -228,7 +264,11 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         }
     };
     auto load_rot = [&](int k) __attribute__((always_inline)) {
-        if (LOAD == FOLD) return;
+        if (OCT) return;
+        if (LOAD == TAB_PLANE) {
+            rot[0] = bt[4 * k + wave];
+            return;
+        }
         const int at = (k * KC + 4 * wave) >> 1;
         rot[0] = bt[at];
         rot[1] = bt[at + 1];
@@ -261,6 +301,26 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
             py[2 * i + 1] = xm - xp;
             return;
         }
+        if constexpr (TAB) {
+            // TAB_ROW: row i < MG; TAB_PLANE: channel i < 2 of the wave's pair.
+            // px = (x, y), py = (y, -x).
+            if (i >= (LOAD == TAB_ROW ? MG : 2)) return;
+            const float w = LOAD == TAB_ROW ? R.q[2] : i ? rot[0].z : rot[0].x;
+            float x = R.q[i] * w, y = R.u[i] * w;
+            if (FLAGS) {
+                x = w == 0.0f ? 0.0f : x;
+                y = w == 0.0f ? 0.0f : y;
+            }
+            if (PREC == RMSYNTH_SPLIT_FP16) {
+                x *= LOAD == TAB_ROW ? fsc[i] : lsc;
+                y *= LOAD == TAB_ROW ? fsc[i] : lsc;
+            }
+            px[2 * i] = x;
+            px[2 * i + 1] = y;
+            py[2 * i] = y;
+            py[2 * i + 1] = -x;
+            return;
+        }
         const f32x4_t rr = rot[i >> 1];
         const float rc = (i & 1) ? rr.z : rr.x;
         const float rs = (i & 1) ? rr.w : rr.y;
@@ -279,8 +339,27 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         py[i] = yr;
     };
     auto store_data = [&](int buf) __attribute__((always_inline)) {
-        if constexpr (LOAD == FOLD) {
-            // rows Re: (Sx, Dy), Im: (Sy, -Dx) against columns (cos, sin).  Split:
+        if constexpr (LOAD == TAB_PLANE) {
+            // As below, two channels: 8 bytes each.
+            uint2* const a = reinterpret_cast<uint2*>(&lds.a[buf][(wave >> 1) * (4 * MT) + row]) + (wave & 1);
+            uint2 w[4];
+            if (F32) {
+                w[0] = make_uint2(__float_as_uint(px[0]), __float_as_uint(px[2]));
+                w[1] = make_uint2(__float_as_uint(px[1]), __float_as_uint(px[3]));
+                w[2] = make_uint2(__float_as_uint(py[0]), __float_as_uint(py[2]));
+                w[3] = make_uint2(__float_as_uint(py[1]), __float_as_uint(py[3]));
+            } else {
+                split2<PREC>(px[0], px[1], w[0].x, w[1].x);
+                split2<PREC>(px[2], px[3], w[0].y, w[1].y);
+                split2<PREC>(py[0], py[1], w[2].x, w[3].x);
+                split2<PREC>(py[2], py[3], w[2].y, w[3].y);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[2 * MT * e] = w[e];
+            return;
+        }
+        if constexpr (OCT) {
+            // rows Re: (Sx, Dy), Im: (Sy, -Dx) (TAB: S = D = X) against columns (cos, sin).  Split:
             // [pair quad][Re hi, Re lo, Im hi, Im lo][row], one dword per pair;
             // FP32: [pair quad][Re, Im][cos part, sin part][row], one float each.
 #pragma unroll
@@ -332,7 +411,7 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
         }
     };
 
-    // acc[g][s]: LOS group g (32 LOS), sums s = xc, ys, yc, xs (FOLD: with Re, Im
+    // acc[g][s]: LOS group g (32 LOS), sums s = xc, ys, yc, xs (COLS: with Re, Im
     // for x, y and the wave's two blocks of 32 columns for c, s).
     f32x16_t acc[MG][4];
 #pragma unroll
@@ -502,14 +581,15 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     }
     // The sums become the outputs in place: Fq, Fu of column cp in acc[g][0],
     // acc[g][2], of column cm in acc[g][1], acc[g][3].
-    const int cp = LOAD == FOLD ? 64 * wave + col : NH + 32 * wave + col;            // +h
-    const int cm = LOAD == FOLD ? 64 * wave + 32 + col : NH - 1 - 32 * wave - col;  // -h
-    if constexpr (LOAD == FOLD) {
-        const float2 b0 = kbase[n0 + cp], b1 = kbase[n0 + cm];
+    const int cp = COLS ? 64 * wave + col : NH + 32 * wave + col;            // +h
+    const int cm = COLS ? 64 * wave + 32 + col : NH - 1 - 32 * wave - col;  // -h
+    if constexpr (COLS) {
 #pragma unroll
         for (int g = 0; g < MG; ++g) {
-            turn(acc[g][0], acc[g][2], b0);
-            turn(acc[g][3], acc[g][1], b1);
+            if constexpr (LOAD == FOLD) {
+                turn(acc[g][0], acc[g][2], kbase[n0 + cp]);
+                turn(acc[g][3], acc[g][1], kbase[n0 + cm]);
+            }
             const f32x16_t re = acc[g][3];
             acc[g][3] = acc[g][1];
             acc[g][1] = re;
@@ -743,11 +823,58 @@ __global__ void fold_tables_kernel(const double* __restrict__ grid, int nphi_pad
     }
 }
 
+// Table of the table form: T[K-step][64-output block][4][lane] as in the folded
+// form, (c, s) = (cos, sin)(2 pi b_j phi_k) of the K-step's 8 channels;
+// ew_j = (K w_j, 0).
+__global__ void phase_table_kernel(const double* __restrict__ bj, const double* __restrict__ phik,
+                                   const float* __restrict__ wj, int nchan_pad, int nphi_pad, double K,
+                                   float2* __restrict__ ew, uint4* __restrict__ Tbf,
+                                   uint4* __restrict__ Thf, uint4* __restrict__ Tf32)
+{
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx < (int64_t)(nchan_pad / 8) * nphi_pad) {
+        const int kk = (int)(idx / nphi_pad), at = (int)(idx % nphi_pad), lane = at & 63;
+        const int64_t o = 4 * (idx - lane) + lane;
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+            const double g = phik[at - lane + 32 * cb + (lane & 31)];
+            float c[2][4], s[2][4];  // both channel quads
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) phase_cos_sin(g * bj[8 * kk + 4 * p + e], c[p][e], s[p][e]);
+            uint32_t h[4], l[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float ce = lane < 32 ? c[0][e] : c[1][e], se = lane < 32 ? s[0][e] : s[1][e];
+                split2_bf16(ce, se, h[e], l[e]);
+            }
+            Tbf[o + 64 * (2 * cb)] = make_uint4(h[0], h[1], h[2], h[3]);
+            Tbf[o + 64 * (2 * cb + 1)] = make_uint4(l[0], l[1], l[2], l[3]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float ce = lane < 32 ? c[0][e] : c[1][e], se = lane < 32 ? s[0][e] : s[1][e];
+                split2_f16(ce, se, h[e], l[e]);
+            }
+            Thf[o + 64 * (2 * cb)] = make_uint4(h[0], h[1], h[2], h[3]);
+            Thf[o + 64 * (2 * cb + 1)] = make_uint4(l[0], l[1], l[2], l[3]);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const f32x4_t v = lane < 32 ? f32x4_t{c[p][0], c[p][1], c[p][2], c[p][3]}
+                                            : f32x4_t{s[p][0], s[p][1], s[p][2], s[p][3]};
+                Tf32[o + 64 * (2 * p + cb)] = __builtin_bit_cast(uint4, v);
+            }
+        }
+    }
+    if (idx < nchan_pad) ew[idx] = make_float2((float)(K * (double)wj[idx]), 0.0f);
+}
+
 template <int LOAD, int PREC, int MG>
 hipError_t launch(const rmsynth_plan_s& p, const ExecArgs& a)
 {
     // Folded: K-tiles of ksteps K-steps, kpad channels below channel 0.
-    const int nk = LOAD == FOLD ? (p.nchan + p.kpad) / KC : (p.nchan + KC - 1) / KC;
+    constexpr int kc = LOAD == TAB_ROW || LOAD == TAB_PLANE ? 8 : KC;
+    const int nk = LOAD == FOLD ? (p.nchan + p.kpad) / KC : (p.nchan + kc - 1) / kc;
     const int64_t blocks = (a.nlos + 32 * MG - 1) / (32 * MG) * p.ftiles;
     if (blocks <= 0) return hipSuccess;
     const uint4* T = PREC == RMSYNTH_FP32 ? p.d_Tf32 : PREC == RMSYNTH_SPLIT_FP16 ? p.d_Thf : p.d_Tbf;
@@ -793,6 +920,8 @@ template <int PREC>
 hipError_t launch_load(const rmsynth_plan_s& p, const ExecArgs& a)
 {
     if (p.cuniform) return launch_mg<FOLD, PREC>(p, a);
+    if (p.etab)
+        return a.layout != RMSYNTH_LOS_MAJOR ? launch_mg<TAB_PLANE, PREC>(p, a) : launch_mg<TAB_ROW, PREC>(p, a);
     if (a.layout != RMSYNTH_LOS_MAJOR) return launch_mg<LOAD_PLANE, PREC>(p, a);
     return a.vec4 ? launch_mg<LOAD_ROW4, PREC>(p, a) : launch_mg<LOAD_ROW, PREC>(p, a);
 }
@@ -824,5 +953,13 @@ hipError_t launch_fold_tables(const rmsynth_plan_s& p, hipStream_t stream)
     hipLaunchKernelGGL(fold_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
                        p.d_phi, p.nphi_pad, p.ksteps, b0c, p.kdb, p.K, p.d_kbase, p.d_krot, p.d_Tbf,
                        p.d_Thf, p.d_Tf32);
+    return hipGetLastError();
+}
+
+hipError_t launch_phase_table(const rmsynth_plan_s& p, hipStream_t stream)
+{
+    const int64_t n = std::max<int64_t>((int64_t)(p.nchan_pad / 8) * p.nphi_pad, p.nchan_pad);
+    hipLaunchKernelGGL(phase_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, p.d_b,
+                       p.d_phi, p.d_w, p.nchan_pad, p.nphi_pad, p.K, p.d_base, p.d_Tbf, p.d_Thf, p.d_Tf32);
     return hipGetLastError();
 }

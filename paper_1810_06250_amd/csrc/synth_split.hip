@@ -224,6 +224,53 @@ hipError_t launch_t(const rmsynth_plan_s& p, const ExecArgs& a)
     return hipGetLastError();
 }
 
+// Per-LOS power-of-two scale for the FP16 split: M = K max_j w_j max(|Q_j|, |U_j|)
+// (K = 1 for the per-element split kernel, which applies K after the sums)
+// bounds the rotated components up to a factor sqrt 2; the scale 2^(13 - E), with
+// M < 2^E, keeps them below 2^14 (half precision's largest finite value is
+// 65504), so hi and lo stay normal down to 2^-10 of the LOS's largest value.
+// Non-finite values are ignored (they poison their LOS anyway).
+template <int LAYOUT>
+__global__ __launch_bounds__(256) void los_scale_kernel(const float* __restrict__ Q,
+                                                        const float* __restrict__ U,
+                                                        int64_t nlos, int64_t ld, int nchan,
+                                                        const float* __restrict__ wj, float K,
+                                                        float* __restrict__ scale)
+{
+    float m = 0.0f;
+    int64_t l;
+    if (LAYOUT == RMSYNTH_LOS_MAJOR) {
+        // One wave per LOS row.
+        l = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+        if (l >= nlos) return;
+        for (int j = threadIdx.x & 63; j < nchan; j += 64) {
+            const float a = __builtin_fabsf(Q[l * ld + j]), b = __builtin_fabsf(U[l * ld + j]);
+            const float v = wj[j] * __builtin_fmaxf(a, b);
+            if (v <= 3.0e38f) m = __builtin_fmaxf(m, v);
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off, 64));
+        if ((threadIdx.x & 63) != 0) return;
+    } else {
+        // One thread per LOS, channel planes read coalesced along LOS.
+        l = (int64_t)blockIdx.x * 256 + threadIdx.x;
+        if (l >= nlos) return;
+        for (int j = 0; j < nchan; ++j) {
+            const float a = __builtin_fabsf(Q[(int64_t)j * ld + l]), b = __builtin_fabsf(U[(int64_t)j * ld + l]);
+            const float v = wj[j] * __builtin_fmaxf(a, b);
+            if (v <= 3.0e38f) m = __builtin_fmaxf(m, v);
+        }
+    }
+    m *= K;
+    int e = 0;
+    if (m > 0.0f) {
+        (void)__builtin_frexpf(m, &e);  // m < 2^e
+        e = 13 - e;
+        e = e < -100 ? -100 : (e > 100 ? 100 : e);
+    }
+    scale[l] = __builtin_ldexpf(1.0f, e);
+}
+
 }  // namespace
 
 int64_t split_los_per_tile() { return MT; }
@@ -231,4 +278,21 @@ int64_t split_los_per_tile() { return MT; }
 hipError_t launch_synth_split(const rmsynth_plan_s& p, const ExecArgs& a, int precision)
 {
     return precision == RMSYNTH_SPLIT_FP16 ? launch_t<true>(p, a) : launch_t<false>(p, a);
+}
+
+hipError_t launch_los_scale(const rmsynth_plan_s& p, const ExecArgs& a)
+{
+    // The kernels with tables fold K into the data they
+    // split; the per-element split kernel applies it in the epilogue, so its
+    // scale ignores K (K = 1 in the folded adjoint plans).
+    const float k = (p.uniform || p.etab) ? (float)p.K : 1.0f;
+    if (a.layout == RMSYNTH_LOS_MAJOR)
+        hipLaunchKernelGGL(los_scale_kernel<RMSYNTH_LOS_MAJOR>, dim3((unsigned)((a.nlos + 3) / 4)),
+                           dim3(256), 0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_w, k,
+                           a.los_scale);
+    else
+        hipLaunchKernelGGL(los_scale_kernel<RMSYNTH_FREQ_MAJOR>, dim3((unsigned)((a.nlos + 255) / 256)),
+                           dim3(256), 0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_w, k,
+                           a.los_scale);
+    return hipGetLastError();
 }

@@ -71,3 +71,26 @@ def test_folded_adjoint_edges(prec, nlos, nchan, nphi):
     size = np.maximum(np.hypot(rq, ru).max(1), np.sqrt((D ** 2).sum((0, 2))))
     assert np.max(err / size) <= SCALE_TOL[prec]
     plan.close()
+
+
+@pytest.mark.parametrize("prec", list(rs.PRECISIONS))
+@pytest.mark.parametrize("layout", [LOS_MAJOR, FREQ_MAJOR], ids=["los", "freq"])
+@pytest.mark.parametrize("nlos,nchan,nphi", [(1, 7, 40), (31, 8, 255), (33, 9, 256), (64, 16, 257), (65, 23, 100),
+                                             (9001, 25, 513)])
+def test_phase_table_edges(prec, layout, nlos, nchan, nphi):
+    """Irregular grids contract 8 channels per K-step against the plan's phase
+    table: one below, at and above a K-step, one to four of them, ragged LOS
+    and phi tiles, channels of weight 0 holding NaN, both heights of LOS tile."""
+    note(f"phase table {nlos} x {nchan} x {nphi} layout={layout} {prec}")
+    c = make_small_cube(nlos, nchan, 3, seed=nlos + nchan, nflag=nchan // 8, nsrc=nlos // 8 + 1)
+    phi = np.sort(np.random.default_rng(nphi).uniform(-100, 100, nphi))
+    Q, U = np.float32(c["Q"]), np.float32(c["U"])
+    Q[:, c["weights"] == 0] = np.nan
+    pick = np.unique(np.r_[0:min(nlos, 70), max(0, nlos - 70):nlos])
+    plan = rs.Plan(c["lambda2"], c["weights"], phi)
+    rq, ru = oracle.fdf(Q[pick].astype(np.float64), U[pick].astype(np.float64), c["lambda2"], c["weights"], phi)
+    if layout == FREQ_MAJOR:
+        Q, U = np.ascontiguousarray(Q.T), np.ascontiguousarray(U.T)
+    Fq, Fu, _ = plan.execute(dev32(Q), dev32(U), layout, rs.PRECISIONS[prec])
+    assert np.max(oracle.per_los_error(host(Fq)[pick], host(Fu)[pick], rq, ru)) <= SCALE_TOL[prec]
+    plan.close()
