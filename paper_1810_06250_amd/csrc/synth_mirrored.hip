@@ -65,8 +65,7 @@ namespace {
 
 constexpr int KC = kMirrorChan;      // channels per K-step
 constexpr int NH = kMirrorTile / 2;  // pairs per tile
-constexpr int64_t kSmallTiles = 128;  // see launch_mg
-constexpr int SR = kMirrorTile + 4;  // row stride (floats) of the epilogue's tile: conflict-free b128 rows
+constexpr int64_t kSmallWaves = 512;  // see launch_mg
 
 enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2, FOLD = 3, TAB_ROW = 4, TAB_PLANE = 5 };
 
@@ -101,18 +100,20 @@ __device__ __forceinline__ f32x16_t mfma16(uint4 a, uint4 b, f32x16_t c)
 // frequency-major: K-steps of 8 channels, base holds (K w_j, 0).
 // FLAGS: some channel has weight 0; its (zero) rotation then also clears
 // whatever the data hold there, NaN included.
-// MG: LOS groups (of 32) per tile; the results do not depend on it.
+// MG: LOS groups (of 32) per tile; NW: waves of 64 columns per workgroup (4; 2
+// only where a row's lanes need not follow the waves: FOLD, TAB_ROW).  The
+// results depend on neither.
 // PEAKS 1: the epilogue also reduces |F|^2 of every LOS over each 64 phi and
 // writes one PeakPart per (LOS, 64 phi) for peak_merge_kernel, at
 // part[(64-phi block) * part_ld + LOS].  PEAKS 2: F is not stored; one PeakRec
 // each instead, for peak_merge_rec_kernel.
-template <int LOAD, int PREC, bool FLAGS, int PEAKS, int MG>
-__global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
+template <int LOAD, int PREC, bool FLAGS, int PEAKS, int MG, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     const float* __restrict__ Q, const float* __restrict__ U, int64_t nlos, int64_t ld, int nchan,
     const float2* __restrict__ base, const uint4* __restrict__ T, int nchan_pad, int nk, int nphi,
     int tiles_n, float* __restrict__ Fq, float* __restrict__ Fu, float* __restrict__ Fabs,
     const float* __restrict__ los_scale, PeakPart* __restrict__ part, int64_t part_ld,
-    PeakRec* __restrict__ rec, int ksteps, int pad, const float2* __restrict__ kbase,
+    PeakRec* __restrict__ rec, int ldT, int ksteps, int pad, const float2* __restrict__ kbase,
     const float2* __restrict__ krot)
 {
     static_assert(LOAD != FOLD || (PEAKS == 0 && !FLAGS), "the folded form has no peaks and no flags");
@@ -123,7 +124,11 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     constexpr bool COLS = LOAD == FOLD || TAB;
     constexpr bool OCT = LOAD == FOLD || LOAD == TAB_ROW;  // eight lanes share a row
     constexpr bool PLANE = LOAD == LOAD_PLANE || LOAD == TAB_PLANE;
+    static_assert(NW == 4 || OCT, "two waves: rows shared by eight lanes only");
+    constexpr int TILE = COLS ? 64 * NW : kMirrorTile;  // phi (output columns) per tile
+    constexpr int SR = TILE + 4;     // row stride (floats) of the epilogue's tile: conflict-free b128 rows
     constexpr int MT = 32 * MG;      // LOS per tile
+    constexpr int RT = 8 * NW, IT = OCT ? MT / RT : 2;  // OCT: rows per pass, passes
     constexpr int STEP = 4 * MT * 2;  // uint4 of a packed K-step: [2 channel octets or quad pairs][4][MT]
     union Lds {
         uint4 a[3][STEP];
@@ -138,7 +143,7 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     const uint32_t mleft = gridDim.x / tiles_n - 8u * grp, wide = mleft < 8u ? mleft : 8u;
     const int tn = (int)(in_grp / wide);
     const int64_t l0 = (int64_t)(8u * grp + in_grp % wide) * MT;
-    const int n0 = tn * kMirrorTile;
+    const int n0 = tn * TILE;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int half = lane >> 5, col = lane & 31;
@@ -159,24 +164,25 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     const float* const Ut = PLANE ? U + l0 : U + l0 * ld;
     const_f4_ptr bt = (const_f4_ptr)(TAB ? base : base + (int64_t)tn * nchan_pad);
     // OCT: eight lanes share a LOS row, lane cc the pair or channel cc of the
-    // K-step, rows rq + 32 i: a wave's load covers 8 rows x 32 contiguous bytes.
+    // K-step, rows rq + RT i: a wave's load covers 8 rows x 32 contiguous bytes.
     const int cc = t & 7, rq = t >> 3;
-    uint32_t frow[MG];
-    float fsc[MG];
+    uint32_t frow[IT];
+    float fsc[IT];
     if constexpr (OCT) {
 #pragma unroll
-        for (int i = 0; i < MG; ++i) {
-            const int r = rq + 32 * i < left ? rq + 32 * i : (int)left;
+        for (int i = 0; i < IT; ++i) {
+            const int r = rq + RT * i < left ? rq + RT * i : (int)left;
             frow[i] = 4u * (uint32_t)(r * (int)ld);
             fsc[i] = PREC == RMSYNTH_SPLIT_FP16 ? los_scale[l0 + r] : 1.0f;
         }
     }
     // Table columns of this wave: [K-step][64-output block][4][64 lanes].
-    const uint4* const Tw = T + (COLS ? 4 * tn + wave : wave) * 256 + lane;
-    const int tstep = COLS ? 1024 * tiles_n : 1024;
+    const uint4* const Tw = T + (COLS ? NW * tn + wave : wave) * 256 + lane;
+    const int tstep = COLS ? ldT : 1024;
 
     struct Data {
-        float q[4], u[4];
+        float q[2 * IT], u[2 * IT];
+        float w;  // TAB_ROW
     };
     struct Frag {
         uint4 v[4];
@@ -208,30 +214,30 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     };
     auto load_data = [&](Data& R, int k) __attribute__((always_inline)) {
         if constexpr (LOAD == FOLD) {
-            // q, u [0, 1]: the pair's upper channel, [2, 3]: its lower one, of
+            // q, u [i]: the pair's upper channel, [IT + i]: its lower one, of
             // rows i; channels past either end are cleared when packed.
             int jp, jm;
             pair_channels(k, jp, jm);
             const uint32_t op = 4u * (uint32_t)(jp < 0 ? 0 : jp < nchan ? jp : nchan - 1);
             const uint32_t om = 4u * (uint32_t)(jm < 0 ? 0 : jm < nchan ? jm : nchan - 1);
 #pragma unroll
-            for (int i = 0; i < MG; ++i) {
+            for (int i = 0; i < IT; ++i) {
                 auto at = [&](const float* b, uint32_t o) {
                     return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b) + (frow[i] + o));
                 };
                 R.q[i] = at(Qt, op);
                 R.u[i] = at(Ut, op);
-                R.q[2 + i] = at(Qt, om);
-                R.u[2 + i] = at(Ut, om);
+                R.q[IT + i] = at(Qt, om);
+                R.u[IT + i] = at(Ut, om);
             }
             return;
         }
         if constexpr (LOAD == TAB_ROW) {
-            // q, u [i]: rows i; q[2]: the channel's weight (0 past the end).
+            // q, u [i]: rows i; w: the channel's weight (0 past the end).
             const int jw = 8 * k + cc, j = jw < nchan ? jw : nchan - 1;
-            R.q[2] = base[jw].x;
+            R.w = base[jw].x;
 #pragma unroll
-            for (int i = 0; i < MG; ++i) {
+            for (int i = 0; i < IT; ++i) {
                 R.q[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Qt) + (frow[i] + 4u * (uint32_t)j));
                 R.u[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ut) + (frow[i] + 4u * (uint32_t)j));
             }
@@ -284,17 +290,17 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     };
     // Rotate and pack the quad: FP32 as float4 x, y of quad `wave`; split as
     // the 8-byte half of the channel octet's x hi, x lo, y hi, y lo.
-    float px[4], py[4];
+    float px[2 * IT], py[2 * IT];
     auto rotate1 = [&](const Data& R, int i, int k) __attribute__((always_inline)) {
         if constexpr (LOAD == FOLD) {
-            // i < MG: S, D of row i as px = (Sx, Dy), py = (Sy, -Dx)
-            if (i >= MG) return;
+            // i < IT: S, D of row i as px = (Sx, Dy), py = (Sy, -Dx)
+            if (i >= IT) return;
             const float sc = fsc[i];
             int jp, jm;
             pair_channels(k, jp, jm);
             const bool okp = (uint32_t)jp < (uint32_t)nchan, okm = (uint32_t)jm < (uint32_t)nchan;
-            const float xp = okp ? R.q[i] * sc : 0.0f, xm = okm ? R.q[2 + i] * sc : 0.0f;
-            const float yp = okp ? R.u[i] * sc : 0.0f, ym = okm ? R.u[2 + i] * sc : 0.0f;
+            const float xp = okp ? R.q[i] * sc : 0.0f, xm = okm ? R.q[IT + i] * sc : 0.0f;
+            const float yp = okp ? R.u[i] * sc : 0.0f, ym = okm ? R.u[IT + i] * sc : 0.0f;
             px[2 * i] = xp + xm;
             px[2 * i + 1] = yp - ym;
             py[2 * i] = yp + ym;
@@ -302,10 +308,10 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
             return;
         }
         if constexpr (TAB) {
-            // TAB_ROW: row i < MG; TAB_PLANE: channel i < 2 of the wave's pair.
+            // TAB_ROW: row i < IT; TAB_PLANE: channel i < 2 of the wave's pair.
             // px = (x, y), py = (y, -x).
-            if (i >= (LOAD == TAB_ROW ? MG : 2)) return;
-            const float w = LOAD == TAB_ROW ? R.q[2] : i ? rot[0].z : rot[0].x;
+            if (i >= IT) return;
+            const float w = LOAD == TAB_ROW ? R.w : i ? rot[0].z : rot[0].x;
             float x = R.q[i] * w, y = R.u[i] * w;
             if (FLAGS) {
                 x = w == 0.0f ? 0.0f : x;
@@ -363,8 +369,8 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
             // [pair quad][Re hi, Re lo, Im hi, Im lo][row], one dword per pair;
             // FP32: [pair quad][Re, Im][cos part, sin part][row], one float each.
 #pragma unroll
-            for (int i = 0; i < MG; ++i) {
-                uint32_t* const a = reinterpret_cast<uint32_t*>(&lds.a[buf][(cc >> 2) * (4 * MT) + rq + 32 * i]) + (cc & 3);
+            for (int i = 0; i < IT; ++i) {
+                uint32_t* const a = reinterpret_cast<uint32_t*>(&lds.a[buf][(cc >> 2) * (4 * MT) + rq + RT * i]) + (cc & 3);
                 uint32_t w[4];
                 if (F32) {
                     w[0] = __float_as_uint(px[2 * i]);
@@ -629,12 +635,14 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
     };
     if constexpr (PEAKS != 2) {
         const int nl = (int)(nlos - l0 < MT ? nlos - l0 : MT);
-        const int n4 = nphi - n0 - 4 * lane;  // phi left at this lane's first column
+        constexpr int LR = TILE / 4, RW = 64 / LR;  // lanes per row, rows per wave and pass
+        const int lc = 4 * (lane % LR), r0 = RW * wave + lane / LR;
+        const int n4 = nphi - n0 - lc;  // phi left at this lane's first column
         auto store_rows = [&](float* F) __attribute__((always_inline)) {
-            float* out = F + (l0 + wave) * nphi + n0 + 4 * lane;
-            const float* in = sm + wave * SR + 4 * lane;
+            float* out = F + (l0 + r0) * nphi + n0 + lc;
+            const float* in = sm + r0 * SR + lc;
 #pragma unroll 4
-            for (int i = wave; i < nl; i += 4, out += 4 * (int64_t)nphi, in += 4 * SR) {
+            for (int i = r0; i < nl; i += NW * RW, out += NW * RW * (int64_t)nphi, in += NW * RW * SR) {
                 const f32x4_t v = *reinterpret_cast<const f32x4_t*>(in);
                 if (n4 >= 4) {
                     __builtin_nontemporal_store(v, reinterpret_cast<f32x4u_t*>(out));
@@ -700,7 +708,7 @@ __global__ __launch_bounds__(256, 2) void synth_mirrored_kernel(
             }
         }
         const int64_t l = l0 + lane;
-        const int blk = 4 * tn + wave;
+        const int blk = TILE / 64 * tn + wave;
         const bool mine = lane < MT && l < nlos && 64 * blk < nphi;
         const int idx = bad ? -2 : 64 * blk + bk;
         if constexpr (PEAKS == 1) {
@@ -869,20 +877,22 @@ __global__ void phase_table_kernel(const double* __restrict__ bj, const double* 
     if (idx < nchan_pad) ew[idx] = make_float2((float)(K * (double)wj[idx]), 0.0f);
 }
 
-template <int LOAD, int PREC, int MG>
+template <int LOAD, int PREC, int MG, int NW>
 hipError_t launch(const rmsynth_plan_s& p, const ExecArgs& a)
 {
+    constexpr bool tab = LOAD == TAB_ROW || LOAD == TAB_PLANE;
+    constexpr int kc = tab ? 8 : KC;
     // Folded: K-tiles of ksteps K-steps, kpad channels below channel 0.
-    constexpr int kc = LOAD == TAB_ROW || LOAD == TAB_PLANE ? 8 : KC;
     const int nk = LOAD == FOLD ? (p.nchan + p.kpad) / KC : (p.nchan + kc - 1) / kc;
-    const int64_t blocks = (a.nlos + 32 * MG - 1) / (32 * MG) * p.ftiles;
+    const int tiles_n = LOAD == FOLD || tab ? (p.nphi + 64 * NW - 1) / (64 * NW) : p.ftiles;
+    const int64_t blocks = (a.nlos + 32 * MG - 1) / (32 * MG) * tiles_n;
     if (blocks <= 0) return hipSuccess;
     const uint4* T = PREC == RMSYNTH_FP32 ? p.d_Tf32 : PREC == RMSYNTH_SPLIT_FP16 ? p.d_Thf : p.d_Tbf;
-#define RMS_LAUNCH(G, P)                                                                                \
-    hipLaunchKernelGGL((synth_mirrored_kernel<LOAD, PREC, G, P, MG>), dim3((unsigned)blocks), dim3(256),  \
-                       0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_base, T, p.nchan_pad, nk,      \
-                       p.nphi, p.ftiles, a.Fq, a.Fu, a.Fabs, a.los_scale, a.peak_part, a.peak_part_ld,   \
-                       a.peak_rec, p.ksteps, p.kpad, p.d_kbase, p.d_krot)
+#define RMS_LAUNCH(G, P)                                                                                    \
+    hipLaunchKernelGGL((synth_mirrored_kernel<LOAD, PREC, G, P, MG, NW>), dim3((unsigned)blocks),            \
+                       dim3(64 * NW), 0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_base, T, p.nchan_pad, \
+                       nk, p.nphi, tiles_n, a.Fq, a.Fu, a.Fabs, a.los_scale, a.peak_part, a.peak_part_ld,     \
+                       a.peak_rec, 4 * p.nphi_pad, p.ksteps, p.kpad, p.d_kbase, p.d_krot)
 #define RMS_LAUNCH_P(G)                                                               \
     do {                                                                              \
         if constexpr (PREC != RMSYNTH_FP32 && LOAD != FOLD) { /* elsewhere peaks are a kernel of their own */ \
@@ -904,26 +914,41 @@ hipError_t launch(const rmsynth_plan_s& p, const ExecArgs& a)
     return hipGetLastError();
 }
 
-// Half-height tiles where full ones would leave half of the 256 CUs idle: such
-// a call is bound by the latency of one tile (64^2 LOS x 128 ch x 201 phi, 64
-// full tiles: bf16x3 12.7 -> 9.8 us, FP32 24.1 -> 15.8; 64 LOS x 400 x 2001, 8:
-// 19.4 -> 14.5).  At 256 full tiles both take the same time (26 us), at 512 the
-// half-height ones 10 % more.
-template <int LOAD, int PREC>
+// Half-height tiles where full ones would leave half of the chip's 1024 SIMDs
+// without a wave: such a call is bound by the latency of one tile (64^2 LOS x
+// 128 ch x 201 phi, 64 full tiles of 4 waves: bf16x3 12.7 -> 9.8 us, FP32 24.1 ->
+// 15.8; 64 LOS x 400 x 2001, 8 tiles: 19.4 -> 14.5).  At 256 full tiles both take
+// the same time (26 us), at 512 the half-height ones 10 % more.
+template <int LOAD, int PREC, int NW>
 hipError_t launch_mg(const rmsynth_plan_s& p, const ExecArgs& a)
 {
-    const int64_t full = (a.nlos + 63) / 64 * p.ftiles;
-    return full <= kSmallTiles ? launch<LOAD, PREC, 1>(p, a) : launch<LOAD, PREC, 2>(p, a);
+    const int64_t waves = (a.nlos + 63) / 64 * ((p.nphi + 64 * NW - 1) / (64 * NW)) * NW;
+    return waves <= kSmallWaves ? launch<LOAD, PREC, 1, NW>(p, a) : launch<LOAD, PREC, 2, NW>(p, a);
+}
+
+// Output columns come in tiles of 256, or of 128 (two waves) where that pads
+// fewer: what the matrix cores bound (FP32, the table form) gains what is not
+// padded (262144 LOS x 1201 phi -> 288 channels FP32 5.01 -> 3.93 ms; 131072 x
+// 400 -> 300 phi bf16x3 table 0.52 -> 0.48).  The folded split forms read the
+// rows once per tile and are bound by that: one narrow tile gains (1201 -> 100
+// channels bf16x3 1.14 -> 1.09 ms), three instead of two wide ones lose (288
+// channels 1.96 -> 2.24).
+template <int LOAD, int PREC>
+hipError_t launch_cols(const rmsynth_plan_s& p, const ExecArgs& a)
+{
+    const bool fewer = (p.nphi + 127) / 128 * 128 < (p.nphi + 255) / 256 * 256;
+    const bool narrow = fewer && (LOAD == TAB_ROW || PREC == RMSYNTH_FP32 || p.nphi <= 128);
+    return narrow ? launch_mg<LOAD, PREC, 2>(p, a) : launch_mg<LOAD, PREC, 4>(p, a);
 }
 
 template <int PREC>
 hipError_t launch_load(const rmsynth_plan_s& p, const ExecArgs& a)
 {
-    if (p.cuniform) return launch_mg<FOLD, PREC>(p, a);
-    if (p.etab)
-        return a.layout != RMSYNTH_LOS_MAJOR ? launch_mg<TAB_PLANE, PREC>(p, a) : launch_mg<TAB_ROW, PREC>(p, a);
-    if (a.layout != RMSYNTH_LOS_MAJOR) return launch_mg<LOAD_PLANE, PREC>(p, a);
-    return a.vec4 ? launch_mg<LOAD_ROW4, PREC>(p, a) : launch_mg<LOAD_ROW, PREC>(p, a);
+    const bool planes = a.layout != RMSYNTH_LOS_MAJOR;
+    if (p.cuniform) return launch_cols<FOLD, PREC>(p, a);
+    if (p.etab) return planes ? launch_mg<TAB_PLANE, PREC, 4>(p, a) : launch_cols<TAB_ROW, PREC>(p, a);
+    if (planes) return launch_mg<LOAD_PLANE, PREC, 4>(p, a);
+    return a.vec4 ? launch_mg<LOAD_ROW4, PREC, 4>(p, a) : launch_mg<LOAD_ROW, PREC, 4>(p, a);
 }
 
 }  // namespace
