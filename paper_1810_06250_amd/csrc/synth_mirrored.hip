@@ -67,7 +67,7 @@ constexpr int KC = kMirrorChan;      // channels per K-step
 constexpr int NH = kMirrorTile / 2;  // pairs per tile
 constexpr int64_t kSmallWaves = 512;  // see launch_mg
 
-enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2, FOLD = 3, TAB_ROW = 4, TAB_PLANE = 5 };
+enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2, FOLD = 3, TAB_ROW = 4, TAB_PLANE = 5, LOAD_TAIL = 6 };
 
 typedef const __attribute__((address_space(4))) f32x4_t* const_f4_ptr;
 typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
@@ -90,8 +90,9 @@ __device__ __forceinline__ f32x16_t mfma16(uint4 a, uint4 b, f32x16_t c)
                                                        __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// LOAD: how Q/U are read.  ROW4: LOS-major rows of 16-byte aligned quads;
-// ROW: LOS-major, any alignment; PLANE: frequency-major.
+// LOAD: how Q/U are read.  ROW4: LOS-major rows, 4 n channels, as quads of any
+// alignment; TAIL: the same for the other channel counts above 4; ROW:
+// LOS-major, single values; PLANE: frequency-major.
 // FOLD: the folded form (LOS-major, any alignment; no flags, no peaks): T is its
 // table, nk the K-steps of all K-tiles, ksteps those of one, pad the zero
 // channels below channel 0, kbase and krot the K exp(-2 pi i b_0' g) and
@@ -253,10 +254,10 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
             return;
         }
         const int j0 = k * KC + 4 * wave;
-        if (LOAD == LOAD_ROW4) {
-            const int j = j0 < nchan ? j0 : nchan - 4;
-            const float4 a = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(Qt + j) + voff);
-            const float4 b = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(Ut + j) + voff);
+        if (LOAD == LOAD_ROW4 || LOAD == LOAD_TAIL) {
+            const int j = j0 < nchan - 4 ? j0 : nchan - 4;
+            const f32x4u_t a = *reinterpret_cast<const f32x4u_t*>(reinterpret_cast<const char*>(Qt + j) + voff);
+            const f32x4u_t b = *reinterpret_cast<const f32x4u_t*>(reinterpret_cast<const char*>(Ut + j) + voff);
             R.q[0] = a.x; R.q[1] = a.y; R.q[2] = a.z; R.q[3] = a.w;
             R.u[0] = b.x; R.u[1] = b.y; R.u[2] = b.z; R.u[3] = b.w;
         } else {
@@ -267,6 +268,22 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
                 R.q[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Qt + at) + voff);
                 R.u[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ut + at) + voff);
             }
+        }
+    };
+    // TAIL: the last quad of a row was read from its last 4 channels; its own
+    // go to the front (what follows them meets a zero rotation).
+    auto align_tail = [&](Data& R, int k) __attribute__((always_inline)) {
+        if constexpr (LOAD == LOAD_TAIL) {
+            const int past = k * KC + 4 * wave + 4 - nchan;
+            if (past <= 0) return;
+            auto shift = [&](float* v) __attribute__((always_inline)) {
+                const float v1 = v[1], v2 = v[2], v3 = v[3];
+                v[0] = past == 1 ? v1 : past == 2 ? v2 : v3;
+                v[1] = past == 1 ? v2 : v3;
+                v[2] = v3;
+            };
+            shift(R.q);
+            shift(R.u);
         }
     };
     auto load_rot = [&](int k) __attribute__((always_inline)) {
@@ -505,6 +522,7 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
             load_rot(next(k, 3));
             __builtin_amdgcn_sched_barrier(0);
         };
+        align_tail(R, next(k, 2));
         load_b(Bn, next(k, 1));
         if (MG == 2) load_a(A1, bc, 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -533,6 +551,8 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     load_data(R1, next(0, 1));
     load_rot(0);
     load_b(B0, 0);
+    align_tail(R0, 0);
+    align_tail(R1, next(0, 1));
 #pragma unroll
     for (int i = 0; i < 4; ++i) rotate1(R0, i, 0);
     store_data(0);
@@ -948,7 +968,11 @@ hipError_t launch_load(const rmsynth_plan_s& p, const ExecArgs& a)
     if (p.cuniform) return launch_cols<FOLD, PREC>(p, a);
     if (p.etab) return planes ? launch_mg<TAB_PLANE, PREC, 4>(p, a) : launch_cols<TAB_ROW, PREC>(p, a);
     if (planes) return launch_mg<LOAD_PLANE, PREC, 4>(p, a);
-    return a.vec4 ? launch_mg<LOAD_ROW4, PREC, 4>(p, a) : launch_mg<LOAD_ROW, PREC, 4>(p, a);
+    // Quads of any alignment: with single values, 10007 LOS x 333 ch x 777 phi took
+    // 80 us in bf16x3 (now 60) and 165 in FP32 (145), 65536 LOS 405 (297) and 819
+    // (711).  The move of the row's last quad costs 1 %, so 4 n channels go without.
+    if (p.nchan < 4) return launch_mg<LOAD_ROW, PREC, 4>(p, a);
+    return p.nchan % 4 ? launch_mg<LOAD_TAIL, PREC, 4>(p, a) : launch_mg<LOAD_ROW4, PREC, 4>(p, a);
 }
 
 }  // namespace

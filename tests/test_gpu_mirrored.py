@@ -48,6 +48,33 @@ def test_tile_edges(prec, layout, shape):
 
 
 @pytest.mark.parametrize("prec", list(rs.PRECISIONS))
+@pytest.mark.parametrize("nchan,skip", [(1, 0), (2, 1), (3, 3), (4, 1), (5, 0), (6, 2), (7, 3), (18, 1), (19, 0),
+                                        (33, 2), (36, 3), (66, 1), (111, 3)])
+def test_row_quads(prec, nchan, skip):
+    """LOS-major rows are read as quads of any alignment, the last from the row's
+    last 4 channels: bases `skip` floats off, NaN on both sides of the cube, a
+    channel of weight 0 holding NaN, full and half-height tiles."""
+    note(f"row quads {nchan} channels, {skip} floats off, {prec}")
+    import torch
+    for nlos, nphi in ((70, 60), (8300, 300)):
+        c = make_small_cube(nlos, nchan, 3, seed=nchan + nlos, nflag=nchan // 8, nsrc=8)
+        phi = np.linspace(-80.0, 90.0, nphi)
+        Q, U = np.float32(c["Q"]), np.float32(c["U"])
+        Q[:, c["weights"] == 0] = np.nan
+        dev = []
+        for X in (Q, U):
+            buf = torch.full((skip + X.size + 5,), float("nan"), dtype=torch.float32, device="cuda")
+            dev.append(buf[skip:skip + X.size].view(nlos, nchan))
+            dev[-1].copy_(torch.from_numpy(X))
+        pick = np.r_[0:70, nlos - 70:nlos]
+        plan = rs.Plan(c["lambda2"], c["weights"], phi)
+        rq, ru = oracle.fdf(Q[pick].astype(np.float64), U[pick].astype(np.float64), c["lambda2"], c["weights"], phi)
+        Fq, Fu, _ = plan.execute(dev[0], dev[1], LOS_MAJOR, rs.PRECISIONS[prec])
+        assert np.max(oracle.per_los_error(host(Fq)[pick], host(Fu)[pick], rq, ru)) <= SCALE_TOL[prec]
+        plan.close()
+
+
+@pytest.mark.parametrize("prec", list(rs.PRECISIONS))
 @pytest.mark.parametrize("nlos,nchan,nphi", [(1, 3, 2), (31, 40, 31), (33, 255, 32), (64, 256, 33), (65, 257, 255),
                                              (63, 64, 256), (66, 100, 257), (40, 130, 513), (9000, 70, 300)])
 def test_folded_adjoint_edges(prec, nlos, nchan, nphi):
