@@ -158,7 +158,8 @@ int build_adjoint_plan(rmsynth_plan_s* p, const double* lambda2, const double* p
     // (same phase tolerance, now over every output lambda^2).
     double gmax = 0.0, phi0 = 0.0, dphi = 0.0;
     for (int32_t j = 0; j < p->nchan; ++j) gmax = std::max(gmax, std::fabs(hgrid[j]));
-    if (!detect_uniform(phi, p->nphi, gmax, &phi0, &dphi)) return build_etable(q);
+    // (one phi has no neighbour to be read with)
+    if (p->nphi < 2 || !detect_uniform(phi, p->nphi, gmax, &phi0, &dphi)) return build_etable(q);
     q->cuniform = true;
     q->kb0 = phi0 / M_PI;
     q->kdb = dphi / M_PI;

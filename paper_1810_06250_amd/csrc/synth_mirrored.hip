@@ -51,8 +51,9 @@
 // centring a ragged last tile on what is left of the grid, so that waves with
 // no pairs skip the matrix work, gained nothing (the workgroup still waits for
 // its full waves).
-// Folded, 262144 LOS x 2001 phi -> 400 channels (padded to 512), bf16x3: 3.15 ms
-// (6.02 with 96-phi K-tiles and no folding); table form, 131072 x 400 x 2001:
+// Folded, 262144 LOS x 2001 phi -> 400 channels (padded to 512), bf16x3: 3.07 ms
+// (6.02 with 96-phi K-tiles and no folding; 3.22 with rows read 32 bytes at a
+// time, a K-step's share, which fetched each line of a row four times into L1); table form, 131072 x 400 x 2001:
 // 2.16 ms (2.32 with 128 x 128 tiles fed through LDS), 65536 in FP32 3.13 ms
 // (3.81 with the phases generated per element).
 #include <float.h>
@@ -70,6 +71,7 @@ constexpr int64_t kSmallWaves = 512;  // see launch_mg
 enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2, FOLD = 3, TAB_ROW = 4, TAB_PLANE = 5, LOAD_TAIL = 6 };
 
 typedef const __attribute__((address_space(4))) f32x4_t* const_f4_ptr;
+typedef float f32x2u_t __attribute__((ext_vector_type(2), aligned(4)));
 typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int PREC>
@@ -182,7 +184,7 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     const int tstep = COLS ? ldT : 1024;
 
     struct Data {
-        float q[2 * IT], u[2 * IT];
+        float q[4 * IT], u[4 * IT];  // FOLD: two K-steps; else the first 2 IT
         float w;  // TAB_ROW
     };
     struct Frag {
@@ -206,30 +208,36 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
             kk = ksteps - 1;
         }
     };
+    // Pair cc of K-step kk: the K-steps 2 n and 2 n + 1 share 16 pairs, two
+    // neighbouring ones per lane, so that a row is read 64 bytes at a time.
     auto pair_channels = [&](int d, int& jp, int& jm) __attribute__((always_inline)) {
         int J, kk;
         ahead(d, J, kk);
         const int mid = J * ksteps * KC - pad + ksteps * (KC / 2);
-        jp = mid + kk * (KC / 2) + cc;
-        jm = mid - 1 - kk * (KC / 2) - cc;
+        const int i = KC * (kk >> 1) + 2 * cc + (kk & 1);
+        jp = mid + i;
+        jm = mid - 1 - i;
     };
     auto load_data = [&](Data& R, int k) __attribute__((always_inline)) {
         if constexpr (LOAD == FOLD) {
-            // q, u [i]: the pair's upper channel, [IT + i]: its lower one, of
-            // rows i; channels past either end are cleared when packed.
+            // q, u [4 i ..]: rows i; the upper channels of this K-step (an even
+            // one) and the next, then the lower ones of the next and this.
+            // Channels past either end are cleared when packed.
             int jp, jm;
             pair_channels(k, jp, jm);
-            const uint32_t op = 4u * (uint32_t)(jp < 0 ? 0 : jp < nchan ? jp : nchan - 1);
-            const uint32_t om = 4u * (uint32_t)(jm < 0 ? 0 : jm < nchan ? jm : nchan - 1);
+            auto offset = [&](int j) { return 4u * (uint32_t)(j < 0 ? 0 : j < nchan - 1 ? j : nchan - 2); };
+            const uint32_t op = offset(jp), om = offset(jm - 1);
 #pragma unroll
             for (int i = 0; i < IT; ++i) {
-                auto at = [&](const float* b, uint32_t o) {
-                    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b) + (frow[i] + o));
+                auto at = [&](const float* b, uint32_t o, float* to) {
+                    const f32x2u_t v = *reinterpret_cast<const f32x2u_t*>(reinterpret_cast<const char*>(b) + (frow[i] + o));
+                    to[0] = v.x;
+                    to[1] = v.y;
                 };
-                R.q[i] = at(Qt, op);
-                R.u[i] = at(Ut, op);
-                R.q[IT + i] = at(Qt, om);
-                R.u[IT + i] = at(Ut, om);
+                at(Qt, op, R.q + 4 * i);
+                at(Ut, op, R.u + 4 * i);
+                at(Qt, om, R.q + 4 * i + 2);
+                at(Ut, om, R.u + 4 * i + 2);
             }
             return;
         }
@@ -308,16 +316,23 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     // Rotate and pack the quad: FP32 as float4 x, y of quad `wave`; split as
     // the 8-byte half of the channel octet's x hi, x lo, y hi, y lo.
     float px[2 * IT], py[2 * IT];
-    auto rotate1 = [&](const Data& R, int i, int k) __attribute__((always_inline)) {
+    auto rotate1 = [&](const Data& R, int i, int k, bool odd) __attribute__((always_inline)) {
         if constexpr (LOAD == FOLD) {
-            // i < IT: S, D of row i as px = (Sx, Dy), py = (Sy, -Dx)
+            // i < IT: S, D of row i as px = (Sx, Dy), py = (Sy, -Dx).  A pair of
+            // channels read from the row's start instead of from -1 holds its
+            // second one in its first place.
             if (i >= IT) return;
             const float sc = fsc[i];
             int jp, jm;
             pair_channels(k, jp, jm);
             const bool okp = (uint32_t)jp < (uint32_t)nchan, okm = (uint32_t)jm < (uint32_t)nchan;
-            const float xp = okp ? R.q[i] * sc : 0.0f, xm = okm ? R.q[IT + i] * sc : 0.0f;
-            const float yp = okp ? R.u[i] * sc : 0.0f, ym = okm ? R.u[IT + i] * sc : 0.0f;
+            const bool start = (odd ? jp : jm) == 0;
+            const float* const q = R.q + 4 * i;
+            const float* const u = R.u + 4 * i;
+            const float qp = odd ? start ? q[0] : q[1] : q[0], qm = odd ? q[2] : start ? q[2] : q[3];
+            const float up = odd ? start ? u[0] : u[1] : u[0], um = odd ? u[2] : start ? u[2] : u[3];
+            const float xp = okp ? qp * sc : 0.0f, xm = okm ? qm * sc : 0.0f;
+            const float yp = okp ? up * sc : 0.0f, ym = okm ? um * sc : 0.0f;
             px[2 * i] = xp + xm;
             px[2 * i + 1] = yp - ym;
             py[2 * i] = yp + ym;
@@ -511,7 +526,7 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     Frag A0, A1;
     int bc = 0;
     auto next = [&](int k, int d) { return LOAD == FOLD ? d : k + d < nk ? k + d : nk - 1; };
-    auto step = [&](const Frag& B, Frag& Bn, Data& R, int k) __attribute__((always_inline)) {
+    auto step = [&](const Frag& B, Frag& Bn, Data& R, int k, bool odd) __attribute__((always_inline)) {
         const int bf = bc == 2 ? 0 : bc + 1;
         const int bn = bf == 2 ? 0 : bf + 1;
         // The rotations of the next packing are loaded behind the step's last
@@ -528,10 +543,11 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
         __builtin_amdgcn_sched_barrier(0);
         mma(A0, B, 0, [] {});
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rotate1(R, i, next(k, 2));
+        for (int i = 0; i < 4; ++i) rotate1(R, i, next(k, 2), odd);
         store_data(bn);
         __builtin_amdgcn_sched_barrier(0);
-        load_data(R, next(k, 4));
+        if (LOAD != FOLD) load_data(R, next(k, 4));
+        else if (odd) load_data(R, 3);
         load_a(A0, bf, 0);
         if (MG == 2) mma(A1, B, MG - 1, next_rot);
         else next_rot();
@@ -548,20 +564,20 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     Frag B0, B1;
     if (LOAD == FOLD) cj = nk / ksteps - 1;
     load_data(R0, 0);
-    load_data(R1, next(0, 1));
+    if (LOAD != FOLD) load_data(R1, next(0, 1));
     load_rot(0);
     load_b(B0, 0);
     align_tail(R0, 0);
     align_tail(R1, next(0, 1));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) rotate1(R0, i, 0);
+    for (int i = 0; i < 4; ++i) rotate1(R0, i, 0, false);
     store_data(0);
     load_rot(next(0, 1));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) rotate1(R1, i, next(0, 1));
+    for (int i = 0; i < 4; ++i) rotate1(LOAD == FOLD ? R0 : R1, i, next(0, 1), true);
     store_data(1);
     load_data(R0, next(0, 2));
-    load_data(R1, next(0, 3));
+    if (LOAD != FOLD) load_data(R1, next(0, 3));
     load_rot(next(0, 2));
     sync_next();
     load_a(A0, 0, 0);
@@ -578,16 +594,16 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
                     turn(acc[g][3], acc[g][1], r1);
                 }
             }
-            step(B0, B1, R0, k);
-            step(B1, B0, R1, k + 1);
+            step(B0, B1, R0, k, false);
+            step(B1, B0, R0, k + 1, true);
         }
     } else {
         int k = 0;
         for (; k + 1 < nk; k += 2) {
-            step(B0, B1, R0, k);
-            step(B1, B0, R1, k + 1);
+            step(B0, B1, R0, k, false);
+            step(B1, B0, R1, k + 1, true);
         }
-        if (k < nk) step(B0, B1, R0, k);
+        if (k < nk) step(B0, B1, R0, k, false);
     }
 
     // Epilogue.  Rows of this lane: 32 g + 8 (v >> 2) + 4 half + (v & 3).
@@ -823,7 +839,7 @@ __global__ void fold_tables_kernel(const double* __restrict__ grid, int nphi_pad
             auto phase = [&](int quad) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    phase_cos_sin(((double)(8 * kk + 4 * quad + e) + 0.5) * db * g, c[e], s[e]);
+                    phase_cos_sin(((double)(16 * (kk >> 1) + 2 * (4 * quad + e) + (kk & 1)) + 0.5) * db * g, c[e], s[e]);
             };
             phase(lane >> 5);
 #pragma unroll
@@ -951,8 +967,8 @@ hipError_t launch_mg(const rmsynth_plan_s& p, const ExecArgs& a)
 // padded (262144 LOS x 1201 phi -> 288 channels FP32 5.01 -> 3.93 ms; 131072 x
 // 400 -> 300 phi bf16x3 table 0.52 -> 0.48).  The folded split forms read the
 // rows once per tile and are bound by that: one narrow tile gains (1201 -> 100
-// channels bf16x3 1.14 -> 1.09 ms), three instead of two wide ones lose (288
-// channels 1.96 -> 2.24).
+// channels bf16x3 1.14 -> 1.09 ms, 0.90 since), three instead of two wide ones
+// lose (288 channels 1.96 -> 2.24, then; wide 1.87 now).
 template <int LOAD, int PREC>
 hipError_t launch_cols(const rmsynth_plan_s& p, const ExecArgs& a)
 {

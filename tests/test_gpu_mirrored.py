@@ -101,6 +101,29 @@ def test_folded_adjoint_edges(prec, nlos, nchan, nphi):
 
 
 @pytest.mark.parametrize("prec", list(rs.PRECISIONS))
+@pytest.mark.parametrize("nlos,nchan", [(70, 40), (33, 300), (8300, 130)])
+@pytest.mark.parametrize("nphi", [1, 3, 5, 15, 17, 47, 129, 259])
+def test_folded_pairs_at_row_ends(prec, nlos, nchan, nphi):
+    """The folded adjoint reads two neighbouring phi at a time; those that start
+    below phi_0 are read from phi_0 on.  A LOS of NaN must spoil no other."""
+    note(f"folded pairs {nlos} x {nchan} x {nphi} {prec}")
+    c = make_small_cube(2, nchan, 3, seed=nphi)
+    phi = np.linspace(-70.0, 95.0, nphi)
+    C = np.float32(np.random.default_rng(nlos + nphi).standard_normal((2, nlos, nphi)))
+    C[:, 1] = np.nan
+    plan = rs.Plan(c["lambda2"], c["weights"], phi)
+    Pq, Pu = plan.adjoint(dev32(C[0]), dev32(C[1]), rs.PRECISIONS[prec])
+    assert not np.isfinite(host(Pq)[1]).any() and not np.isfinite(host(Pu)[1]).any()
+    pick = np.unique(np.r_[0, 2:min(nlos, 40), max(2, nlos - 40):nlos])
+    D = C[:, pick].astype(np.float64)
+    rq, ru = oracle.adjoint(D[0], D[1], c["lambda2"], c["weights"], phi)
+    err = np.hypot(host(Pq)[pick] - rq, host(Pu)[pick] - ru).max(1)
+    size = np.maximum(np.hypot(rq, ru).max(1), np.sqrt((D ** 2).sum((0, 2))))
+    assert np.max(err / size) <= SCALE_TOL[prec]
+    plan.close()
+
+
+@pytest.mark.parametrize("prec", list(rs.PRECISIONS))
 @pytest.mark.parametrize("layout", [LOS_MAJOR, FREQ_MAJOR], ids=["los", "freq"])
 @pytest.mark.parametrize("nlos,nchan,nphi", [(1, 7, 40), (31, 8, 255), (33, 9, 256), (64, 16, 257), (65, 23, 100),
                                              (9001, 25, 513)])
