@@ -32,7 +32,10 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 MFMA_PEAK_TFLOPS = {"bf16x3": 2516.6, "fp16x3": 2516.6, "fp32": 157.3}
-MFMA_FLOP_PER_SAMPLE = {"bf16x3": 24.0, "fp16x3": 24.0, "fp32": 8.0}
+# Issued by the matrix cores per LOS*channel*phi sample: mirrored pairs of phi (or,
+# in the adjoint, folded pairs of channels) take half of the direct form's flop.
+MFMA_FLOP_PER_SAMPLE = {"bf16x3": 12.0, "fp16x3": 12.0, "fp32": 4.0}
+MFMA_FLOP_IRREGULAR = {"bf16x3": 24.0, "fp16x3": 24.0, "fp32": 8.0}
 HBM_PEAK_GBS = 8000.0
 METRIC = "LOS·chan·φ Gsamples/s + % MFMA peak, split-BF16 vs FP32 at ≤1e-5 rel err"
 
@@ -290,7 +293,7 @@ def search_leg(rs, plan, cube, prec, steps, warmup, ref_pk=None):
            "ms_per_step": wall, "event_ms": ev, "gsamples_s": samples / (wall * 1e-3) / 1e9,
            "workspace_bytes": nb}
     if prec != rs.RMSYNTH_FP32:
-        res["frac_of_mfma_peak"] = 24.0 * samples / (ev * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS["bf16x3"]
+        res["frac_of_mfma_peak"] = MFMA_FLOP_PER_SAMPLE["bf16x3"] * samples / (ev * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS["bf16x3"]
     if ref_pk is not None:
         res["identical_to_execute_peaks"] = bool(all(torch.equal(out[k], ref_pk[k])
                                                      for k in ("idx", "amp", "q_pk", "u_pk")))
@@ -466,7 +469,7 @@ def nonuniform_leg(rs, cube, sub, steps):
         log(f"non-uniform grid: {prec_name}, {n} steps")
         fused = prec_name != "fp32"
         wall, ex, pkms = time_path(rs, plan, cube, prec, Fq, Fu, pk, n, 1, fused=fused)
-        flop = MFMA_FLOP_PER_SAMPLE[prec_name] * samples
+        flop = MFMA_FLOP_IRREGULAR[prec_name] * samples
         errs, _ = oracle_errors(cube2, sub, {prec_name: (Fq, Fu, pk["idx"])})
         res["paths"][prec_name] = {
             "step": "rmsynth_execute_peaks" if fused else "rmsynth_execute + rmsynth_peaks",
@@ -747,8 +750,9 @@ def main():
         gpu_out["fp32"] = (Fq2, Fu2, pk2["idx"])
         fp32 = {"value": samples / (w32 * 1e-3) / 1e9, "unit": "Gsamples/s", "ms_per_step": w32,
                 "execute_ms": ex32, "peaks_ms": pk32,
-                "mfma_tflops": 8.0 * samples / (ex32 * 1e-3) / 1e12,
-                "frac_fp32_peak": 8.0 * samples / (ex32 * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS["fp32"]}
+                "mfma_tflops": MFMA_FLOP_PER_SAMPLE["fp32"] * samples / (ex32 * 1e-3) / 1e12,
+                "frac_fp32_peak": MFMA_FLOP_PER_SAMPLE["fp32"] * samples / (ex32 * 1e-3) / 1e12 /
+                MFMA_PEAK_TFLOPS["fp32"]}
 
     achieved = MFMA_FLOP_PER_SAMPLE[args.precision] * samples / (ex_ms * 1e-3) / 1e12
     peak = MFMA_PEAK_TFLOPS[args.precision]
