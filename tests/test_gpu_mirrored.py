@@ -74,6 +74,31 @@ def test_row_quads(prec, nchan, skip):
         plan.close()
 
 
+@pytest.mark.parametrize("layout", [LOS_MAJOR, FREQ_MAJOR], ids=["los", "freq"])
+@pytest.mark.parametrize("nlos", [1, 65, 4097, 65600])
+@pytest.mark.parametrize("nchan", [1, 8, 33, 129, 257])
+def test_half_scale_sees_every_channel(layout, nlos, nchan):
+    """The per-LOS scale of the IEEE-half split is found by up to 16 waves that
+    share the channels: LOS l has its one large value, 1e7 times the others (half
+    overflows at 65504 unscaled), in channel l % nchan, of Q and U in turn."""
+    note(f"half scale {nlos} x {nchan} layout={layout}")
+    rng = np.random.default_rng(nchan)
+    Q, U = (np.float32(1e-2 * rng.uniform(-1, 1, (nlos, nchan))) for _ in "QU")
+    l = np.arange(nlos)
+    for X, at in ((Q, l[0::2]), (U, l[1::2])):
+        X[at, at % nchan] = 1e5
+    c = make_small_cube(2, nchan, 3, seed=nchan)
+    phi = np.linspace(-40.0, 50.0, 21)
+    plan = rs.Plan(c["lambda2"], c["weights"], phi)
+    pick = np.unique(np.r_[0:min(nlos, 300), max(0, nlos - 300):nlos])
+    rq, ru = oracle.fdf(Q[pick].astype(np.float64), U[pick].astype(np.float64), c["lambda2"], c["weights"], phi)
+    if layout == FREQ_MAJOR:
+        Q, U = np.ascontiguousarray(Q.T), np.ascontiguousarray(U.T)
+    Fq, Fu, _ = plan.execute(dev32(Q), dev32(U), layout, rs.RMSYNTH_SPLIT_FP16)
+    assert np.max(oracle.per_los_error(host(Fq)[pick], host(Fu)[pick], rq, ru)) <= SCALE_TOL["fp16x3"]
+    plan.close()
+
+
 @pytest.mark.parametrize("prec", list(rs.PRECISIONS))
 @pytest.mark.parametrize("nlos,nchan,nphi", [(1, 3, 2), (31, 40, 31), (33, 255, 32), (64, 256, 33), (65, 257, 255),
                                              (63, 64, 256), (66, 100, 257), (40, 130, 513), (9000, 70, 300)])
