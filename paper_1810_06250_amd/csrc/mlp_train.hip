@@ -23,6 +23,7 @@
 // More than four weight fragments ahead (8: 25 us, 12: 30 us) spills registers.
 #include "mlp.h"
 #include "mlp_device.h"
+#include "mlp_frag.h"
 
 #include <algorithm>
 
@@ -47,7 +48,7 @@ struct Group {
 __device__ __forceinline__ void load_group(Group& g, const uint4* __restrict__ w, int s0, int ks)
 {
 #pragma unroll
-    for (int i = 0; i < TG; ++i) g.v[i] = w[(s0 + i < ks ? s0 + i : ks - 1) * 64];
+    for (int i = 0; i < TG; ++i) g.v[i] = w[frag_step(s0 + i, ks) * 64];
 }
 // acc += A (LDS rows a, 16 columns per step) x the fragments at w; g holds the
 // first TG of them.
@@ -109,7 +110,7 @@ __global__ __launch_bounds__(64 * TW, 1) void train_rows_kernel(RowsArgs p)
     const int n1 = 32 * wave + col, n2 = n1;  // this lane's hidden unit of each layer
     const int ks0 = p.nin_pad / 16, ks1 = p.h1 / 16, ks2 = p.h2 / 16;
     const uint4* const w1 = p.W1f + (int64_t)wave * ks0 * 64 + lane;
-    const uint4* const w2 = p.W2f + (int64_t)wave * ks1 * 64 + lane;
+    const uint4* const w2 = p.W2f + frag_column(wave, p.h2, ks1) + lane;
     const uint4* const wt = p.W2t + (int64_t)wave * ks2 * 64 + lane;
     const int64_t steps = 2 * p.nblk;  // 16-row steps of the batch
     const float bias1 = on1 ? p.b1[n1] : 0.0f, bias2 = on2 ? p.b2[n2] : 0.0f;
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(64 * TW, 1) void train_rows_kernel(RowsArgs p)
         uint32_t m1 = 0;
         if (on1) {
             z1 = layer(sx + col * LX + 8 * half, w1, ks0, g);
-            load_group(g, w2, 0, ks1);
+            load_group(g, w2, 0, ks1);  // (also without on2)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 f16x2_t h[2];
@@ -570,8 +571,9 @@ hipError_t mlp_launch_rows(const MlpTrainArgs& a, hipStream_t s)
     r.h2 = L.h2;
     r.w = a.chan_w;
     r.W1f = a.frag;
-    r.W2f = a.frag + L.nW1 / 8;
-    r.W2t = r.W2f + L.nW2 / 8;
+    const FragLayout f = frag_layout(L.nin_pad, L.h1, L.h2);
+    r.W2f = a.frag + f.w2;
+    r.W2t = a.frag + f.w2t;
     r.b1 = a.p + L.nW1;
     r.b2 = r.b1 + L.h1 + L.nW2;
     r.b3 = r.b2 + L.h2 + L.nW3;
