@@ -70,6 +70,13 @@ constexpr int64_t kSmallWaves = 512;  // see launch_mg
 
 enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2, FOLD = 3, TAB_ROW = 4, TAB_PLANE = 5, LOAD_TAIL = 6 };
 
+// Tiles of NW waves per workgroup.  Of workgroups of two waves the first two on a
+// CU share two of its SIMDs, so that calls which do not fill the chip take twice
+// the time (table form, 32768 LOS x 256 ch x 100 phi, FP32: 124 us, in
+// pairs 73).
+// The folded form is 3-5 % faster with tiles on their own where it takes them.
+constexpr int tiles_per_wg(int load, int nw) { return load == FOLD ? 1 : 4 / nw; }
+
 typedef const __attribute__((address_space(4))) f32x4_t* const_f4_ptr;
 typedef float f32x2u_t __attribute__((ext_vector_type(2), aligned(4)));
 typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
@@ -103,15 +110,15 @@ __device__ __forceinline__ f32x16_t mfma16(uint4 a, uint4 b, f32x16_t c)
 // frequency-major: K-steps of 8 channels, base holds (K w_j, 0).
 // FLAGS: some channel has weight 0; its (zero) rotation then also clears
 // whatever the data hold there, NaN included.
-// MG: LOS groups (of 32) per tile; NW: waves of 64 columns per workgroup (4; 2
-// only where a row's lanes need not follow the waves: FOLD, TAB_ROW).  The
-// results depend on neither.
+// MG: LOS groups (of 32) per tile; NW: waves of 64 columns per tile (4 or 2).
+// The results depend on neither.  tiles_per_wg: 128-column tiles of the table
+// form go in pairs, one below the other.
 // PEAKS 1: the epilogue also reduces |F|^2 of every LOS over each 64 phi and
 // writes one PeakPart per (LOS, 64 phi) for peak_merge_kernel, at
 // part[(64-phi block) * part_ld + LOS].  PEAKS 2: F is not stored; one PeakRec
 // each instead, for peak_merge_rec_kernel.
 template <int LOAD, int PREC, bool FLAGS, int PEAKS, int MG, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
+__global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mirrored_kernel(
     const float* __restrict__ Q, const float* __restrict__ U, int64_t nlos, int64_t ld, int nchan,
     const float2* __restrict__ base, const uint4* __restrict__ T, int nchan_pad, int nk, int nphi,
     int tiles_n, float* __restrict__ Fq, float* __restrict__ Fu, float* __restrict__ Fabs,
@@ -127,17 +134,19 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     constexpr bool COLS = LOAD == FOLD || TAB;
     constexpr bool OCT = LOAD == FOLD || LOAD == TAB_ROW;  // eight lanes share a row
     constexpr bool PLANE = LOAD == LOAD_PLANE || LOAD == TAB_PLANE;
-    static_assert(NW == 4 || OCT, "two waves: rows shared by eight lanes only");
+    static_assert(NW == 4 || (NW == 2 && COLS), "two waves: column forms only");
     constexpr int TILE = COLS ? 64 * NW : kMirrorTile;  // phi (output columns) per tile
     constexpr int SR = TILE + 4;     // row stride (floats) of the epilogue's tile: conflict-free b128 rows
     constexpr int MT = 32 * MG;      // LOS per tile
     constexpr int RT = 8 * NW, IT = OCT ? MT / RT : 2;  // OCT: rows per pass, passes
+    constexpr int PQ = 4 / NW;       // else: quads (TAB_PLANE: pairs) of channels per wave
     constexpr int STEP = 4 * MT * 2;  // uint4 of a packed K-step: [2 channel octets or quad pairs][4][MT]
     union Lds {
         uint4 a[3][STEP];
         float f[MT * SR];
     };
-    __shared__ Lds lds;
+    constexpr int SUB = tiles_per_wg(LOAD, NW);
+    __shared__ Lds lds_sub[SUB];
     // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
     // L2: groups of 8 LOS tiles, one per XCD, whose phi tiles then follow one
     // another on it (they read the same Q/U rows).  The whole chip so works on
@@ -145,14 +154,19 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     const uint32_t grp = blockIdx.x / (8u * tiles_n), in_grp = blockIdx.x - grp * (8u * tiles_n);
     const uint32_t mleft = gridDim.x / tiles_n - 8u * grp, wide = mleft < 8u ? mleft : 8u;
     const int tn = (int)(in_grp / wide);
-    const int64_t l0 = (int64_t)(8u * grp + in_grp % wide) * MT;
     const int n0 = tn * TILE;
-    const int t = threadIdx.x, lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int t = threadIdx.x & (64 * NW - 1), lane = t & 63;
+    const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = SUB == 1 ? wg_wave : wg_wave % NW, sub = SUB == 1 ? 0 : wg_wave / NW;  // wave of its tile, tile
+    Lds& lds = lds_sub[sub];
+    const int64_t l_tile = ((int64_t)(8u * grp + in_grp % wide) * SUB + sub) * MT;
+    // A tile that starts past the cube reads its last LOS and stores nothing.
+    const int64_t l0 = SUB == 1 || l_tile < nlos ? l_tile : nlos - 1;
+    const int nl = SUB == 1 || l_tile < nlos ? (int)(nlos - l0 < MT ? nlos - l0 : MT) : 0;  // LOS of the tile
     const int half = lane >> 5, col = lane & 31;
 
-    // Pack role: LOS `row` of the tile, channel quad `wave` of the K-step (so
-    // that the channel rotations are scalar loads; with 32 LOS both halves of
+    // Pack role: LOS `row` of the tile, channel quads PQ wave .. of the K-step
+    // (so that the channel rotations are scalar loads; with 32 LOS both halves of
     // the wave pack the same values).  Rows past the cube read
     // its last LOS; their outputs are never stored.  Channels past the end
     // read the last ones; their rotation is zero, and a non-finite value they
@@ -190,7 +204,7 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     struct Frag {
         uint4 v[4];
     };
-    f32x4_t rot[2];  // (cos, sin) K w_j of the quad to be packed next
+    f32x4_t rot[2 * PQ];  // (cos, sin) K w_j of the quads to be packed next
 
     // FOLD: K-tile and K-step within it of the current step, and of the K-step d
     // further on (at most one K-tile away, or clamped to the last; d is passed
@@ -254,8 +268,8 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
         }
         if constexpr (LOAD == TAB_PLANE) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int jw = 8 * k + 2 * wave + i, j = jw < nchan ? jw : nchan - 1;
+            for (int i = 0; i < 2 * PQ; ++i) {
+                const int jw = 8 * k + 2 * PQ * wave + i, j = jw < nchan ? jw : nchan - 1;
                 R.q[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Qt + (int64_t)j * ld) + voff);
                 R.u[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ut + (int64_t)j * ld) + voff);
             }
@@ -297,7 +311,8 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     auto load_rot = [&](int k) __attribute__((always_inline)) {
         if (OCT) return;
         if (LOAD == TAB_PLANE) {
-            rot[0] = bt[4 * k + wave];
+#pragma unroll
+            for (int p = 0; p < PQ; ++p) rot[p] = bt[4 * k + PQ * wave + p];
             return;
         }
         const int at = (k * KC + 4 * wave) >> 1;
@@ -315,7 +330,7 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     };
     // Rotate and pack the quad: FP32 as float4 x, y of quad `wave`; split as
     // the 8-byte half of the channel octet's x hi, x lo, y hi, y lo.
-    float px[2 * IT], py[2 * IT];
+    float px[OCT ? 2 * IT : 4 * PQ], py[OCT ? 2 * IT : 4 * PQ];
     auto rotate1 = [&](const Data& R, int i, int k, bool odd) __attribute__((always_inline)) {
         if constexpr (LOAD == FOLD) {
             // i < IT: S, D of row i as px = (Sx, Dy), py = (Sy, -Dx).  A pair of
@@ -340,10 +355,10 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
             return;
         }
         if constexpr (TAB) {
-            // TAB_ROW: row i < IT; TAB_PLANE: channel i < 2 of the wave's pair.
+            // TAB_ROW: row i < IT; TAB_PLANE: channel i of the wave's pairs.
             // px = (x, y), py = (y, -x).
-            if (i >= IT) return;
-            const float w = LOAD == TAB_ROW ? R.w : i ? rot[0].z : rot[0].x;
+            if (i >= (OCT ? IT : 2 * PQ)) return;
+            const float w = LOAD == TAB_ROW ? R.w : (i & 1) ? rot[i >> 1].z : rot[i >> 1].x;
             float x = R.q[i] * w, y = R.u[i] * w;
             if (FLAGS) {
                 x = w == 0.0f ? 0.0f : x;
@@ -379,21 +394,27 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
     auto store_data = [&](int buf) __attribute__((always_inline)) {
         if constexpr (LOAD == TAB_PLANE) {
             // As below, two channels: 8 bytes each.
-            uint2* const a = reinterpret_cast<uint2*>(&lds.a[buf][(wave >> 1) * (4 * MT) + row]) + (wave & 1);
-            uint2 w[4];
-            if (F32) {
-                w[0] = make_uint2(__float_as_uint(px[0]), __float_as_uint(px[2]));
-                w[1] = make_uint2(__float_as_uint(px[1]), __float_as_uint(px[3]));
-                w[2] = make_uint2(__float_as_uint(py[0]), __float_as_uint(py[2]));
-                w[3] = make_uint2(__float_as_uint(py[1]), __float_as_uint(py[3]));
-            } else {
-                split2<PREC>(px[0], px[1], w[0].x, w[1].x);
-                split2<PREC>(px[2], px[3], w[0].y, w[1].y);
-                split2<PREC>(py[0], py[1], w[2].x, w[3].x);
-                split2<PREC>(py[2], py[3], w[2].y, w[3].y);
-            }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) a[2 * MT * e] = w[e];
+            for (int p = 0; p < PQ; ++p) {
+                const int at = PQ * wave + p;
+                const float* const x = px + 4 * p;
+                const float* const y = py + 4 * p;
+                uint2* const a = reinterpret_cast<uint2*>(&lds.a[buf][(at >> 1) * (4 * MT) + row]) + (at & 1);
+                uint2 w[4];
+                if (F32) {
+                    w[0] = make_uint2(__float_as_uint(x[0]), __float_as_uint(x[2]));
+                    w[1] = make_uint2(__float_as_uint(x[1]), __float_as_uint(x[3]));
+                    w[2] = make_uint2(__float_as_uint(y[0]), __float_as_uint(y[2]));
+                    w[3] = make_uint2(__float_as_uint(y[1]), __float_as_uint(y[3]));
+                } else {
+                    split2<PREC>(x[0], x[1], w[0].x, w[1].x);
+                    split2<PREC>(x[2], x[3], w[0].y, w[1].y);
+                    split2<PREC>(y[0], y[1], w[2].x, w[3].x);
+                    split2<PREC>(y[2], y[3], w[2].y, w[3].y);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[2 * MT * e] = w[e];
+            }
             return;
         }
         if constexpr (OCT) {
@@ -670,7 +691,6 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
             }
     };
     if constexpr (PEAKS != 2) {
-        const int nl = (int)(nlos - l0 < MT ? nlos - l0 : MT);
         constexpr int LR = TILE / 4, RW = 64 / LR;  // lanes per row, rows per wave and pass
         const int lc = 4 * (lane % LR), r0 = RW * wave + lane / LR;
         const int n4 = nphi - n0 - lc;  // phi left at this lane's first column
@@ -745,7 +765,7 @@ __global__ __launch_bounds__(64 * NW, 2) void synth_mirrored_kernel(
         }
         const int64_t l = l0 + lane;
         const int blk = TILE / 64 * tn + wave;
-        const bool mine = lane < MT && l < nlos && 64 * blk < nphi;
+        const bool mine = lane < nl && 64 * blk < nphi;
         const int idx = bad ? -2 : 64 * blk + bk;
         if constexpr (PEAKS == 1) {
             if (mine) part[blk * part_ld + l] = PeakPart{best, idx};
@@ -921,12 +941,13 @@ hipError_t launch(const rmsynth_plan_s& p, const ExecArgs& a)
     // Folded: K-tiles of ksteps K-steps, kpad channels below channel 0.
     const int nk = LOAD == FOLD ? (p.nchan + p.kpad) / KC : (p.nchan + kc - 1) / kc;
     const int tiles_n = LOAD == FOLD || tab ? (p.nphi + 64 * NW - 1) / (64 * NW) : p.ftiles;
-    const int64_t blocks = (a.nlos + 32 * MG - 1) / (32 * MG) * tiles_n;
+    constexpr int sub = tiles_per_wg(LOAD, NW), rows = 32 * MG * sub;  // LOS per workgroup
+    const int64_t blocks = (a.nlos + rows - 1) / rows * tiles_n;
     if (blocks <= 0) return hipSuccess;
     const uint4* T = PREC == RMSYNTH_FP32 ? p.d_Tf32 : PREC == RMSYNTH_SPLIT_FP16 ? p.d_Thf : p.d_Tbf;
 #define RMS_LAUNCH(G, P)                                                                                    \
     hipLaunchKernelGGL((synth_mirrored_kernel<LOAD, PREC, G, P, MG, NW>), dim3((unsigned)blocks),            \
-                       dim3(64 * NW), 0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_base, T, p.nchan_pad, \
+                       dim3(64 * NW * sub), 0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_base, T, p.nchan_pad, \
                        nk, p.nphi, tiles_n, a.Fq, a.Fu, a.Fabs, a.los_scale, a.peak_part, a.peak_part_ld,     \
                        a.peak_rec, 4 * p.nphi_pad, p.ksteps, p.kpad, p.d_kbase, p.d_krot)
 #define RMS_LAUNCH_P(G)                                                               \
@@ -962,18 +983,31 @@ hipError_t launch_mg(const rmsynth_plan_s& p, const ExecArgs& a)
     return waves <= kSmallWaves ? launch<LOAD, PREC, 1, NW>(p, a) : launch<LOAD, PREC, 2, NW>(p, a);
 }
 
-// Output columns come in tiles of 256, or of 128 (two waves) where that pads
-// fewer: what the matrix cores bound (FP32, the table form) gains what is not
-// padded (262144 LOS x 1201 phi -> 288 channels FP32 5.01 -> 3.93 ms; 131072 x
-// 400 -> 300 phi bf16x3 table 0.52 -> 0.48).  The folded split forms read the
-// rows once per tile and are bound by that: one narrow tile gains (1201 -> 100
-// channels bf16x3 1.14 -> 1.09 ms, 0.90 since), three instead of two wide ones
-// lose (288 channels 1.96 -> 2.24, then; wide 1.87 now).
+// Output columns come in tiles of 256, or of 128 where that pads fewer.  A narrow
+// tile packs its rows for half the matrix work, so what the matrix cores bound
+// gains less than what is not padded.
 template <int LOAD, int PREC>
 hipError_t launch_cols(const rmsynth_plan_s& p, const ExecArgs& a)
 {
-    const bool fewer = (p.nphi + 127) / 128 * 128 < (p.nphi + 255) / 256 * 256;
-    const bool narrow = fewer && (LOAD == TAB_ROW || PREC == RMSYNTH_FP32 || p.nphi <= 128);
+    const int64_t n128 = (p.nphi + 127) / 128, n256 = (p.nphi + 255) / 256, tiles = (a.nlos + 63) / 64;
+    bool narrow = n128 < 2 * n256;
+    if constexpr (LOAD == FOLD) {
+        // One narrow tile gains (262144 LOS x 1201 -> 100 channels bf16x3 1.14 ->
+        // 1.09 ms).  The split forms read the rows once per tile and are bound by
+        // that: three instead of two wide ones lose (288 channels 1.96 -> 2.24).
+        // FP32 gains (1201 -> 288 channels 5.01 -> 3.93 ms) once there are
+        // workgroups for every SIMD (500 -> 300 channels: 4096 LOS 42 us wide, 70
+        // narrow, 16384 137 and 138, 65536 532 and 422).
+        narrow = narrow && (p.nphi <= 128 || (PREC == RMSYNTH_FP32 && tiles * n128 >= 1024));
+    } else {
+        // The time of a workgroup times the most that a CU is given of them, in
+        // units of a half-height one (launch_mg); narrow ones take 17/16 (FP32) or
+        // 19/16 (split) of a wide one's.  256 channels x 300 phi, wide and narrow:
+        // 8192 LOS bf16x3 24 and 26 us, FP32 68 and 71; 65536 LOS 163 and 148,
+        // 511 and 396; 880 phi bf16x3 342 and 346.
+        auto rounds = [](int64_t full) { return full <= 128 ? 1 : 2 * ((full + 255) / 256); };
+        narrow = narrow && (PREC == RMSYNTH_FP32 ? 17 : 19) * rounds((tiles + 1) / 2 * n128) < 16 * rounds(tiles * n256);
+    }
     return narrow ? launch_mg<LOAD, PREC, 2>(p, a) : launch_mg<LOAD, PREC, 4>(p, a);
 }
 
@@ -982,7 +1016,7 @@ hipError_t launch_load(const rmsynth_plan_s& p, const ExecArgs& a)
 {
     const bool planes = a.layout != RMSYNTH_LOS_MAJOR;
     if (p.cuniform) return launch_cols<FOLD, PREC>(p, a);
-    if (p.etab) return planes ? launch_mg<TAB_PLANE, PREC, 4>(p, a) : launch_cols<TAB_ROW, PREC>(p, a);
+    if (p.etab) return planes ? launch_cols<TAB_PLANE, PREC>(p, a) : launch_cols<TAB_ROW, PREC>(p, a);
     if (planes) return launch_mg<LOAD_PLANE, PREC, 4>(p, a);
     // Quads of any alignment: with single values, 10007 LOS x 333 ch x 777 phi took
     // 80 us in bf16x3 (now 60) and 165 in FP32 (145), 65536 LOS 405 (297) and 819
