@@ -20,11 +20,12 @@
 // input per butterfly and copy it to its 2^B1 outputs, so the next pass reads
 // its inputs straight from the short grid.
 //
-// T = n / 8 threads (16 to 512) per LOS, several LOS per workgroup of up to
-// 256 threads where T is less.  The channels' c_j go to LDS; each thread sums
+// T = n / 8 threads (16 to 512) per LOS, or one per point on small grids with many
+// channels; several LOS per workgroup of up to 256 threads where T is less.  The channels' c_j go to LDS; each thread sums
 // grid points from their lists of entries (a fixed order, no atomics; the
 // entries of 64 neighbouring points are interleaved, so that a wave reads
-// them contiguously).  The FFT runs as Stockham passes of radix 8 or 16 in
+// them contiguously, the first of each block of points a block ahead: 32768 LOS x
+// 64 ch x 1500 phi 335 -> 264 us).  The FFT runs as Stockham passes of radix 8 or 16 in
 // registers, three for n / 2^B1 up to 4096, through LDS; the last one scales
 // its modes and stores them.
 //
@@ -129,13 +130,16 @@ __device__ __forceinline__ int swz(int i) { return i ^ ((i >> 4) & 31); }
 
 // Radices (log2) of the passes over the 2^M points that are left after the
 // copying first one: at most 4, as radix 32 takes too many registers for
-// enough waves (4096 points as 8 x 16 x 32: 3.9 ms on the case above).
+// enough waves (4096 points as 8 x 16 x 32: 3.9 ms on the case above).  2048 points
+// end with radix 8, one butterfly per thread where the modes are stored (32768 LOS
+// x 64 ch x 600 phi: 133 us as 8 x 16 x 16, 123 as 16 x 16 x 8).
 template <int M>
 struct Radices {
     static constexpr int count = M <= 4 ? 1 : M <= 8 ? 2 : M <= 12 ? 3 : 4;
     static constexpr int log2r(int i)
     {
         return count == 1 ? M : count == 2 ? (i == 0 ? M / 2 : M - M / 2)
+               : M == 11 ? (i < 2 ? 4 : 3)
                : count == 3 ? (i == 0 ? M / 3 : i == 1 ? (M - M / 3) / 2 : M - M / 3 - (M - M / 3) / 2)
                             : (i < 3 ? 3 : M - 9);
     }
@@ -231,6 +235,10 @@ constexpr int threads_per_los(int logn)
     return logn >= 12 ? 512 : logn <= 7 ? 16 : 1 << (logn - 3);
 }
 
+// Threads of a LOS with many channels on a small grid: one per point.  Its c_j
+// leave little LDS for other LOS, and the lists take longer than the FFT.
+constexpr int most_threads(int logn) { return logn >= 5 && logn <= 8 ? 1 << logn : threads_per_los(logn); }
+
 // Threads that share a grid point's list.
 constexpr int grid_parts(int logn, int b1)
 {
@@ -245,14 +253,14 @@ inline int64_t lds_points(int logn, int b1, int nchan)
     return b1 ? std::max<int64_t>(n, nchan) + (n >> b1) * grid_parts(logn, b1) : n + nchan;
 }
 
-template <int LOGN, int B1>
-__global__ __launch_bounds__(std::max(kThreads, threads_per_los(LOGN))) void nufft_kernel(
+template <int LOGN, int B1, int T>
+__global__ __launch_bounds__(std::max(kThreads, T)) void nufft_kernel(
     const float* __restrict__ Q, const float* __restrict__ U, int64_t nlos, int nchan,
     const float2* __restrict__ rot, const int2* __restrict__ blk, const int2* __restrict__ ent,
     const float2* __restrict__ tw, const float2* __restrict__ deconv, int N, int kc, int per_los,
     float* __restrict__ Fq, float* __restrict__ Fu, float* __restrict__ Fabs)
 {
-    constexpr int n = 1 << LOGN, T = threads_per_los(LOGN), M = n >> B1;
+    constexpr int n = 1 << LOGN, M = n >> B1;
     extern __shared__ float4 smem4[];
     const int t = threadIdx.x & (T - 1);
     // The LOS of the workgroup that this thread works on, the same over a wave
@@ -266,49 +274,76 @@ __global__ __launch_bounds__(std::max(kThreads, threads_per_los(LOGN))) void nuf
     float2* const cb = B1 ? grid : grid + n;
     float2* const g = B1 ? grid + (per_los - M * grid_parts(LOGN, B1)) : grid;
 
+    // Block p / 64 of grid points: its first entry and the entries per point (lists
+    // shorter than the block's longest end in entries of weight 0; a multiple
+    // of S).  S threads share a point's list where there are fewer points than
+    // threads.  A thread's points are in NP blocks, the same ones over a wave.
+    constexpr int S = grid_parts(LOGN, B1), NP = S == 1 ? (M + T - 1) / T : 1;
+    static_assert(S == 1 || (B1 == 6 && kNufftListPad % S == 0), "whole shares of a list");
+    const int wave = T > 64 ? __builtin_amdgcn_readfirstlane(t >> 6) : 0;
+    int2 b[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int at = S == 1 ? (T * i >> 6) + wave : wave & ((M - 1) >> 6);
+        b[i] = blk[M % T == 0 || at < (M + 63) / 64 ? at : 0];
+    }
+    // The first entries of a block are loaded a block ahead.
+    constexpr int PRE = 4;
+    int2 pre[PRE];
+    auto load_first = [&](int i) __attribute__((always_inline)) {
+        const int2* const e = ent + b[i].x + ((t + T * i) & 63);
+#pragma unroll
+        for (int q = 0; q < PRE; ++q)
+            if (q < b[i].y) pre[q] = e[64 * q];
+    };
+    if (S == 1) load_first(0);
+
     // c_j = rot_j (Q_j + i U_j); flagged channels are in no gridding list.
     const float* q = Q + lr * nchan;
     const float* u = U + lr * nchan;
     for (int j = t; j < nchan; j += T) cb[j] = cmul(rot[j], make_float2(q[j], u[j]));
     __syncthreads();
     // Gridding: g_p = sum over the channels within reach of p of psi_jp c_j.
-    // Block p / 64 of points: its first entry and the entries per point (lists
-    // shorter than the block's longest end in entries of weight 0; a multiple
-    // of S).  S threads share a point's list where there are fewer points than
-    // threads.
-    constexpr int S = grid_parts(LOGN, B1);
-    static_assert(S == 1 || (B1 == 6 && kNufftListPad % S == 0), "whole shares of a list");
-    auto sum_entries = [&](const int2* e, int count) __attribute__((always_inline)) {
-        float2 acc = make_float2(0.0f, 0.0f);
-        auto add = [&](int2 en) __attribute__((always_inline)) {
-            const float w = __int_as_float(en.y);
-            const float2 c = cb[en.x];
-            acc.x = __builtin_fmaf(w, c.x, acc.x);
-            acc.y = __builtin_fmaf(w, c.y, acc.y);
-        };
+    auto add = [&](float2& acc, int2 en) __attribute__((always_inline)) {
+        const float w = __int_as_float(en.y);
+        const float2 c = cb[en.x];
+        acc.x = __builtin_fmaf(w, c.x, acc.x);
+        acc.y = __builtin_fmaf(w, c.y, acc.y);
+    };
+    auto sum_entries = [&](float2 acc, const int2* e, int count) __attribute__((always_inline)) {
         int i = 0;
         for (; i + 4 <= count; i += 4) {
             const int2 e0 = e[64 * i], e1 = e[64 * i + 64], e2 = e[64 * i + 128], e3 = e[64 * i + 192];
-            add(e0);
-            add(e1);
-            add(e2);
-            add(e3);
+            add(acc, e0);
+            add(acc, e1);
+            add(acc, e2);
+            add(acc, e3);
         }
-        for (; i < count; ++i) add(e[64 * i]);
+        for (; i < count; ++i) add(acc, e[64 * i]);
         return acc;
     };
     if constexpr (S == 1) {
-        for (int p = t; p < M; p += T) {
-            const int2 b = blk[p >> 6];
-            const float2 acc = sum_entries(ent + b.x + (p & 63), b.y);
-            if (B1) g[p] = acc;
-            else g[swz(p)] = acc;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            int2 cur[PRE];
+#pragma unroll
+            for (int q = 0; q < PRE; ++q) cur[q] = pre[q];
+            if (i + 1 < NP) load_first(i + 1);
+            float2 acc = make_float2(0.0f, 0.0f);
+#pragma unroll
+            for (int q = 0; q < PRE; ++q)
+                if (q < b[i].y) add(acc, cur[q]);
+            const int p = t + T * i;
+            if (b[i].y > PRE) acc = sum_entries(acc, ent + b[i].x + 64 * PRE + (p & 63), b[i].y - PRE);
+            if (M % T == 0 || p < M) {
+                if (B1) g[p] = acc;
+                else g[swz(p)] = acc;
+            }
         }
     } else {
         const int p = t & (M - 1), part = t / M;
-        const int2 b = blk[p >> 6];
-        const int each = b.y / S;
-        g[t] = sum_entries(ent + b.x + 64 * each * part + (p & 63), each);
+        const int each = b[0].y / S;
+        g[t] = sum_entries(make_float2(0.0f, 0.0f), ent + b[0].x + 64 * each * part + (p & 63), each);
         __syncthreads();
         if (t < M) {
             float2 acc = g[t];
@@ -389,11 +424,18 @@ hipError_t launch_nufft(const rmsynth_plan_s& p, const float* Q, const float* U,
                         float* Fq, float* Fu, float* Fabs, hipStream_t s)
 {
     const int logn = log2_of(p.nufft_n);
-    const int T = threads_per_los(logn);
     const size_t each = nufft_lds_bytes(p);
     // LOS per workgroup: 256 threads' worth, within 40 KB of LDS (four
     // workgroups on a CU) unless one LOS alone takes more.
-    const int64_t per = std::min<int64_t>(std::max(1, kThreads / T), std::max<int64_t>(1, (int64_t)(40960 / each)));
+    const int64_t fit = std::max<int64_t>(1, (int64_t)(40960 / each));
+    // Before and after, 32768 LOS of a band over half the circle: 64 phi (128 points),
+    // 200 channels 82 -> 79 us, 800 434 -> 237, 4096 7620 -> 1535; fewer channels
+    // lose (128: 51 -> 60).  128 phi, 400 138 -> 127 (300: 96 -> 105), 3000 2185 ->
+    // 785; 32 phi, 300 107 -> 88 (200: 61 -> 65).  Larger grids fill the lanes as
+    // they are.
+    const bool many = p.nchan >= std::max(3 << logn >> 1, logn < 7 ? 256 : 0);
+    const int T = many ? most_threads(logn) : threads_per_los(logn);
+    const int64_t per = std::min<int64_t>(std::max(1, kThreads / T), fit);
     const int64_t max_los = max_items(per, per * T);
     for (int64_t l0 = 0; l0 < nlos;) {
         const int64_t n = std::min<int64_t>(nlos - l0, max_los);
@@ -402,11 +444,16 @@ hipError_t launch_nufft(const rmsynth_plan_s& p, const float* Q, const float* U,
         float* fq = Fq + l0 * p.nphi;
         float* fu = Fu + l0 * p.nphi;
         float* fa = Fabs ? Fabs + l0 * p.nphi : nullptr;
-#define RMS_NUFFT(L, B)                                                                               \
-    hipLaunchKernelGGL((nufft_kernel<L, B>), dim3((unsigned)((n + per - 1) / per)),                     \
+#define RMS_NUFFT_T(L, B, TT)                                                                         \
+    hipLaunchKernelGGL((nufft_kernel<L, B, TT>), dim3((unsigned)((n + per - 1) / per)),                     \
                        dim3((unsigned)(per * T)), (size_t)per * each, s, q, u, n, p.nchan, p.d_nufft_rot,  \
                        p.d_nufft_blk, p.d_nufft_ent, p.d_nufft_tw, p.d_nufft_deconv, p.nphi, p.nufft_kc,   \
                        (int)(each / sizeof(float2)), fq, fu, fa)
+#define RMS_NUFFT(L, B)                                                \
+    do {                                                               \
+        if (T > threads_per_los(L)) RMS_NUFFT_T(L, B, most_threads(L)); \
+        else RMS_NUFFT_T(L, B, threads_per_los(L));                    \
+    } while (0)
 #define RMS_NUFFT_3(L)                      \
     do {                                    \
         if (p.nufft_b1 == 3) RMS_NUFFT(L, 3); \
@@ -433,6 +480,7 @@ hipError_t launch_nufft(const rmsynth_plan_s& p, const float* Q, const float* U,
 #undef RMS_NUFFT_6
 #undef RMS_NUFFT_3
 #undef RMS_NUFFT
+#undef RMS_NUFFT_T
         if (hipError_t e = hipGetLastError()) return e;
         l0 += n;
     }
