@@ -81,7 +81,7 @@ hipError_t alloc_tables(rmsynth_plan_s* p, size_t n)
 
 int build_mirror_tables(rmsynth_plan_s* p)
 {
-    p->ftiles = (int32_t)((p->nphi + kMirrorTile - 1) / kMirrorTile);
+    p->ftiles = (int32_t)((p->nphi + mirror_tile(*p) - 1) / mirror_tile(*p));
     const size_t nT = (size_t)((p->nchan + kMirrorChan - 1) / kMirrorChan) * 1024;
     hipError_t e;
     if ((e = hipMalloc(&p->d_base, sizeof(float2) * (size_t)p->ftiles * p->nchan_pad)) != hipSuccess ||

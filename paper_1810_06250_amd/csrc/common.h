@@ -35,7 +35,7 @@ struct rmsynth_plan_s {
     float* d_w;
     double* d_phi;
     // Mirrored-pair tables (synth_mirrored.hip), present when the phi grid is
-    // uniform (phi_k = phi_0 + k dphi), in tiles of kMirrorTile phi:
+    // uniform (phi_k = phi_0 + k dphi), in tiles of mirror_tile() phi:
     //   d_base [ftiles][nchan_pad] float2  K w_j (cos, sin)(2 a_j phi_c), phi_c the tile's centre
     //   d_T{bf,hf,f32} [K-steps][4][4][64] uint4: (cos, sin)(2 a_j (i + 1/2) dphi) of 16
     //                   channels x 128 pairs in MFMA operand order, split into 16-bit
@@ -88,7 +88,9 @@ size_t nufft_lds_bytes(const rmsynth_plan_s& p);
 hipError_t launch_nufft(const rmsynth_plan_s& p, const float* Q, const float* U, int64_t nlos,
                         float* Fq, float* Fu, float* Fabs, hipStream_t s);
 
-constexpr int kMirrorTile = 256;  // phi per tile of the mirrored-pair kernels
+constexpr int kMirrorTile = 256;  // most phi per tile of the mirrored-pair kernels
+// Phi per tile: half for the grids that fit.
+inline int mirror_tile(const rmsynth_plan_s& p) { return p.nphi <= kMirrorTile / 2 ? kMirrorTile / 2 : kMirrorTile; }
 constexpr int kMirrorChan = 16;   // channels per K-step of the mirrored-pair kernels
 constexpr int kFoldTile = 256;    // most channels per K-tile of the folded form
 constexpr size_t kEtabMaxBytes = size_t(256) << 20;  // largest phase table, both split forms

@@ -65,10 +65,9 @@
 namespace {
 
 constexpr int KC = kMirrorChan;      // channels per K-step
-constexpr int NH = kMirrorTile / 2;  // pairs per tile
 constexpr int64_t kSmallWaves = 512;  // see launch_mg
 
-enum { LOAD_ROW4 = 0, LOAD_ROW = 1, LOAD_PLANE = 2, FOLD = 3, TAB_ROW = 4, TAB_PLANE = 5, LOAD_TAIL = 6 };
+enum { LOAD_ROW4 = 0, LOAD_TAIL = 1, LOAD_ONE = 2, FOLD = 3, TAB_ROW = 4, TAB_PLANE = 5 };
 
 // Tiles of NW waves per workgroup.  Of workgroups of two waves the first two on a
 // CU share two of its SIMDs, so that calls which do not fill the chip take twice
@@ -100,8 +99,9 @@ __device__ __forceinline__ f32x16_t mfma16(uint4 a, uint4 b, f32x16_t c)
 }
 
 // LOAD: how Q/U are read.  ROW4: LOS-major rows, 4 n channels, as quads of any
-// alignment; TAIL: the same for the other channel counts above 4; ROW:
-// LOS-major, single values; PLANE: frequency-major.
+// alignment; TAIL: the same for the other channel counts above 4; ONE: single
+// values, frequency-major (ls = 1) and LOS-major below 4 channels (ls = ld, and
+// ld 1).  nh: pairs of depths per tile, at most 32 NW; waves past it only pack.
 // FOLD: the folded form (LOS-major, any alignment; no flags, no peaks): T is its
 // table, nk the K-steps of all K-tiles, ksteps those of one, pad the zero
 // channels below channel 0, kbase and krot the K exp(-2 pi i b_0' g) and
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
     int tiles_n, float* __restrict__ Fq, float* __restrict__ Fu, float* __restrict__ Fabs,
     const float* __restrict__ los_scale, PeakPart* __restrict__ part, int64_t part_ld,
     PeakRec* __restrict__ rec, int ldT, int ksteps, int pad, const float2* __restrict__ kbase,
-    const float2* __restrict__ krot)
+    const float2* __restrict__ krot, int ls, int nh)
 {
     static_assert(LOAD != FOLD || (PEAKS == 0 && !FLAGS), "the folded form has no peaks and no flags");
     constexpr bool F32 = PREC == RMSYNTH_FP32;
@@ -133,9 +133,9 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
     // contract 8 pairs or channels, as (cos, sin) neighbours.
     constexpr bool COLS = LOAD == FOLD || TAB;
     constexpr bool OCT = LOAD == FOLD || LOAD == TAB_ROW;  // eight lanes share a row
-    constexpr bool PLANE = LOAD == LOAD_PLANE || LOAD == TAB_PLANE;
-    static_assert(NW == 4 || (NW == 2 && COLS), "two waves: column forms only");
-    constexpr int TILE = COLS ? 64 * NW : kMirrorTile;  // phi (output columns) per tile
+    constexpr bool ONE = LOAD == LOAD_ONE;
+    static_assert(NW == 4 || NW == 2, "tiles of four or two waves");
+    constexpr int TILE = 64 * NW;    // phi (output columns) per tile
     constexpr int SR = TILE + 4;     // row stride (floats) of the epilogue's tile: conflict-free b128 rows
     constexpr int MT = 32 * MG;      // LOS per tile
     constexpr int RT = 8 * NW, IT = OCT ? MT / RT : 2;  // OCT: rows per pass, passes
@@ -176,9 +176,10 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
     const int64_t left = nlos - 1 - l0;
     const int lr = row < left ? row : (int)left;
     const float lsc = PREC == RMSYNTH_SPLIT_FP16 ? los_scale[l0 + lr] : 1.0f;
-    const uint32_t voff = 4u * (PLANE ? (uint32_t)lr : (uint32_t)(lr * (int)ld));  // < 2^24
-    const float* const Qt = PLANE ? Q + l0 : Q + l0 * ld;
-    const float* const Ut = PLANE ? U + l0 : U + l0 * ld;
+    const int64_t lstride = LOAD == TAB_PLANE ? 1 : ONE ? ls : ld;
+    const uint32_t voff = 4u * (uint32_t)(lr * (int)lstride);  // < 2^24
+    const float* const Qt = Q + l0 * lstride;
+    const float* const Ut = U + l0 * lstride;
     const_f4_ptr bt = (const_f4_ptr)(TAB ? base : base + (int64_t)tn * nchan_pad);
     // OCT: eight lanes share a LOS row, lane cc the pair or channel cc of the
     // K-step, rows rq + RT i: a wave's load covers 8 rows x 32 contiguous bytes.
@@ -275,20 +276,25 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
             }
             return;
         }
-        const int j0 = k * KC + 4 * wave;
-        if (LOAD == LOAD_ROW4 || LOAD == LOAD_TAIL) {
-            const int j = j0 < nchan - 4 ? j0 : nchan - 4;
-            const f32x4u_t a = *reinterpret_cast<const f32x4u_t*>(reinterpret_cast<const char*>(Qt + j) + voff);
-            const f32x4u_t b = *reinterpret_cast<const f32x4u_t*>(reinterpret_cast<const char*>(Ut + j) + voff);
-            R.q[0] = a.x; R.q[1] = a.y; R.q[2] = a.z; R.q[3] = a.w;
-            R.u[0] = b.x; R.u[1] = b.y; R.u[2] = b.z; R.u[3] = b.w;
-        } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int j = j0 + i < nchan ? j0 + i : nchan - 1;
-                const int64_t at = LOAD == LOAD_PLANE ? (int64_t)j * ld : (int64_t)j;
-                R.q[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Qt + at) + voff);
-                R.u[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ut + at) + voff);
+        for (int p = 0; p < PQ; ++p) {
+            const int j0 = k * KC + 4 * (PQ * wave + p);
+            float* const q = R.q + 4 * p;
+            float* const u = R.u + 4 * p;
+            if (LOAD == LOAD_ROW4 || LOAD == LOAD_TAIL) {
+                const int j = j0 < nchan - 4 ? j0 : nchan - 4;
+                const f32x4u_t a = *reinterpret_cast<const f32x4u_t*>(reinterpret_cast<const char*>(Qt + j) + voff);
+                const f32x4u_t b = *reinterpret_cast<const f32x4u_t*>(reinterpret_cast<const char*>(Ut + j) + voff);
+                q[0] = a.x; q[1] = a.y; q[2] = a.z; q[3] = a.w;
+                u[0] = b.x; u[1] = b.y; u[2] = b.z; u[3] = b.w;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int j = j0 + i < nchan ? j0 + i : nchan - 1;
+                    const int64_t at = (int64_t)j * ld;
+                    q[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Qt + at) + voff);
+                    u[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ut + at) + voff);
+                }
             }
         }
     };
@@ -296,16 +302,19 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
     // go to the front (what follows them meets a zero rotation).
     auto align_tail = [&](Data& R, int k) __attribute__((always_inline)) {
         if constexpr (LOAD == LOAD_TAIL) {
-            const int past = k * KC + 4 * wave + 4 - nchan;
-            if (past <= 0) return;
-            auto shift = [&](float* v) __attribute__((always_inline)) {
-                const float v1 = v[1], v2 = v[2], v3 = v[3];
-                v[0] = past == 1 ? v1 : past == 2 ? v2 : v3;
-                v[1] = past == 1 ? v2 : v3;
-                v[2] = v3;
-            };
-            shift(R.q);
-            shift(R.u);
+#pragma unroll
+            for (int p = 0; p < PQ; ++p) {
+                const int past = k * KC + 4 * (PQ * wave + p) + 4 - nchan;
+                if (past <= 0) continue;
+                auto shift = [&](float* v) __attribute__((always_inline)) {
+                    const float v1 = v[1], v2 = v[2], v3 = v[3];
+                    v[0] = past == 1 ? v1 : past == 2 ? v2 : v3;
+                    v[1] = past == 1 ? v2 : v3;
+                    v[2] = v3;
+                };
+                shift(R.q + 4 * p);
+                shift(R.u + 4 * p);
+            }
         }
     };
     auto load_rot = [&](int k) __attribute__((always_inline)) {
@@ -315,9 +324,9 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
             for (int p = 0; p < PQ; ++p) rot[p] = bt[4 * k + PQ * wave + p];
             return;
         }
-        const int at = (k * KC + 4 * wave) >> 1;
-        rot[0] = bt[at];
-        rot[1] = bt[at + 1];
+        const int at = (k * KC + 4 * PQ * wave) >> 1;
+#pragma unroll
+        for (int i = 0; i < 2 * PQ; ++i) rot[i] = bt[at + i];
     };
     auto load_b = [&](Frag& B, int k) __attribute__((always_inline)) {
         if constexpr (LOAD == FOLD) {
@@ -439,23 +448,29 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
             }
             return;
         }
-        if (F32) {
-            // [quad pair][x, y][quad of the pair][row]
-            uint4* const a = &lds.a[buf][(wave >> 1) * (4 * MT) + (wave & 1) * MT + row];
-            a[0] = __builtin_bit_cast(uint4, f32x4_t{px[0], px[1], px[2], px[3]});
-            a[2 * MT] = __builtin_bit_cast(uint4, f32x4_t{py[0], py[1], py[2], py[3]});
-        } else {
-            uint2 xh, xl, yh, yl;
-            split2<PREC>(px[0], px[1], xh.x, xl.x);
-            split2<PREC>(px[2], px[3], xh.y, xl.y);
-            split2<PREC>(py[0], py[1], yh.x, yl.x);
-            split2<PREC>(py[2], py[3], yh.y, yl.y);
-            // [octet][x hi, x lo, y hi, y lo][row], 8-byte halves
-            uint2* const a = reinterpret_cast<uint2*>(&lds.a[buf][(wave >> 1) * (4 * MT) + row]) + (wave & 1);
-            a[0] = xh;
-            a[2 * MT] = xl;
-            a[4 * MT] = yh;
-            a[6 * MT] = yl;
+#pragma unroll
+        for (int p = 0; p < PQ; ++p) {
+            const int at = PQ * wave + p;
+            const float* const x = px + 4 * p;
+            const float* const y = py + 4 * p;
+            if (F32) {
+                // [quad pair][x, y][quad of the pair][row]
+                uint4* const a = &lds.a[buf][(at >> 1) * (4 * MT) + (at & 1) * MT + row];
+                a[0] = __builtin_bit_cast(uint4, f32x4_t{x[0], x[1], x[2], x[3]});
+                a[2 * MT] = __builtin_bit_cast(uint4, f32x4_t{y[0], y[1], y[2], y[3]});
+            } else {
+                uint2 xh, xl, yh, yl;
+                split2<PREC>(x[0], x[1], xh.x, xl.x);
+                split2<PREC>(x[2], x[3], xh.y, xl.y);
+                split2<PREC>(y[0], y[1], yh.x, yl.x);
+                split2<PREC>(y[2], y[3], yh.y, yl.y);
+                // [octet][x hi, x lo, y hi, y lo][row], 8-byte halves
+                uint2* const a = reinterpret_cast<uint2*>(&lds.a[buf][(at >> 1) * (4 * MT) + row]) + (at & 1);
+                a[0] = xh;
+                a[2 * MT] = xl;
+                a[4 * MT] = yh;
+                a[6 * MT] = yl;
+            }
         }
     };
     auto load_a = [&](Frag& A, int buf, int g) __attribute__((always_inline)) {
@@ -564,7 +579,7 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
         __builtin_amdgcn_sched_barrier(0);
         mma(A0, B, 0, [] {});
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rotate1(R, i, next(k, 2), odd);
+        for (int i = 0; i < 4 * PQ; ++i) rotate1(R, i, next(k, 2), odd);
         store_data(bn);
         __builtin_amdgcn_sched_barrier(0);
         if (LOAD != FOLD) load_data(R, next(k, 4));
@@ -591,11 +606,11 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
     align_tail(R0, 0);
     align_tail(R1, next(0, 1));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) rotate1(R0, i, 0, false);
+    for (int i = 0; i < 4 * PQ; ++i) rotate1(R0, i, 0, false);
     store_data(0);
     load_rot(next(0, 1));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) rotate1(LOAD == FOLD ? R0 : R1, i, next(0, 1), true);
+    for (int i = 0; i < 4 * PQ; ++i) rotate1(LOAD == FOLD ? R0 : R1, i, next(0, 1), true);
     store_data(1);
     load_data(R0, next(0, 2));
     if (LOAD != FOLD) load_data(R1, next(0, 3));
@@ -644,8 +659,8 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
     }
     // The sums become the outputs in place: Fq, Fu of column cp in acc[g][0],
     // acc[g][2], of column cm in acc[g][1], acc[g][3].
-    const int cp = COLS ? 64 * wave + col : NH + 32 * wave + col;            // +h
-    const int cm = COLS ? 64 * wave + 32 + col : NH - 1 - 32 * wave - col;  // -h
+    const int cp = COLS ? 64 * wave + col : nh + 32 * wave + col;            // +h
+    const int cm = COLS ? 64 * wave + 32 + col : nh - 1 - 32 * wave - col;  // -h
     if constexpr (COLS) {
 #pragma unroll
         for (int g = 0; g < MG; ++g) {
@@ -682,6 +697,7 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
         r[cm] = m;
     };
     auto put_all = [&](auto&& value) __attribute__((always_inline)) {
+        if (!COLS && 32 * wave >= nh) return;
 #pragma unroll
         for (int g = 0; g < MG; ++g)
 #pragma unroll
@@ -792,7 +808,7 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
 //     split: c hi, c lo, s hi, s lo of the channel octet lane >> 5;
 //     FP32:  c, s of quad lane >> 5, then c, s of quad 2 + (lane >> 5).
 __global__ void mirror_tables_kernel(const double* __restrict__ bj, const float* __restrict__ wj,
-                                     int nchan_pad, int nk, int ftiles, double phi0, double dphi,
+                                     int nchan_pad, int nk, int ftiles, int tile, double phi0, double dphi,
                                      double K, float2* __restrict__ base, uint4* __restrict__ Tbf,
                                      uint4* __restrict__ Thf, uint4* __restrict__ Tf32)
 {
@@ -830,7 +846,7 @@ __global__ void mirror_tables_kernel(const double* __restrict__ bj, const float*
     if (idx < (int64_t)ftiles * nchan_pad) {
         const int tt = (int)(idx / nchan_pad), j = (int)(idx % nchan_pad);
         float c, s;
-        phase_cos_sin((phi0 + ((double)tt * kMirrorTile + (NH - 0.5)) * dphi) * bj[j], c, s);
+        phase_cos_sin((phi0 + ((double)tt * tile + (tile / 2 - 0.5)) * dphi) * bj[j], c, s);
         const float kw = (float)(K * (double)wj[j]);
         base[idx] = make_float2(kw * c, kw * s);
     }
@@ -944,12 +960,16 @@ hipError_t launch(const rmsynth_plan_s& p, const ExecArgs& a)
     constexpr int sub = tiles_per_wg(LOAD, NW), rows = 32 * MG * sub;  // LOS per workgroup
     const int64_t blocks = (a.nlos + rows - 1) / rows * tiles_n;
     if (blocks <= 0) return hipSuccess;
+    const bool rows_one = LOAD == LOAD_ONE && a.layout == RMSYNTH_LOS_MAJOR;  // below 4 channels
+    const int64_t ld = rows_one ? 1 : a.ld;
+    const int ls = rows_one ? p.nchan : 1;
     const uint4* T = PREC == RMSYNTH_FP32 ? p.d_Tf32 : PREC == RMSYNTH_SPLIT_FP16 ? p.d_Thf : p.d_Tbf;
 #define RMS_LAUNCH(G, P)                                                                                    \
     hipLaunchKernelGGL((synth_mirrored_kernel<LOAD, PREC, G, P, MG, NW>), dim3((unsigned)blocks),            \
-                       dim3(64 * NW * sub), 0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_base, T, p.nchan_pad, \
+                       dim3(64 * NW * sub), 0, a.stream, a.Q, a.U, a.nlos, ld, p.nchan, p.d_base, T, p.nchan_pad, \
                        nk, p.nphi, tiles_n, a.Fq, a.Fu, a.Fabs, a.los_scale, a.peak_part, a.peak_part_ld,     \
-                       a.peak_rec, 4 * p.nphi_pad, p.ksteps, p.kpad, p.d_kbase, p.d_krot)
+                       a.peak_rec, 4 * p.nphi_pad, p.ksteps, p.kpad, p.d_kbase, p.d_krot, ls,                 \
+                       mirror_tile(p) / 2)
 #define RMS_LAUNCH_P(G)                                                               \
     do {                                                                              \
         if constexpr (PREC != RMSYNTH_FP32 && LOAD != FOLD) { /* elsewhere peaks are a kernel of their own */ \
@@ -1011,18 +1031,31 @@ hipError_t launch_cols(const rmsynth_plan_s& p, const ExecArgs& a)
     return narrow ? launch_mg<LOAD, PREC, 2>(p, a) : launch_mg<LOAD, PREC, 4>(p, a);
 }
 
+// Mirrored pairs.  Grids of at most 128 phi are one tile of 64 pairs: on two waves,
+// in pairs of tiles, or, where that would leave the chip short of waves, on the
+// first two of the four (the others pack; the values are the same).  With tiles
+// of 128 pairs on four waves, 262144 LOS x 24 ch x 20 phi took, bf16x3 61 us, FP32
+// 110 (now 39 and 62), 131072 x 128 x 100 bf16x3 69 (50), 4096 x 400 x 100 bf16x3
+// 15 (19 on two waves).
+template <int LOAD, int PREC>
+hipError_t launch_pairs(const rmsynth_plan_s& p, const ExecArgs& a)
+{
+    const int64_t waves = (a.nlos + 63) / 64 * 4;
+    return mirror_tile(p) == 128 && waves > kSmallWaves ? launch_mg<LOAD, PREC, 2>(p, a)
+                                                                         : launch_mg<LOAD, PREC, 4>(p, a);
+}
+
 template <int PREC>
 hipError_t launch_load(const rmsynth_plan_s& p, const ExecArgs& a)
 {
     const bool planes = a.layout != RMSYNTH_LOS_MAJOR;
     if (p.cuniform) return launch_cols<FOLD, PREC>(p, a);
     if (p.etab) return planes ? launch_cols<TAB_PLANE, PREC>(p, a) : launch_cols<TAB_ROW, PREC>(p, a);
-    if (planes) return launch_mg<LOAD_PLANE, PREC, 4>(p, a);
+    if (planes || p.nchan < 4) return launch_pairs<LOAD_ONE, PREC>(p, a);
     // Quads of any alignment: with single values, 10007 LOS x 333 ch x 777 phi took
     // 80 us in bf16x3 (now 60) and 165 in FP32 (145), 65536 LOS 405 (297) and 819
     // (711).  The move of the row's last quad costs 1 %, so 4 n channels go without.
-    if (p.nchan < 4) return launch_mg<LOAD_ROW, PREC, 4>(p, a);
-    return p.nchan % 4 ? launch_mg<LOAD_TAIL, PREC, 4>(p, a) : launch_mg<LOAD_ROW4, PREC, 4>(p, a);
+    return p.nchan % 4 ? launch_pairs<LOAD_TAIL, PREC>(p, a) : launch_pairs<LOAD_ROW4, PREC>(p, a);
 }
 
 }  // namespace
@@ -1039,7 +1072,7 @@ hipError_t launch_mirror_tables(const rmsynth_plan_s& p, hipStream_t stream)
     const int nk = (p.nchan + KC - 1) / KC;
     const int64_t n = std::max<int64_t>((int64_t)nk * 256, (int64_t)p.ftiles * p.nchan_pad);
     hipLaunchKernelGGL(mirror_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                       p.d_b, p.d_w, p.nchan_pad, nk, p.ftiles, p.phi0, p.dphi, p.K, p.d_base, p.d_Tbf,
+                       p.d_b, p.d_w, p.nchan_pad, nk, p.ftiles, mirror_tile(p), p.phi0, p.dphi, p.K, p.d_base, p.d_Tbf,
                        p.d_Thf, p.d_Tf32);
     return hipGetLastError();
 }
