@@ -231,74 +231,91 @@ hipError_t launch_t(const rmsynth_plan_s& p, const ExecArgs& a)
 // 65504), so hi and lo stay normal down to 2^-10 of the LOS's largest value.
 // Non-finite values are ignored (they poison their LOS anyway).
 //
-// What bounds it: HBM reads, if enough are in flight.  LOS-major, a wave takes a
-// row, 8 loads at a time.  Frequency-major, the WAVES waves of a workgroup share
-// the channels of 64 LOS, 16 loads at a time: with one thread per LOS over all
-// channels a transform of 4096 LOS x 800 ch x 1001 phi took 280 us in all (now 54),
-// 65536 954 (717), 262144 3007 (2856).
-template <int LAYOUT, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void los_scale_kernel(const float* __restrict__ Q,
-                                                               const float* __restrict__ U,
-                                                               int64_t nlos, int64_t ld, int nchan,
-                                                               const float* __restrict__ wj, float K,
-                                                               float* __restrict__ scale)
+// What bounds it: HBM reads, if enough are in flight.  LOS-major, a row is shared
+// by `lanes` lanes (a power of two, at most 64) with N loads in flight each: rows
+// of up to 64 channels take one load a lane, 131072 LOS x 7 ch x 201 phi 46 us in all
+// (68 with 64 lanes and four loads for every row).  Frequency-major, the WAVES waves
+// of a workgroup share the channels of 64 LOS, 16 loads at a time: with one thread
+// per LOS over all channels a transform of 4096 LOS x 800 ch x 1001 phi took 280 us
+// in all (now 54), 65536 954 (717), 262144 3007 (2856).
+__device__ __forceinline__ float los_max(float m, float q, float u, float w)
 {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    float m = 0.0f;
-    // (a channel past the end reads the last one again)
-    auto take = [&](float q, float u, float w) {
-        const float v = w * __builtin_fmaxf(__builtin_fabsf(q), __builtin_fabsf(u));
-        m = v <= 3.0e38f ? __builtin_fmaxf(m, v) : m;
-    };
-    int64_t l;
-    if constexpr (LAYOUT == RMSYNTH_LOS_MAJOR) {
-        l = (int64_t)blockIdx.x * WAVES + wave;
-        if (l >= nlos) return;
-        for (int j0 = lane; j0 < nchan; j0 += 256) {
-            float q[4], u[4], w[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int j = j0 + 64 * i < nchan ? j0 + 64 * i : nchan - 1;
-                q[i] = Q[l * ld + j];
-                u[i] = U[l * ld + j];
-                w[i] = wj[j];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) take(q[i], u[i], w[i]);
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off, 64));
-        if (lane != 0) return;
-    } else {
-        __shared__ float part[WAVES][64];
-        l = (int64_t)blockIdx.x * 64 + lane;
-        const int64_t lc = l < nlos ? l : nlos - 1;
-        for (int j0 = 8 * wave; j0 < nchan; j0 += 8 * WAVES) {
-            float q[8], u[8], w[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int j = j0 + i < nchan ? j0 + i : nchan - 1;
-                q[i] = Q[(int64_t)j * ld + lc];
-                u[i] = U[(int64_t)j * ld + lc];
-                w[i] = wj[j];
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) take(q[i], u[i], w[i]);
-        }
-        part[wave][lane] = m;
-        __syncthreads();
-        if (wave != 0 || l >= nlos) return;
-#pragma unroll
-        for (int i = 1; i < WAVES; ++i) m = __builtin_fmaxf(m, part[i][lane]);
-    }
-    m *= K;
+    const float v = w * __builtin_fmaxf(__builtin_fabsf(q), __builtin_fabsf(u));
+    return v <= 3.0e38f ? __builtin_fmaxf(m, v) : m;
+}
+
+__device__ __forceinline__ float los_scale_of(float m)
+{
     int e = 0;
     if (m > 0.0f) {
         (void)__builtin_frexpf(m, &e);  // m < 2^e
         e = 13 - e;
         e = e < -100 ? -100 : (e > 100 ? 100 : e);
     }
-    scale[l] = __builtin_ldexpf(1.0f, e);
+    return __builtin_ldexpf(1.0f, e);
+}
+
+// (In both kernels a channel past the end reads the last one again.)
+template <int N>
+__global__ __launch_bounds__(256) void los_scale_rows_kernel(const float* __restrict__ Q,
+                                                             const float* __restrict__ U, int64_t nlos,
+                                                             int64_t ld, int nchan, int shift,
+                                                             const float* __restrict__ wj, float K,
+                                                             float* __restrict__ scale)
+{
+    if (N > 1) shift = 6;  // a row per wave, known to be
+    const int lanes = 1 << shift;
+    const int64_t l = N > 1 ? (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
+                            : ((int64_t)blockIdx.x * 256 + threadIdx.x) >> shift;
+    const int64_t lc = l < nlos ? l : nlos - 1;
+    const int first = threadIdx.x & (lanes - 1);
+    float m = 0.0f;
+    for (int j0 = first; j0 < nchan; j0 += N * lanes) {
+        float q[N], u[N], w[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int j = j0 + lanes * i < nchan ? j0 + lanes * i : nchan - 1;
+            q[i] = Q[lc * ld + j];
+            u[i] = U[lc * ld + j];
+            w[i] = wj[j];
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) m = los_max(m, q[i], u[i], w[i]);
+    }
+    for (int off = lanes >> 1; off > 0; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off, 64));
+    if (first == 0 && l < nlos) scale[l] = los_scale_of(m * K);
+}
+
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void los_scale_planes_kernel(const float* __restrict__ Q,
+                                                                      const float* __restrict__ U,
+                                                                      int64_t nlos, int64_t ld, int nchan,
+                                                                      const float* __restrict__ wj, float K,
+                                                                      float* __restrict__ scale)
+{
+    __shared__ float part[WAVES][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t l = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t lc = l < nlos ? l : nlos - 1;
+    float m = 0.0f;
+    for (int j0 = 8 * wave; j0 < nchan; j0 += 8 * WAVES) {
+        float q[8], u[8], w[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int j = j0 + i < nchan ? j0 + i : nchan - 1;
+            q[i] = Q[(int64_t)j * ld + lc];
+            u[i] = U[(int64_t)j * ld + lc];
+            w[i] = wj[j];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m = los_max(m, q[i], u[i], w[i]);
+    }
+    part[wave][lane] = m;
+    __syncthreads();
+    if (wave != 0 || l >= nlos) return;
+#pragma unroll
+    for (int i = 1; i < WAVES; ++i) m = __builtin_fmaxf(m, part[i][lane]);
+    scale[l] = los_scale_of(m * K);
 }
 
 }  // namespace
@@ -316,13 +333,21 @@ hipError_t launch_los_scale(const rmsynth_plan_s& p, const ExecArgs& a)
     // split; the per-element split kernel applies it in the epilogue, so its
     // scale ignores K (K = 1 in the folded adjoint plans).
     const float k = (p.uniform || p.etab) ? (float)p.K : 1.0f;
-#define RMS_SCALE(LAYOUT, WAVES, ROWS)                                                               \
-    hipLaunchKernelGGL((los_scale_kernel<LAYOUT, WAVES>), dim3((unsigned)((a.nlos + ROWS - 1) / ROWS)), \
-                       dim3(64 * WAVES), 0, a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, p.d_w, k, a.los_scale)
-    // 16 waves where 4 would leave the chip short of loads (65536 LOS: 4096 waves)
-    if (a.layout == RMSYNTH_LOS_MAJOR) RMS_SCALE(RMSYNTH_LOS_MAJOR, 4, 4);
-    else if (a.nlos > 65536) RMS_SCALE(RMSYNTH_FREQ_MAJOR, 4, 64);
-    else RMS_SCALE(RMSYNTH_FREQ_MAJOR, 16, 64);
+#define RMS_SCALE(KERNEL, THREADS, ROWS, ...)                                                    \
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)((a.nlos + ROWS - 1) / ROWS)), dim3(THREADS), 0,   \
+                       a.stream, a.Q, a.U, a.nlos, a.ld, p.nchan, ##__VA_ARGS__, p.d_w, k, a.los_scale)
+    if (a.layout == RMSYNTH_LOS_MAJOR) {
+        int shift = 0;  // log2 of the lanes per row
+        while (shift < 6 && 1 << shift < p.nchan) ++shift;
+        const int rows = 256 >> shift;
+        if (p.nchan <= 64) RMS_SCALE(los_scale_rows_kernel<1>, 256, rows, shift);
+        else if (p.nchan <= 128) RMS_SCALE(los_scale_rows_kernel<2>, 256, rows, shift);
+        else RMS_SCALE(los_scale_rows_kernel<4>, 256, rows, shift);
+    } else if (a.nlos > 65536) {  // 16 waves where 4 would leave the chip short of loads (65536 LOS: 4096 waves)
+        RMS_SCALE(los_scale_planes_kernel<4>, 256, 64);
+    } else {
+        RMS_SCALE(los_scale_planes_kernel<16>, 1024, 64);
+    }
 #undef RMS_SCALE
     return hipGetLastError();
 }
