@@ -165,8 +165,12 @@ int build_adjoint_plan(rmsynth_plan_s* p, const double* lambda2, const double* p
     // (same phase tolerance, now over every output lambda^2).
     double gmax = 0.0, phi0 = 0.0, dphi = 0.0;
     for (int32_t j = 0; j < p->nchan; ++j) gmax = std::max(gmax, std::fabs(hgrid[j]));
-    // (one phi has no neighbour to be read with)
-    if (p->nphi < 2 || !detect_uniform(phi, p->nphi, gmax, &phi0, &dphi)) return build_etable(q);
+    // One phi has no neighbour to be read with; up to half of the 32 that folding
+    // contracts at least, the table's steps of 8 pad less where a row is one tile of
+    // outputs (131072 LOS x 10 phi -> 100 channels bf16x3 34 us folded, 26 from the
+    // table; 16 -> 300 channels 91 and 100).
+    const bool few = p->nphi < 2 || (p->nphi <= kMirrorChan && p->nchan <= kMirrorTile);
+    if (few || !detect_uniform(phi, p->nphi, gmax, &phi0, &dphi)) return build_etable(q);
     q->cuniform = true;
     q->kb0 = phi0 / M_PI;
     q->kdb = dphi / M_PI;
