@@ -1024,9 +1024,12 @@ hipError_t launch_cols(const rmsynth_plan_s& p, const ExecArgs& a)
         // units of a half-height one (launch_mg); narrow ones take 17/16 (FP32) or
         // 19/16 (split) of a wide one's.  256 channels x 300 phi, wide and narrow:
         // 8192 LOS bf16x3 24 and 26 us, FP32 68 and 71; 65536 LOS 163 and 148,
-        // 511 and 396; 880 phi bf16x3 342 and 346.
+        // 511 and 396; 880 phi bf16x3 342 and 346.  With few channels the stores take
+        // longest, which wide tiles make in longer pieces (131072 x 24 x 600 bf16x3
+        // 163 wide, 185 narrow).
         auto rounds = [](int64_t full) { return full <= 128 ? 1 : 2 * ((full + 255) / 256); };
-        narrow = narrow && (PREC == RMSYNTH_FP32 ? 17 : 19) * rounds((tiles + 1) / 2 * n128) < 16 * rounds(tiles * n256);
+        narrow = narrow && (n128 == 1 || p.nchan >= 64) &&
+                 (PREC == RMSYNTH_FP32 ? 17 : 19) * rounds((tiles + 1) / 2 * n128) < 16 * rounds(tiles * n256);
     }
     return narrow ? launch_mg<LOAD, PREC, 2>(p, a) : launch_mg<LOAD, PREC, 4>(p, a);
 }
@@ -1035,7 +1038,7 @@ hipError_t launch_cols(const rmsynth_plan_s& p, const ExecArgs& a)
 // in pairs of tiles, or, where that would leave the chip short of waves, on the
 // first two of the four (the others pack; the values are the same).  With tiles
 // of 128 pairs on four waves, 262144 LOS x 24 ch x 20 phi took, bf16x3 61 us, FP32
-// 110 (now 39 and 62), 131072 x 128 x 100 bf16x3 69 (50), 4096 x 400 x 100 bf16x3
+// 110 (now 39 and 62), 131072 x 128 x 100 bf16x3 72 (57), 4096 x 400 x 100 bf16x3
 // 15 (19 on two waves).
 template <int LOAD, int PREC>
 hipError_t launch_pairs(const rmsynth_plan_s& p, const ExecArgs& a)
