@@ -30,6 +30,7 @@
 #include <vector>
 
 #include "common.h"
+#include "nufft_grid.h"
 
 namespace {
 
@@ -103,23 +104,9 @@ int build_nufft_tables(rmsynth_plan_s* p, const double* lambda2, const double* w
             if (std::fabs(d) < alpha) lists[pp].push_back({j, (float)psi(d)});
         }
     }
-    // The widest cyclic run of empty points ends where the stretch starts.
-    int p0 = 0, gap = 0;
-    for (int pp = 0, run = 0; pp < 2 * n; ++pp) {
-        if (lists[pp % n].empty()) {
-            if (++run > gap && run <= n) {
-                gap = run;
-                p0 = (pp + 1) % n;
-            }
-        } else {
-            run = 0;
-        }
-    }
-    const int span = n - gap;
-    int b1 = 0;
-    if (span <= (n >> 6) && (n >> 6) >= 16) b1 = 6;
-    else if (span <= (n >> 3) && (n >> 3) >= 16) b1 = 3;
-    if (!b1) p0 = 0;
+    std::vector<bool> occupied(n);
+    for (int pp = 0; pp < n; ++pp) occupied[pp] = !lists[pp].empty();
+    const auto [b1, p0] = nufft_stretch(occupied);
     // Filling entries name a channel of the point itself (or, for a point
     // without any, one of non-zero weight), so that they add 0 unless that
     // channel is not finite and spoils the line of sight anyway.
