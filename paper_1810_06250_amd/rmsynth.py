@@ -199,16 +199,16 @@ def _need_bytes(ws, nbytes):
 
 class PlanHandle(ctypes.c_void_p):
     """rmsynth_plan_t with the sizes its plan was made for, which every call
-    checks its tensors against."""
+    checks its tensors against: (pointer, nchan, nphi)."""
     dims = None
 
 
 def _plan_dims(plan):
     dims = getattr(plan, "dims", None)
-    if dims is None:  # a bare pointer
+    if dims is None or dims[0] != plan.value:  # a bare pointer, or a handle that was given another plan
         info = rmsynth_plan_info(plan)
-        dims = info["nchan"], info["nphi"]
-    return dims
+        return info["nchan"], info["nphi"]
+    return dims[1:]
 
 
 # ------------------------------------------------------------------ C-ABI names
@@ -220,7 +220,7 @@ def rmsynth_plan(lambda2, weights, phi, lambda0_sq: float = float("nan")) -> cty
     _check("rmsynth_plan", load_library().rmsynth_plan(
         lam.ctypes.data_as(_P), w.ctypes.data_as(_P), lam.size, ph.ctypes.data_as(_P), ph.size,
         float(lambda0_sq), ctypes.byref(h)))
-    h.dims = lam.size, ph.size
+    h.dims = h.value, lam.size, ph.size
     return h
 
 
