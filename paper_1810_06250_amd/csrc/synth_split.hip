@@ -320,8 +320,6 @@ __global__ __launch_bounds__(64 * WAVES) void los_scale_planes_kernel(const floa
 
 }  // namespace
 
-int64_t split_los_per_tile() { return MT; }
-
 hipError_t launch_synth_split(const rmsynth_plan_s& p, const ExecArgs& a, int precision)
 {
     return precision == RMSYNTH_SPLIT_FP16 ? launch_t<true>(p, a) : launch_t<false>(p, a);

@@ -85,3 +85,22 @@ def test_fused_peaks(prec, layout, shape):
         np.testing.assert_array_equal(host(pk[k]), out[k], err_msg=k)
     assert out["idx"][3] == -1
     plan.close()
+
+
+@pytest.mark.parametrize("prec", list(rs.PRECISIONS))
+@pytest.mark.parametrize("nlos,nchan,nphi", [(40, 90, 77), (8257, 128, 33), (16400, 65, 20)])
+def test_adjoint_onto_uniform_channels(prec, nlos, nchan, nphi):
+    """Channels uniform in lambda^2 are the adjoint's uniform grid."""
+    note(f"short grid of channels {nlos} x {nchan} x {nphi} {prec}")
+    lam = np.linspace(0.03, 0.19, nchan)
+    phi = -50.0 + 3.1 * np.arange(nphi)
+    C = np.float32(np.random.default_rng(nchan).standard_normal((2, nlos, nphi)))
+    plan = rs.Plan(lam, np.ones(nchan), phi)
+    Pq, Pu = plan.adjoint(dev32(C[0]), dev32(C[1]), rs.PRECISIONS[prec])
+    pick = np.unique(np.r_[0:min(nlos, 70), max(0, nlos - 70):nlos])
+    D = C[:, pick].astype(np.float64)
+    rq, ru = oracle.adjoint(D[0], D[1], lam, np.ones(nchan), phi)
+    err = np.hypot(host(Pq)[pick] - rq, host(Pu)[pick] - ru).max(1)
+    size = np.maximum(np.hypot(rq, ru).max(1), np.sqrt((D ** 2).sum((0, 2))))
+    assert np.max(err / size) <= SCALE_TOL[prec]
+    plan.close()
