@@ -137,10 +137,11 @@ int rmsynth_rmsf(rmsynth_plan_t plan, float* R_re, float* R_im, void* stream);
  * power-of-two scale in the workspace (any phi grid); the workspace is
  * overwritten, and calls that share one workspace must not overlap.
  * On a uniform phi grid every precision evaluates mirrored pairs of depths
- * from plan-time tables.  On other grids the split precisions use a plan-time
- * table of the whole split phase matrix when it holds at most 256 MiB (nchan
- * x nphi up to about 1.6e7); beyond that, and in FP32, the phases are
- * generated per element.  The results agree to the same bounds.
+ * from plan-time tables.  On other grids every precision reads the whole phase
+ * matrix from a plan-time table when its two split forms hold at most 256 MiB
+ * (nchan x nphi up to about 1.6e7; with the FP32 form the table takes 1.5 times
+ * as much device memory), and generates the phases per element beyond that.
+ * The results agree to the same bounds.
  * Errors: EINVAL (NULL buffers with nlos > 0, bad layout/precision, wrong
  * device current), EWORKSPACE, EHIP (launch failure).
  */
@@ -243,8 +244,10 @@ size_t rmsynth_search_noalloc_scratch_bytes(void);
  *   precision  any rmsynth_precision.  Plan-time tables serve channels
  *            uniform in lambda^2 (as on a uniform phi grid of the forward
  *            transform) and uniform phi grids (mirrored pairs of phi folded
- *            in K-tiles of at most 256, combined by Horner's rule); otherwise
- *            as rmsynth_execute on other grids.
+ *            in K-tiles of at most 256, combined by Horner's rule); otherwise,
+ *            and onto at most 256 channels from at most 16 phi, as
+ *            rmsynth_execute on other grids, with a table of the plan's own
+ *            under the same cap.
  *   workspace  rmsynth_adjoint_workspace_size() bytes (0 except FP16), or
  *            less down to its value for 128 LOS (batches).
  * Every channel gets a value (weights do not enter).  A LOS with a

@@ -29,8 +29,9 @@
 // registers, three for n / 2^B1 up to 4096, through LDS; the last one scales
 // its modes and stores them.
 //
-// What bounds it: VALU issue (64 % of the time at the first size below) and
-// the waits between the passes of a LOS.  Per launch, before (radix-16 passes
+// What bounds it: VALU issue (60 % of the time at the first size below,
+// SQ_ACTIVE_INST_VALU over SQ_BUSY_CU_CYCLES) and the waits between the passes of
+// a LOS.  Per launch, before (radix-16 passes
 // over the whole grid, one contiguous list of entries per point) and after:
 //   262144 LOS x 400 ch x 2001 phi, 1/8 of 4096 points    4.07 -> 2.66 ms
 //   262144 x 288 x 1201, 1/64 of 4096                     4.59 -> 1.88 ms

@@ -35,7 +35,8 @@
 //
 // Workgroup: 256 threads, 64 LOS x 256 phi, 16 channels per K-step.  Wave w
 // owns all 64 LOS and the pairs i = 32 w .. 32 w + 31 (64 phi): 2 LOS groups x
-// 4 sums (128 accumulators per lane), so two workgroups share a CU.  A wave's
+// 4 sums (128 accumulators per lane), so two workgroups share a CU (tiles of 128
+// columns: two such tiles of two waves).  A wave's
 // table columns are its own, so they go from L2 straight to registers, one
 // K-step ahead, in MFMA operand order (1 KB contiguous per load); LDS carries
 // only the packed data (8 KB per K-step, triple buffered).  Per K-step and
@@ -43,10 +44,11 @@
 // of 4 channels of 64 LOS.
 //
 // What bounds it: the matrix cores, at the clock the power limit leaves them.
-// 65536 LOS x 2001 phi, bf16x3, no F stored: 0.56 ms with 400 channels, 1.07
-// with 800, 2.04 with 1600, so the K-loop alone issues 1300 TFLOP/s (a library
-// bf16 GEMM of 16384^3 reaches 1375 on the same card) and a tile's start and
-// end cost 12 % at 400 channels.  Storing F adds 1.5 of 10.9 ms at 1024^2 LOS.
+// 65536 LOS x 2001 phi, bf16x3, no F stored: 0.54 ms with 400 channels, 1.06
+// with 800, 2.03 with 1600, so the K-loop alone issues 1290 TFLOP/s, 12 flop for
+// each of 2048 padded depths (a library bf16 GEMM of 16384^3 reaches 1375 on the
+// same card), and a tile's start and end cost 8 % at 400 channels.  Storing F
+// adds 1.5 of 10.9 ms at 1024^2 LOS.
 // Packing two K-steps between barriers (six LDS buffers) was 1-2 % slower;
 // centring a ragged last tile on what is left of the grid, so that waves with
 // no pairs skip the matrix work, gained nothing (the workgroup still waits for
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
     const int lr = row < left ? row : (int)left;
     const float lsc = PREC == RMSYNTH_SPLIT_FP16 ? los_scale[l0 + lr] : 1.0f;
     const int64_t lstride = LOAD == TAB_PLANE ? 1 : ONE ? ls : ld;
-    const uint32_t voff = 4u * (uint32_t)(lr * (int)lstride);  // < 2^24
+    const uint32_t voff = 4u * (uint32_t)(lr * (int)lstride);  // < 2^28: 63 rows of at most 2^20 values
     const float* const Qt = Q + l0 * lstride;
     const float* const Ut = U + l0 * lstride;
     const_f4_ptr bt = (const_f4_ptr)(TAB ? base : base + (int64_t)tn * nchan_pad);
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(64 * NW * tiles_per_wg(LOAD, NW), 2) void synth_mir
 #pragma unroll
         for (int i = 0; i < IT; ++i) {
             const int r = rq + RT * i < left ? rq + RT * i : (int)left;
-            frow[i] = 4u * (uint32_t)(r * (int)ld);
+            frow[i] = 4u * (uint32_t)(r * (int)ld);  // < 2^28, as voff
             fsc[i] = PREC == RMSYNTH_SPLIT_FP16 ? los_scale[l0 + r] : 1.0f;
         }
     }
