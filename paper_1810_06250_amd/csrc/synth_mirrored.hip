@@ -1026,11 +1026,13 @@ hipError_t launch_cols(const rmsynth_plan_s& p, const ExecArgs& a)
         // units of a half-height one (launch_mg); narrow ones take 17/16 (FP32) or
         // 19/16 (split) of a wide one's.  256 channels x 300 phi, wide and narrow:
         // 8192 LOS bf16x3 24 and 26 us, FP32 68 and 71; 65536 LOS 163 and 148,
-        // 511 and 396; 880 phi bf16x3 342 and 346.  With few channels the stores take
-        // longest, which wide tiles make in longer pieces (131072 x 24 x 600 bf16x3
-        // 163 wide, 185 narrow).
+        // 511 and 396; 880 phi bf16x3 342 and 346.  With few channels the stores of F
+        // take longest, which wide tiles make in longer pieces (200000 LOS, wide and
+        // narrow: 24 ch x 600 phi bf16x3 248 and 287, 7 x 300 FP32 157 and 174, but
+        // 17 x 300 219 and 182); the search stores none (12 x 300 98 and 85).
         auto rounds = [](int64_t full) { return full <= 128 ? 1 : 2 * ((full + 255) / 256); };
-        narrow = narrow && (n128 == 1 || p.nchan >= 64) &&
+        const int few = a.peak_rec ? 0 : PREC == RMSYNTH_FP32 ? 16 : 64;
+        narrow = narrow && (n128 == 1 || p.nchan >= few) &&
                  (PREC == RMSYNTH_FP32 ? 17 : 19) * rounds((tiles + 1) / 2 * n128) < 16 * rounds(tiles * n256);
     }
     return narrow ? launch_mg<LOAD, PREC, 2>(p, a) : launch_mg<LOAD, PREC, 4>(p, a);
