@@ -140,8 +140,9 @@ int rmsynth_rmsf(rmsynth_plan_t plan, float* R_re, float* R_im, void* stream);
  * from plan-time tables.  On other grids every precision reads the whole phase
  * matrix from a plan-time table when its two split forms hold at most 256 MiB
  * (nchan x nphi up to about 1.6e7; with the FP32 form the table takes 1.5 times
- * as much device memory), and generates the phases per element beyond that.
- * The results agree to the same bounds.
+ * as much device memory), and generates the phases per element beyond that;
+ * so does FP32 on few channels and few phi (at most 24 and 96).  The results
+ * agree to the same bounds.
  * Errors: EINVAL (NULL buffers with nlos > 0, bad layout/precision, wrong
  * device current), EWORKSPACE, EHIP (launch failure).
  */
@@ -247,7 +248,8 @@ size_t rmsynth_search_noalloc_scratch_bytes(void);
  *            in K-tiles of at most 256, combined by Horner's rule); otherwise,
  *            and onto at most 256 channels from at most 16 phi, as
  *            rmsynth_execute on other grids, with a table of the plan's own
- *            under the same cap.
+ *            under the same cap.  FP32 from at most 24 phi may generate its
+ *            phases (from 16, onto at most 640 channels).
  *   workspace  rmsynth_adjoint_workspace_size() bytes (0 except FP16), or
  *            less down to its value for 128 LOS (batches).
  * Every channel gets a value (weights do not enter).  A LOS with a

@@ -424,6 +424,20 @@ int batch_size(const rmsynth_plan_s* p, Mode mode, int32_t precision, int64_t nl
     return RMSYNTH_OK;
 }
 
+// FP32 calls of few channels and few phi go to the kernel that generates its
+// phases (its K-steps are 8 channels, and its workgroups leave room for more of
+// them on a CU): 200000 LOS x 5 ch x 9 phi 41 us from the tables, 28 generated; 8 x 96
+// 44 and 40, 8 x 128 43 and 49, 16 x 9 uniform 41 and 45, irregular 56 and 43, 24 x 32
+// irregular 65 and 61, x 48 68 and 66; folded, 12 phi onto 300 channels 190 and 184,
+// 5 onto 520 281 and 214, onto 700 314 and 336, 24 onto 9 64 and 60.  Smaller calls
+// differ less.
+bool few_phases(const rmsynth_plan_s* p)
+{
+    if (p->uniform) return p->nchan <= 8 && p->nphi <= 96;
+    const int32_t most = p->cuniform ? 640 : p->nchan <= 8 ? 96 : 64;  // up to 16 channels
+    return p->nchan <= 16 ? p->nphi <= most : p->nchan <= 24 && p->nphi <= 32;
+}
+
 // The transform of one batch of n LOS starting at LOS l0 of the call, in
 // launches whose grids stay within the dispatch limit (tiles of at least 64
 // LOS of 256 threads).  ld is the call's row stride (LOS-major: nchan) or
@@ -464,8 +478,9 @@ int run_execute(const rmsynth_plan_s* p, const float* Q, const float* U, int64_t
             if (e != hipSuccess) return rms_hip_fail(e, who);
         }
         hipError_t e;
-        if (p->uniform || p->cuniform || p->etab) e = launch_synth_mirrored(*p, a, precision);
-        else if (precision == RMSYNTH_FP32) e = launch_synth_fp32(*p, a);
+        const bool tables = p->uniform || p->cuniform || p->etab;
+        if (precision == RMSYNTH_FP32 && (!tables || few_phases(p))) e = launch_synth_fp32(*p, a);
+        else if (tables) e = launch_synth_mirrored(*p, a, precision);
         else e = launch_synth_split(*p, a, precision);
         if (e != hipSuccess) return rms_hip_fail(e, who);
         b0 += m;
